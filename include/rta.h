@@ -110,15 +110,18 @@ typedef struct rta_info {
     int64_t spectra_bytes;        /* filter spectra resident in HBM        */
     int64_t device_bytes;         /* all device memory held by the context */
     double  h_bytes_per_block;    /* filter-spectrum bytes streamed per
-                                     block, averaged over the tier phases  */
+                                     block, averaged over the tier phases
+                                     (under uniform partitions a far row is
+                                     read once for eight blocks)           */
     double  x_bytes_per_block;    /* input-spectrum (FDL) bytes read per
-                                     block, counted once per (q, slot)     */
+                                     block, counted once per (q, slot)
+                                     that the block's rows pair with       */
     double  io_bytes_per_block;   /* input block + output block bytes      */
     double  cmacs_per_block;      /* complex multiply-accumulates / block  */
     double  tail_bytes_per_block; /* algorithmic bytes of the multiply-
-                                     accumulate kernel (partitions >= 1):
-                                     their spectrum rows once plus their
-                                     delay-line slots once per input       */
+                                     accumulate kernel (partitions >= 2):
+                                     the spectrum rows it streams plus
+                                     their delay-line slots per input      */
     int32_t grid;                 /* workgroups per block launch           */
     int32_t outputs_per_group;    /* outputs sharing one input-spectrum
                                      load in the multiply-accumulate       */
@@ -141,8 +144,9 @@ typedef struct rta_info {
     int64_t host_slowest_call;
     double  host_slowest_us;
     int64_t host_late_waits;
-    int32_t bin_slices;           /* first-tier items per partition row,
-                                     each over 1/bin_slices of the bins:
+    int32_t bin_slices;           /* first-tier items per partition row
+                                     (per row read every block), each over
+                                     1/bin_slices of the bins:
                                      rta_tuning's, or chosen when a long
                                      filter feeds few outputs (the partial
                                      slots per output group are capped so
@@ -188,7 +192,10 @@ int rta_create(rta_ctx** out, double fs, int32_t block,
  *                      workgroup adds up from registers (16 per thread,
  *                      256 / (bins per row) threads per bin), where the
  *                      block size and inputs allow it.
- *   tail_rows          partitions per first-tier item; overrides tail_items.
+ *   tail_rows          partitions per first-tier item; overrides tail_items,
+ *                      and has every row read every block (else uniform
+ *                      partitions of 18 rows or more are read once for eight
+ *                      blocks from the ninth row on).
  *   tier_rows          partitions per later-tier item (default 16).
  *   bin_slices         S in {1, 2, 4, 8}: first-tier items cover 1/S of a
  *                      partition row's bins over S times more rows, so each

@@ -23,10 +23,13 @@
 //   tail workgroups (bandwidth bound): work item i covers a group of G
 //   outputs, one input, a partition range [p0, p1) with p0 >= 2 and a slice
 //   of bins, and writes sum_{p in [p0,p1)} H_{l,q,p} X_q[(n+1-p) mod K] for
-//   the NEXT block into its partial-sum slot.
+//   the NEXT block into its partial-sum slot.  Under uniform partitions the
+//   far ones (p > kTile) are read once in kTile launches, for kTile blocks at
+//   a time (mac_tile).
 //
-// Partial sums are double-buffered by block parity: launch n reads parity
-// n & 1 (heads) and writes parity (n+1) & 1 (tails).  The tails read ring
+// Partial sums are kept by block index, of 2 blocks (2 kTile when tiled):
+// launch n reads block n's (heads) and writes block n+1's, or those of blocks
+// n+1 .. n+kTile (tails).  The tails read ring
 // slots n-1 ... n+2-K, never slot n, which the heads write in the same
 // launch.  Each slot is written by exactly one item and read in a fixed
 // order, so results are reproducible bit for bit; the sum is the same as
@@ -48,6 +51,8 @@ constexpr int kUnroll = 4;  // rows in flight per lane, FP32 spectra (16-byte lo
 #endif
 constexpr int kUnroll16 = RTA_UNROLL16;  // rows in flight per lane, 16-bit spectra (8-byte loads)
 
+constexpr int kTile = 8;    // blocks that one reading of a far partition row serves
+
 enum ItemKind : int32_t {
   K_MAC = 0,    // tail: multiply-accumulate of a partition range
   K_NOP = 1,    // padding
@@ -57,7 +62,9 @@ enum ItemKind : int32_t {
   K_FFT_A = 2,  // input frame -> N2-point transforms of its columns
   K_FFT_B = 3,  // N1-point transforms of column pairs -> packed spectrum -> ring
   K_FIN_A = 4,  // partial sums of column pairs -> N1-point inverse transforms
-  K_FIN_B = 5   // N2-point inverse transforms of rows -> output ring
+  K_FIN_B = 5,  // N2-point inverse transforms of rows -> output ring
+  K_TILE = 6    // tail: multiply-accumulate of a far partition range for the
+                // next kTile blocks
 };
 
 struct Item {          // one workgroup's work in one block (96 bytes)
@@ -71,10 +78,11 @@ struct Item {          // one workgroup's work in one block (96 bytes)
   int32_t k0;          // K_MAC: first bin of the slice; tier passes: index of
                        // the item within its pass
   int32_t slot;        // partial-sum slot (tier-local)
-  int32_t acc;         // K_MAC of a later tier: add to the slot (0: store)
+  int32_t acc;         // K_MAC of a later tier: add to the slot (0: store);
+                       // K_TILE: its first output within the group
   int32_t lag;         // tiers >= 1: launch index minus the block in which
                        // the frame's input completed
-  int32_t nl;          // K_MAC: outputs of its group
+  int32_t nl;          // K_MAC: outputs of its group; K_TILE: its outputs (at most 2)
   // K_MAC, per output g of the group: the end of the partitions to read,
   // min(p1, partitions of pair (l0 + g, q)) (0: no path), and that pair's
   // first spectrum row.  Carried here so that a tail workgroup needs one
@@ -94,7 +102,7 @@ struct DevTier {
   const int64_t* pair_row;   // [L*Q] first row of pair (l,q), -1 = no path
   const int32_t* pair_K;     // [L*Q] partitions of pair (l,q)
   float2* X;                 // FDL ring [Q][K][P]
-  float2* partial;           // [2][slots][G][P], by block parity
+  float2* partial;           // [pmask + 1][slots][G][P], by block index
   const float2* tw;          // W_P^j (j<P) then W_2P^k (k<P)
   float* oring;              // tiers >= 1: output ring [L][R]
   float2* tfwd;              // tiers >= 1: forward column-pass results [Q][P]
@@ -105,7 +113,7 @@ struct DevTier {
   int32_t lg1;               // tiers >= 1: log2 N1, P = N1 N2, N1 <= N2
   int32_t r3;                // 1: P = 3 * 2^logP (the n_f = 3 n_x first tier:
                              // B-tap partitions, 3B-point transforms, 3B/2 bins)
-  int32_t pad5;
+  int32_t pmask;             // partial sums kept of pmask + 1 blocks
 };
 
 // Feedback convolution fused into the synthesis launch (Sec. III-A Eq. 3,
@@ -140,7 +148,7 @@ struct KArgs {
   int64_t hist_mask;         // hist_len - 1
   int64_t ring_mask;         // output ring length - 1
   int32_t B, Q, L, n_tiers;
-  int32_t n_phase, max_items;
+  int32_t n_phase, max_items; // work-list period (n_phase >= 1 lists), longest list
   int32_t head_nq;           // inputs transformed per pass by a head
   int32_t n_head;            // head workgroups (one per output)
   int32_t head_slots;        // head part of the grid (n_head rounded up to 8)
@@ -205,6 +213,13 @@ template <> struct HVec<float2> {
   // work, a converted load would make the wave wait for it at once)
   typedef float2 one_t;
   static __device__ __forceinline__ one_t load1_raw(const float2* p) { return *p; }
+  template <bool NT>
+  static __device__ __forceinline__ one_t load1_stream(const float2* p) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    if (!NT) return *p;
+    const f32x2 v = __builtin_nontemporal_load(reinterpret_cast<const f32x2*>(p));
+    return make_float2(v.x, v.y);
+  }
   static __device__ __forceinline__ float2 cvt1(one_t v) { return v; }
 };
 
@@ -236,6 +251,10 @@ template <> struct HVec<f16c_t> {
   static __device__ __forceinline__ float2 load1(const f16c_t* p) { return f16pair(p->bits); }
   typedef uint32_t one_t;
   static __device__ __forceinline__ one_t load1_raw(const f16c_t* p) { return p->bits; }
+  template <bool NT>
+  static __device__ __forceinline__ one_t load1_stream(const f16c_t* p) {
+    return NT ? __builtin_nontemporal_load(&p->bits) : p->bits;
+  }
   static __device__ __forceinline__ float2 cvt1(one_t v) { return f16pair(v); }
 };
 
@@ -255,6 +274,10 @@ template <> struct HVec<bf16c_t> {
   static __device__ __forceinline__ float2 load1(const bf16c_t* p) { return bf16pair(p->bits); }
   typedef uint32_t one_t;
   static __device__ __forceinline__ one_t load1_raw(const bf16c_t* p) { return p->bits; }
+  template <bool NT>
+  static __device__ __forceinline__ one_t load1_stream(const bf16c_t* p) {
+    return NT ? __builtin_nontemporal_load(&p->bits) : p->bits;
+  }
   static __device__ __forceinline__ float2 cvt1(one_t v) { return bf16pair(v); }
 };
 
@@ -391,6 +414,129 @@ __device__ __forceinline__ void mac_item(const DevTier& T, const Item& it, int64
     for (int s2 = 1; s2 < RP; ++s2) sum = cadd(sum, red[(s2 * G + g) * W + b]);
     float2* d = part + (int64_t)g * P + it.k0 + b;
     *d = it.acc ? cadd(*d, sum) : sum;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Far partitions, tiled in time.  Partition p >= kTile + 1 of block b pairs
+// with X(b - p), which exists kTile blocks before b does: one reading of its
+// row in launch n serves the blocks n + 1 .. n + kTile (their newest spectrum
+// is X(n + kTile - p), at most X(n - 1)).  Every far range is read in one of
+// kTile consecutive launches, so a launch streams 1/kTile of the far rows and
+// does the same multiply-accumulates as before.
+//
+// Lane -> (bin, run of rows): the item's W bins by kThreads / W runs of
+// consecutive rows.  Along a run the window of kTile spectra moves by one
+// slot per row, so a row costs one new spectrum load and one load per output
+// for 4 kTile multiply-adds per output; kTile rows are in flight per lane.
+// Bound by the VALU: 4 multiply-adds per (bin, row, block, output).  16-bit
+// spectra are converted once per row: left to itself the compiler folds the
+// conversion into every multiply-add (v_fma_mix_f32), which runs at half the
+// rate (1 -> 64 x 576,000 taps FP16: launch 13.8 -> 11.2 us).
+// Measured against reading every row every block (us per block, back to
+// back): 1 -> 32 x 480,000 taps FP32 21.5 -> 10.0 (then bound by the heads),
+// 1 -> 64 x 576,000 FP16 25.8 -> 12.9, block 2048 61.4 -> 43.1.
+// ---------------------------------------------------------------------------
+__host__ __device__ constexpr int tile_outputs(int G) { return G < 2 ? 1 : 2; }
+
+template <typename HT, int G, bool NT>
+__device__ __forceinline__ void mac_tile(const DevTier& T, const Item& it, int64_t n, float2* red) {
+  constexpr int GF = tile_outputs(G), M = kTile, U = kTile;
+  const int P = T.P, K = T.K, W = it.w;
+  const int lw = 31 - __builtin_clz(W);
+  const int tid = threadIdx.x;
+  const int r = tid & (W - 1), s = tid >> lw;
+  const int kb = it.k0 + r;
+  const int RP = kThreads >> lw;
+  const int per = (it.p1 - it.p0 + RP - 1) >> (8 - lw);  // rows per run
+  const int pa = min(it.p0 + s * per, it.p1), pe = min(it.p1, pa + per);
+  const HT* Hbase = reinterpret_cast<const HT*>(T.H);
+  const HT* hp[GF];
+  int left[GF];  // rows of the run still to read
+#pragma unroll
+  for (int g = 0; g < GF; ++g) {
+    const int end = g < it.nl ? min(it.pend[g], pe) : 0;
+    left[g] = max(end - pa, 0);
+    hp[g] = Hbase + ((g < it.nl ? it.row[g] : 0) + (left[g] > 0 ? pa : 0)) * (int64_t)P + kb;
+  }
+  float acc[GF][M][4];
+#pragma unroll
+  for (int g = 0; g < GF; ++g)
+#pragma unroll
+    for (int m = 0; m < M; ++m) acc[g][m][0] = acc[g][m][1] = acc[g][m][2] = acc[g][m][3] = 0.f;
+
+  // x[i] = X(n + 1 - (p + U - 1) + i): row p + u pairs block n + 1 + m with
+  // x[U - 1 - u + m]
+  const float2* Xq = T.X + (int64_t)it.q * K * P + kb;
+  int sl = wrap_slot(n + 1, K) - (pa + U - 1);
+  if (sl < 0) sl += K;
+  if (sl < 0) sl += K;
+  float2 x[U + M - 1];
+  {
+    int t = sl;
+#pragma unroll
+    for (int i = 0; i < U + M - 1; ++i) {
+      x[i] = Xq[(int64_t)t * P];
+      t = t + 1 == K ? 0 : t + 1;
+    }
+  }
+  for (int p = 0; p < per; p += U) {
+    typename HVec<HT>::one_t h[U][GF];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int g = 0; g < GF; ++g)  // (clamped: rows past the run are not used)
+        h[u][g] = HVec<HT>::template load1_stream<NT>(hp[g] + (int64_t)min(u, max(left[g] - 1, 0)) * P);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int g = 0; g < GF; ++g)
+        if (u < left[g]) {
+          const float2 hv = pin(HVec<HT>::cvt1(h[u][g]));
+#pragma unroll
+          for (int m = 0; m < M; ++m) {
+            const float2 xv = x[U - 1 - u + m];
+            acc[g][m][0] += hv.x * xv.x;
+            acc[g][m][1] += hv.y * xv.y;
+            acc[g][m][2] += hv.x * xv.y;
+            acc[g][m][3] += hv.y * xv.x;
+          }
+        }
+    if (p + U >= per) break;
+#pragma unroll
+    for (int g = 0; g < GF; ++g) {
+      left[g] = max(left[g] - U, 0);
+      if (left[g] > 0) hp[g] += U * P;
+    }
+    sl -= U;
+    if (sl < 0) sl += K;
+#pragma unroll
+    for (int i = M - 2; i >= 0; --i) x[U + i] = x[i];
+    int t = sl;
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      x[i] = Xq[(int64_t)t * P];
+      t = t + 1 == K ? 0 : t + 1;
+    }
+  }
+
+  // the runs' sums, added up in run order: red [run][g][m][W]
+  const int E = GF * M * W;
+#pragma unroll
+  for (int g = 0; g < GF; ++g)
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      const float* a = acc[g][m];
+      red[s * E + (g * M + m) * W + r] =
+          kb == 0 ? make_float2(a[0], a[1]) : make_float2(a[0] - a[1], a[2] + a[3]);
+    }
+  __syncthreads();
+  for (int e = tid; e < E; e += kThreads) {
+    const int b = e & (W - 1), gm = e >> lw, m = gm % M, g = gm / M;
+    if (g >= it.nl) break;
+    float2 sum = red[e];
+    for (int s2 = 1; s2 < RP; ++s2) sum = cadd(sum, red[s2 * E + e]);
+    T.partial[((((n + 1 + m) & T.pmask) * (int64_t)T.nslots + it.slot) * G + it.acc + g) * P + it.k0 + b] = sum;
   }
 }
 
@@ -784,7 +930,7 @@ __device__ __forceinline__ void head_work(const KArgs& A, int64_t n, const Group
   //    window's transform (step 2) where the shape allows, else done here
   const DevTier Tcur = [&] {
     DevTier t = T;
-    t.partial = T.partial + (n & 1) * (int64_t)T.nslots * G * P + (int64_t)gsel * P;
+    t.partial = T.partial + (n & T.pmask) * (int64_t)T.nslots * G * P + (int64_t)gsel * P;
     return t;
   }();
   HeadRed<HT> red;
@@ -1409,11 +1555,15 @@ __global__ __launch_bounds__(kThreads) void k_block(const KArgs A) {
   asm volatile("" ::"s"(T.H), "s"(T.X), "s"(T.partial), "s"(T.K), "s"(T.P), "s"(T.nslots));
   const Item it = A.items[(int64_t)phase * A.max_items + i];
   if (it.kind == K_NOP) return;
+  if (it.kind == K_TILE) {
+    mac_tile<HT, G, NT>(T, it, n, lds);
+    return;
+  }
   if (it.tier != 0) T = A.tier[it.tier];
   int64_t frame;
   if (it.tier == 0) {
     frame = n + 1;  // first-tier tails prepare the next block
-    T.partial += (frame & 1) * (int64_t)T.nslots * G * T.P;
+    T.partial += (frame & T.pmask) * (int64_t)T.nslots * G * T.P;
   } else {
     // later tier: the frame whose input completed in block n - lag
     frame = (n - it.lag + 1) / T.r - 1;

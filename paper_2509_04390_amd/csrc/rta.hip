@@ -21,9 +21,11 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <map>
 #include <mutex>
 #include <new>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "rta.h"
@@ -125,6 +127,9 @@ struct rta_ctx {
   int n_tiers = 0;
   TierHost tier[kMaxTiers];
   int G = 1, rows_per_item = 0, n_phase = 1, max_items = 0, n_items = 0;
+  int n_list = 1;              // work lists per phase period: n_phase, or kTile when tiled
+  bool tile_ok = true;         // far partitions may be tiled in time (see build_plan)
+  bool tiled = false;
   int tail_items = 512, tier_rows = 16;
   int max_group_slots = 0;     // first tier: the most partial slots of one output group
   int spectra_loads = 0;       // 0 default, 1 non-temporal, 2 ordinary
@@ -396,10 +401,13 @@ int validate(double fs, int32_t block, const rta_scheme* scheme, int32_t n_in, i
 
 // ---------------------------------------------------------------------------
 // Work lists.  The block index n selects phase n mod n_phase (n_phase =
-// P_max / B).  The tail list of a phase holds
+// P_max / B; kTile for uniform partitions tiled in time).  The tail list of a
+// phase holds
 //   - the first tier's tail items (every phase): partitions p >= 2 of every
 //     (output group, input), cut into chunks of about R rows and bin slices;
 //     each chunk owns one partial slot of its group (the heads do p = 0, 1);
+//   - tiled: those items for the partitions 2 .. kTile alone, and an eighth of
+//     the far chunks (p > kTile), each for the next kTile blocks at once;
 //   - the multiply-accumulate items of later tiers whose frame is being
 //     accumulated in that block.
 // The transform list of a phase holds the later tiers' transform passes
@@ -413,7 +421,7 @@ int validate(double fs, int32_t block, const rta_scheme* scheme, int32_t n_in, i
 // r - 1), or 1 with RTA_FLAG_SPIKE.
 // ---------------------------------------------------------------------------
 struct Bucket {
-  int tier, q, p0, k0;
+  int tier, q, p0, unit;
   std::vector<Item> items;
   int64_t rows = 0;
 };
@@ -461,16 +469,73 @@ std::vector<Item> place_on_xcds(std::vector<Bucket>& buckets) {
 // bytes): an XCD that streamed only one byte range of every row would reach
 // only part of the HBM channels (measured: the XCDs holding one slice of two
 // finished 3 us after the others).
-void add_to_bucket(std::vector<Bucket>& buckets, const Item& it, int nl) {
+void add_to_bucket(std::vector<Bucket>& buckets, const Item& it, int nl, int unit = 0) {
   auto bit = std::find_if(buckets.begin(), buckets.end(), [&](const Bucket& b) {
-    return b.tier == it.tier && b.q == it.q && b.p0 == it.p0;
+    return b.tier == it.tier && b.q == it.q && b.p0 == it.p0 && b.unit == unit;
   });
   if (bit == buckets.end()) {
-    buckets.push_back(Bucket{it.tier, it.q, it.p0, 0, {}, 0});
+    buckets.push_back(Bucket{it.tier, it.q, it.p0, unit, {}, 0});
     bit = buckets.end() - 1;
   }
   bit->items.push_back(it);
   bit->rows += (int64_t)(it.p1 - it.p0) * nl;
+}
+
+// Tiling of the far partitions (kernels.hpp, mac_tile): W bins by kThreads / W
+// runs of rows per item, `rows` partitions per chunk and partial slot.
+//   - Runs of at least kTile rows where the filters have them (a run's first
+//     row costs kTile spectrum loads, each later one one).
+//   - At least 16 bins where the row has them: 128 bytes of FP32 spectra per
+//     load.
+//   - A chunk of 8 rows per run, longer ones until a group's slots are within
+//     what a head adds up from registers (HeadRed) and a launch's items
+//     within tail_items and a half.
+//   - The items of one chunk and `unit` output groups are read in the same
+//     launch on one XCD (they share their delay-line rows): as many groups as
+//     leave every XCD of every launch two units.
+struct TilePlan {
+  int W = 0, rows = 0, unit = 1;
+  int64_t slots = 0;
+};
+
+TilePlan tile_plan(const rta_ctx* c) {
+  const TierHost& T = c->tier[0];
+  TilePlan t;
+  if (!c->tiled) return t;
+  const int far = T.K - kTile - 1;
+  const int ng = T.P <= kThreads ? kThreads / T.P : 0;
+  const bool capped = ng > 0 && is_pow2(T.P) && (c->Q + ng - 1) / ng <= HeadRed<float2>::kInputs;
+  const int64_t cap = capped ? (int64_t)HeadRed<float2>::kSlots * ng : INT32_MAX;
+  int runs = 1;
+  while (runs < 16 && far >= 2 * runs * kTile) runs *= 2;
+  const int wmax = T.P & -T.P;
+  t.W = std::min(kThreads / runs, wmax);
+  runs = kThreads / t.W;
+  const int ngroups = (c->L + c->G - 1) / c->G, per_group = (c->G + tile_outputs(c->G) - 1) / tile_outputs(c->G);
+  for (int k = 1;; ++k) {
+    t.rows = runs * kTile * k;
+    int64_t most = 0, items = 0, chunks = 0, all = 0;
+    for (int g = 0; g < ngroups; ++g) {
+      int64_t slots = 0;
+      for (int q = 0; q < c->Q; ++q) {
+        int kg = 0;
+        for (int l = g * c->G; l < std::min(c->L, (g + 1) * c->G); ++l) kg = std::max(kg, T.kp[l * c->Q + q]);
+        if (kg > 2) ++slots;  // its partitions 2 .. kTile
+        const int ch = std::max(0, kg - kTile - 1 + t.rows - 1) / t.rows;
+        slots += ch;
+        chunks += ch;
+        items += (int64_t)ch * per_group * (T.P / t.W);
+      }
+      most = std::max(most, slots);
+      all += slots;
+    }
+    t.slots = all;
+    const bool whole = t.rows >= far;  // one chunk per input: no fewer slots to be had
+    if (whole || (most <= cap && items <= (int64_t)kTile * c->tail_items * 3 / 2)) {
+      while (t.unit < 8 && chunks / (2 * t.unit) >= 2 * kTile * kXcds) t.unit *= 2;
+      return t;
+    }
+  }
 }
 
 int build_plan(rta_ctx* c, Plan& plan) {
@@ -480,8 +545,12 @@ int build_plan(rta_ctx* c, Plan& plan) {
   const bool fixed = c->serve != nullptr;
   const int n_phase = c->tier[c->n_tiers - 1].P / c->B;
   c->n_phase = n_phase;
-  plan.block.assign(n_phase, {});
-  plan.tier.assign(n_phase, {});
+  // far partitions (p > kTile) tiled in time: see tile_plan
+  const int near_end = c->tiled ? kTile + 1 : INT32_MAX;
+  const int n_list = c->tiled ? std::max(n_phase, kTile) : n_phase;
+  c->n_list = n_list;
+  plan.block.assign(n_list, {});
+  plan.tier.assign(n_list, {});
   plan.groups.clear();
   plan.tier_slot0.assign((size_t)kMaxTiers * ngroups, 0);
   plan.tier_nslot.assign((size_t)kMaxTiers * ngroups, 0);
@@ -495,6 +564,10 @@ int build_plan(rta_ctx* c, Plan& plan) {
     int kg = 0;
     for (int l = gr.l0; l < gr.l0 + gr.nl; ++l) kg = std::max(kg, T.kp[l * c->Q + q]);
     return kg;
+  };
+  // partitions of the items that serve one block each
+  auto near_rows = [&](const TierHost& T, const Group& gr, int q) {
+    return std::min(group_rows(T, gr, q), near_end);
   };
   // a multiply-accumulate item's per-output spectrum rows (Item::row, pend)
   auto mac_rows = [&](Item& it, const TierHost& T) {
@@ -515,6 +588,9 @@ int build_plan(rta_ctx* c, Plan& plan) {
 
   // ---- first tier: partitions >= 2, every phase
   std::vector<Item> tier0;
+  std::vector<std::vector<Item>> far(n_list);  // K_TILE items, by the launch that runs them
+  std::map<std::tuple<int, int, int>, std::vector<Item>> units;  // by (input, chunk, groups)
+  const TilePlan tile = tile_plan(c);
   {
     TierHost& T = c->tier[0];
     // bin slices per row: each item covers W bins of nslice-fold more rows,
@@ -526,7 +602,7 @@ int build_plan(rta_ctx* c, Plan& plan) {
     int W = std::max(C, Wmax / std::max(1, c->bin_slices)), nslice = T.P / W;
     int64_t total_rows = 0;
     for (const Group& gr : plan.groups)
-      for (int q = 0; q < c->Q; ++q) total_rows += std::max(0, group_rows(T, gr, q) - 2);
+      for (int q = 0; q < c->Q; ++q) total_rows += std::max(0, near_rows(T, gr, q) - 2);
     // serving: every (group, input) owns the slots of a max_taps filter, so
     // a slot's meaning does not depend on which sources are present
     const int cap_rows = fixed ? std::max(0, T.kcap - 2) : 0;
@@ -552,7 +628,7 @@ int build_plan(rta_ctx* c, Plan& plan) {
           int64_t tot = 0, m = 0;
           for (const Group& gr : plan.groups) {
             int64_t ns = 0;
-            for (int q = 0; q < c->Q; ++q) ns += (std::max(0, group_rows(T, gr, q) - 2) + r - 1) / r;
+            for (int q = 0; q < c->Q; ++q) ns += (std::max(0, near_rows(T, gr, q) - 2) + r - 1) / r;
             tot += ns;
             m = std::max(m, ns);
           }
@@ -579,7 +655,7 @@ int build_plan(rta_ctx* c, Plan& plan) {
       // 60 ranges 27.5 us, 64 ranges 24.4 us)
       int kmax = 0;
       for (const Group& gr : plan.groups)
-        for (int q = 0; q < c->Q; ++q) kmax = std::max(kmax, group_rows(T, gr, q) - 2);
+        for (int q = 0; q < c->Q; ++q) kmax = std::max(kmax, near_rows(T, gr, q) - 2);
       if (fixed) kmax = std::max(0, T.kcap - 2);
       int step = kXcds;
       for (int qq = c->Q; qq % 2 == 0 && step > 1; qq /= 2) step /= 2;  // 8 / gcd(Q, 8)
@@ -603,7 +679,7 @@ int build_plan(rta_ctx* c, Plan& plan) {
         slot += gr.nslot;
       }
       for (int q = 0; q < c->Q; ++q) {
-        const int kg = group_rows(T, gr, q);
+        const int kg = near_rows(T, gr, q);
         if (kg <= 2) continue;  // partitions 0 and 1 are done by the heads
         const int rows = kg - 2;
         const int nch = (rows + R - 1) / R;
@@ -631,8 +707,57 @@ int build_plan(rta_ctx* c, Plan& plan) {
           }
         }
       }
+      // far partitions: chunks of about tile_rows rows, one slot each; the
+      // group's outputs in pairs, each pair's bin slices an item of their own
+      for (int q = 0; c->tiled && q < c->Q; ++q) {
+        const int rows = group_rows(T, gr, q) - near_end;
+        const int nch = rows > 0 ? (rows + tile.rows - 1) / tile.rows : 0;
+        for (int ch = 0; ch < nch; ++ch) {
+          for (int g0 = 0; g0 < gr.nl; g0 += tile_outputs(G)) {
+            Item it{};
+            it.kind = K_TILE;
+            it.group = g;
+            it.q = q;
+            it.p0 = near_end + (int)((int64_t)ch * rows / nch);
+            it.p1 = near_end + (int)((int64_t)(ch + 1) * rows / nch);
+            it.w = tile.W;
+            it.slot = slot;
+            it.acc = g0;
+            it.nl = std::min(tile_outputs(G), gr.nl - g0);
+            for (int i = 0; i < it.nl; ++i) {
+              const size_t pair = (size_t)(gr.l0 + g0 + i) * c->Q + q;
+              if (T.row[pair] < 0) continue;
+              it.row[i] = T.row[pair];
+              it.pend[i] = std::min(it.p1, T.kp[pair]);
+            }
+            it.tier = 0;
+            auto& unit = units[std::make_tuple(q, ch, g / tile.unit)];
+            for (int k0 = 0; k0 < T.P; k0 += tile.W) {
+              it.k0 = k0;
+              unit.push_back(it);
+            }
+          }
+          ++slot;
+          ++gr.nslot;
+        }
+      }
     }
     T.nslots = slot;
+    // every launch reads an eighth of the far rows, whole units at a time
+    std::vector<std::pair<int64_t, const std::vector<Item>*>> by_rows;
+    for (const auto& u : units) {
+      int64_t rows = 0;
+      for (const Item& it : u.second) rows += (int64_t)(it.p1 - it.p0) * it.nl;
+      by_rows.push_back({rows, &u.second});
+    }
+    std::stable_sort(by_rows.begin(), by_rows.end(),
+                     [](const auto& a, const auto& b) { return a.first > b.first; });
+    std::vector<int64_t> load(n_list, 0);
+    for (const auto& u : by_rows) {
+      const size_t ph = std::min_element(load.begin(), load.end()) - load.begin();
+      load[ph] += u.first;
+      far[ph].insert(far[ph].end(), u.second->begin(), u.second->end());
+    }
     c->max_group_slots = 0;
     for (const Group& gr : plan.groups) c->max_group_slots = std::max(c->max_group_slots, gr.nslot);
   }
@@ -796,10 +921,12 @@ int build_plan(rta_ctx* c, Plan& plan) {
   c->n_groups = ngroups;
 
   // ---- per-phase k_block lists, XCD-aware
-  for (int ph = 0; ph < n_phase; ++ph) {
+  for (int ph = 0; ph < n_list; ++ph) {
     std::vector<Bucket> buckets;
+    for (const Item& it : far[ph]) add_to_bucket(buckets, it, it.nl, 1 + it.group / tile.unit);
     for (const Item& it : tier0) add_to_bucket(buckets, it, plan.groups[it.group].nl);
-    for (const Item& it : tier_mac[ph]) add_to_bucket(buckets, it, plan.groups[it.group].nl);
+    if (c->n_tiers > 1)
+      for (const Item& it : tier_mac[ph]) add_to_bucket(buckets, it, plan.groups[it.group].nl);
     plan.block[ph] = place_on_xcds(buckets);
   }
 
@@ -814,9 +941,25 @@ int build_plan(rta_ctx* c, Plan& plan) {
       const int s0 = plan.tier_slot0[(size_t)t * ngroups + g], ns = plan.tier_nslot[(size_t)t * ngroups + g];
       if (s0 < 0 || ns < 0 || s0 + ns > c->tier[t].nslots) return RTA_E_STATE;
     }
-  for (int ph = 0; ph < n_phase; ++ph) {
+  for (int ph = 0; ph < n_list; ++ph) {
     for (const Item& it : plan.block[ph]) {
       if (it.kind == K_NOP) continue;
+      if (it.kind == K_TILE) {
+        const TierHost& T = c->tier[0];
+        const int W = it.w;
+        if (it.tier != 0 || it.group < 0 || it.group >= ngroups || it.q < 0 || it.q >= c->Q) return RTA_E_STATE;
+        const Group& gr = plan.groups[it.group];
+        if (T.K < 2 * kTile || it.p0 < kTile + 1 || it.p1 < it.p0 || it.p1 > T.K) return RTA_E_STATE;
+        if (W < 1 || W > kThreads || !is_pow2(W) || T.P % W != 0) return RTA_E_STATE;
+        if (it.k0 < 0 || it.k0 % W != 0 || it.k0 + W > T.P) return RTA_E_STATE;
+        if (it.nl < 1 || it.nl > tile_outputs(G) || it.acc < 0 || it.acc + it.nl > gr.nl) return RTA_E_STATE;
+        if (it.slot < gr.slot0 || it.slot >= gr.slot0 + gr.nslot) return RTA_E_STATE;
+        for (int g = 0; g < it.nl; ++g)
+          if (it.pend[g] < 0 || it.pend[g] > it.p1 || it.row[g] < 0 ||
+              (it.pend[g] > 0 && it.row[g] + it.pend[g] > T.h_rows))
+            return RTA_E_STATE;
+        continue;
+      }
       if (it.kind != K_MAC || it.tier < 0 || it.tier >= c->n_tiers) return RTA_E_STATE;
       if (it.group < 0 || it.group >= ngroups) return RTA_E_STATE;
       const TierHost& T = c->tier[it.tier];
@@ -840,7 +983,7 @@ int build_plan(rta_ctx* c, Plan& plan) {
         if (it.lag < 2 || it.lag > tier_nmac(c, it.tier) + 1) return RTA_E_STATE;
       }
     }
-    for (const Item& it : plan.tier[ph]) {
+    for (const Item& it : plan.tier[ph]) {  // (empty lists when tiled: one tier)
       if (it.tier < 1 || it.tier >= c->n_tiers) return RTA_E_STATE;
       const TierHost& T = c->tier[it.tier];
       const int nmac = tier_nmac(c, it.tier);
@@ -871,6 +1014,10 @@ int build_plan(rta_ctx* c, Plan& plan) {
   return RTA_OK;
 }
 
+// Blocks whose first-tier partial sums are kept at once: this launch's and the
+// next one's, or this one's and the kTile next ones', as a power of two.
+int partial_blocks(const rta_ctx* c) { return c->tiled ? 2 * kTile : 2; }
+
 KArgs make_args(const rta_ctx* c, const float* in, float* out, int64_t n) {
   KArgs a{};
   for (int t = 0; t < c->n_tiers; ++t) {
@@ -892,6 +1039,7 @@ KArgs make_args(const rta_ctx* c, const float* in, float* out, int64_t n) {
     d.logP = T.logP;
     d.K = T.K;
     d.nslots = std::max(1, T.nslots);
+    d.pmask = (t == 0 ? partial_blocks(c) : 1) - 1;
     d.r = T.P / c->B;
   }
   a.items = c->items;
@@ -906,7 +1054,7 @@ KArgs make_args(const rta_ctx* c, const float* in, float* out, int64_t n) {
   a.Q = c->Q;
   a.L = c->L;
   a.n_tiers = c->n_tiers;
-  a.n_phase = c->n_phase;
+  a.n_phase = c->n_list;
   a.max_items = c->max_items;
   a.head_nq = c->head_nq;
   a.n_head = c->L;
@@ -941,6 +1089,7 @@ KArgs make_args(const rta_ctx* c, const float* in, float* out, int64_t n) {
     F.T.r3 = T.r3;
     F.T.K = T.K;
     F.T.nslots = std::max(1, T.nslots);
+    F.T.pmask = partial_blocks(f) - 1;
     F.T.r = 1;
     F.items = f->items;
     F.groups = f->groups;
@@ -1116,7 +1265,7 @@ int zero_state(rta_ctx* c) {
     HIP_TRY(c, hipMemsetAsync(T.X, 0, sizeof(float2) * (size_t)c->Q * T.K * T.P, c->stream));
     // before the first block the terms p >= 2 are all zero (zero history)
     HIP_TRY(c, hipMemsetAsync(T.partial, 0,
-                              sizeof(float2) * (t == 0 ? 2 : 1) * (size_t)std::max(1, T.nslots) * c->G * T.P,
+                              sizeof(float2) * (t == 0 ? partial_blocks(c) : 1) * (size_t)std::max(1, T.nslots) * c->G * T.P,
                               c->stream));
     if (T.oring)
       HIP_TRY(c, hipMemsetAsync(T.oring, 0, sizeof(float) * (size_t)c->L * c->ring_len, c->stream));
@@ -1459,22 +1608,45 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
   if (sv != nullptr) {
     if ((st = serve_lists(c, plan)) != RTA_OK) return st;
   } else {
+  // Far partitions tiled in time (kernels.hpp, mac_tile): uniform partitions,
+  // unless the caller set the rows per item, once a delay line is longer than
+  // two tiles (shorter ones have as many near rows as far ones) and the
+  // partial sums of 2 kTile blocks take no more memory than the spectra (many
+  // inputs with few partitions each would) or 64 MB
+  c->tiled = c->tile_ok && c->n_tiers == 1 && c->rows_per_item == 0 && c->tier[0].K >= 2 * kTile + 2;
+  if (c->tiled && (double)tile_plan(c).slots * 2 * kTile * c->G * c->tier[0].P * 8.0 >
+                      std::max((double)(64 << 20), (double)c->spectra_bytes))
+    c->tiled = false;
+  if (c->tiled) {  // far rows are streamed once in kTile blocks, and so are their delay-line slots
+    const TierHost& T = c->tier[0];
+    auto streamed = [](int kp) { return std::min(kp, kTile + 1) + std::max(0, kp - kTile - 1) / (double)kTile; };
+    double rows = 0, tail_rows = 0;
+    int kmax = 0;
+    for (int32_t kp : T.kp) {
+      rows += streamed(kp);
+      tail_rows += std::max(0.0, streamed(kp) - 2);
+      kmax = std::max(kmax, (int)kp);
+    }
+    c->h_bytes = rows * T.P * eb;
+    c->x_bytes = (double)c->Q * streamed(kmax) * T.P * 8.0;
+    c->tail_bytes = tail_rows * T.P * eb + (double)c->Q * std::max(0.0, streamed(kmax) - 2) * T.P * 8.0;
+  }
   if ((st = build_plan(c, plan)) != RTA_OK) return st;
   c->n_groups = (int)plan.groups.size();
   c->head_slots = (c->L + kXcds - 1) / kXcds * kXcds;  // keeps tails' XCD residues
   size_t mb = 1, mt = 1;
-  for (int ph = 0; ph < c->n_phase; ++ph) {
+  for (int ph = 0; ph < c->n_list; ++ph) {
     mb = std::max(mb, plan.block[ph].size());
     mt = std::max(mt, plan.tier[ph].size());
   }
   c->max_items = (int)mb;
   c->max_tier_items = (int)mt;
   c->n_items = (int)plan.block[0].size();
-  std::vector<Item> all_b((size_t)c->n_phase * mb, Item{}), all_t((size_t)c->n_phase * mt, Item{});
-  std::vector<int32_t> cnt_b(c->n_phase), cnt_t(c->n_phase);
+  std::vector<Item> all_b((size_t)c->n_list * mb, Item{}), all_t((size_t)c->n_list * mt, Item{});
+  std::vector<int32_t> cnt_b(c->n_list), cnt_t(c->n_list);
   for (auto& it : all_b) it.kind = K_NOP;
   for (auto& it : all_t) it.kind = K_NOP;
-  for (int ph = 0; ph < c->n_phase; ++ph) {
+  for (int ph = 0; ph < c->n_list; ++ph) {
     std::copy(plan.block[ph].begin(), plan.block[ph].end(), all_b.begin() + (size_t)ph * mb);
     std::copy(plan.tier[ph].begin(), plan.tier[ph].end(), all_t.begin() + (size_t)ph * mt);
     cnt_b[ph] = (int32_t)plan.block[ph].size();
@@ -1503,7 +1675,7 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
 
   for (int t = 0; t < c->n_tiers; ++t) {
     TierHost& T = c->tier[t];
-    const size_t bufs = t == 0 ? 2 : 1;  // the first tier's partials alternate by block parity
+    const size_t bufs = t == 0 ? partial_blocks(c) : 1;  // the first tier's partials go by block index
     if ((st = dev_alloc(c, &T.partial, bufs * (size_t)std::max(1, T.nslots) * c->G * T.P)) != RTA_OK)
       return st;
   }
@@ -1545,7 +1717,7 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
   c->head_nq = std::max(1, std::min(c->Q, (6144 - fixed) / (2 * P0)));
   // With later tiers, also a transform pass's buffers (kTierLds).
   c->lds = sizeof(float2) * std::max((size_t)head_lds(P0, 1, c->head_nq).total,
-                                     (size_t)kThreads * C * c->G);
+                                     (size_t)kThreads * (c->tiled ? tile_outputs(c->G) * kTile : C * c->G));
   if (c->n_tiers > 1) c->lds = std::max(c->lds, sizeof(float2) * (size_t)kTierLds);
   if ((int64_t)c->lds + 64 > (int64_t)max_lds) return RTA_E_UNSUPPORTED;
   if (c->lds > 65536)
@@ -1949,6 +2121,7 @@ int create_ctx(rta_ctx** out, double fs, int32_t block, const std::vector<int>& 
   rta_ctx* c = new (std::nothrow) rta_ctx();
   if (c == nullptr) return RTA_E_NOMEM;
   c->min_ring = min_ring;
+  c->tile_ok = min_ring == 1;
   c->fs = fs;
   c->B = block;
   c->Q = n_in;

@@ -1,0 +1,86 @@
+"""Far partitions tiled in time (one reading of a far partition row serves
+eight blocks): the shapes at the edges of that tiling against the FP64 oracle,
+sample by sample past the filters' ends, and the window of spectra it reads
+(Sec. IV step 2: block n needs spectra n - p only)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2509_04390_amd import workloads
+
+from test_parity_gpu import BF16_DB, FP16_DB, FP32_DB, check_db, make_filters, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rta():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a visible GPU"
+    from paper_2509_04390_amd import rta as mod
+    return mod
+
+
+# (B, lens[q][l], flags): 18 partitions are the first to be tiled (9 far
+# ones); runs of 8 rows, 16 runs of a 16-bin slice make 128-row chunks
+SHAPES = [
+    (16, [[16 * 17]], 0), (16, [[16 * 18]], 0), (16, [[16 * 18 + 1]], 0),
+    (16, [[16 * 1100, 16 * 500 + 3]], 0),
+    (64, [[64 * 25, 64 * 26 + 1, 64 * 18 + 5], [64 * 200 - 3, 0, 700]], 0),
+    (128, [[128 * 137]], 0), (128, [[128 * 138, 128 * 10, 128 * 9 + 1]], 0),
+    (128, [[128 * (20 + 3 * l) - l for l in range(17)]], 0),      # two outputs per item, one left
+    (128, [[128 * 40 - 5] * 3 for _ in range(5)], 0),             # more inputs than a head prefetches
+    (256, [[256 * 70 + 100, 256 * 30]], 0),
+    (512, [[512 * 40, 512 * 33 + 7]], 0),
+    (4096, [[4096 * 19, 5]], 0),
+    (16, [[16 * 60, 16 * 21]], 2), (128, [[128 * 45 + 7], [128 * 19]], 2),   # n_f = 3B
+]
+
+
+@pytest.mark.parametrize("spectra,limit", [("fp32", FP32_DB), ("fp16", FP16_DB), ("bf16", BF16_DB)])
+@pytest.mark.parametrize("shape", range(len(SHAPES)))
+def test_tiled_shapes_match_oracle(rta, shape, spectra, limit):
+    B, lens, flags = SHAPES[shape]
+    filt = make_filters(700 + shape, lens)
+    n = max(max(r) for r in lens) // B * B + 20 * B
+    x = workloads.white_noise(701 + shape, len(lens), n)
+    say(f"B={B} lens={lens} flags={flags} {spectra}")
+    with rta.Convolver(filt, B, spectra=spectra, flags=flags) as cv:
+        y = cv.run_device(x)
+        cv.reset()
+        assert np.array_equal(cv.run(x[:, :40 * B]), y[:, :40 * B])
+    rng = np.random.default_rng(shape)
+    idx = np.unique(np.r_[0, B - 1, B, n - 1, rng.integers(0, n, 300)])
+    check_db(y[:, idx], oracle.direct_at(x, filt, idx), limit, f"tiled B={B}")
+
+
+@pytest.mark.parametrize("G", [1, 2, 4])
+def test_tiled_outputs_per_group(rta, G):
+    B, L = 64, 9
+    lens = [[64 * (30 + 2 * l) + l for l in range(L)], [64 * 50] * L]
+    filt = make_filters(740, lens)
+    n = 90 * B
+    x = workloads.white_noise(741, 2, n)
+    with rta.Convolver(filt, B, tuning=rta.make_tuning(outputs_per_group=G)) as cv:
+        y = cv.run_device(x)
+    check_db(y, oracle.direct(x, filt, 0, n), FP32_DB, f"tiled G={G}")
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_a_bad_block_is_heard_for_its_partitions_only(rta, bad):
+    """Blocks before a NaN or infinite one are untouched bit for bit, and the
+    outputs recover as soon as the last partition has passed it."""
+    B, K, at = 64, 40, 60
+    filt = make_filters(750, [[B * K, B * K]])
+    x = workloads.white_noise(751, 1, (at + K + 40) * B)
+    xb = x.copy()
+    xb[0, at * B + 5] = bad
+    with rta.Convolver(filt, B) as cv:
+        y = cv.run_device(x)
+        cv.reset()
+        yb = cv.run_device(xb)
+    assert np.array_equal(y[:, :at * B], yb[:, :at * B])
+    assert not np.isfinite(yb[:, at * B:(at + K) * B]).any()
+    # block at + K's window still begins with the bad block; partition K - 1
+    # pairs block at + K with the spectrum of [x(at), x(at + 1)]
+    assert np.array_equal(y[:, (at + K + 1) * B:], yb[:, (at + K + 1) * B:])
