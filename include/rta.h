@@ -480,7 +480,11 @@ typedef struct rta_slot_info {
     int64_t stop_block;         /* first block that ignored it, or -1       */
     int64_t free_block;         /* block from which the slot is free, or -1 */
     int64_t taps;               /* longest of its filters                   */
-    double  bytes_per_block;    /* spectrum + delay-line bytes it streams   */
+    double  bytes_per_block;    /* spectrum + delay-line bytes of its filters
+                                   per block, every row counted once (an
+                                   upper bound of what it streams: under
+                                   uniform partitions far rows are read once
+                                   for eight blocks)                        */
 } rta_slot_info;
 
 typedef struct rta_serve_info {

@@ -63,8 +63,10 @@ enum ItemKind : int32_t {
   K_FFT_B = 3,  // N1-point transforms of column pairs -> packed spectrum -> ring
   K_FIN_A = 4,  // partial sums of column pairs -> N1-point inverse transforms
   K_FIN_B = 5,  // N2-point inverse transforms of rows -> output ring
-  K_TILE = 6    // tail: multiply-accumulate of a far partition range for the
+  K_TILE = 6,   // tail: multiply-accumulate of a far partition range for the
                 // next kTile blocks
+  K_NEAR = 7    // tail: multiply-accumulate of the partitions before it, of
+                // several inputs, for the next block
 };
 
 struct Item {          // one workgroup's work in one block (96 bytes)
@@ -73,7 +75,8 @@ struct Item {          // one workgroup's work in one block (96 bytes)
                        // tier passes: columns (rows) or column pairs per item
   int32_t tier;
   int32_t group;       // reduction group (outputs l0 .. l0+nl-1)
-  int32_t q;           // input channel; K_FIN_*: output within the group
+  int32_t q;           // input channel (K_TILE, K_NEAR: the first one);
+                       // K_FIN_*: output within the group
   int32_t p0, p1;      // partition range
   int32_t k0;          // K_MAC: first bin of the slice; tier passes: index of
                        // the item within its pass
@@ -81,12 +84,13 @@ struct Item {          // one workgroup's work in one block (96 bytes)
   int32_t acc;         // K_MAC of a later tier: add to the slot (0: store);
                        // K_TILE: its first output within the group
   int32_t lag;         // tiers >= 1: launch index minus the block in which
-                       // the frame's input completed
-  int32_t nl;          // K_MAC: outputs of its group; K_TILE: its outputs (at most 2)
+                       // the frame's input completed; K_TILE, K_NEAR: inputs
+  int32_t nl;          // K_MAC, K_NEAR: outputs of its group; K_TILE: its outputs
   // K_MAC, per output g of the group: the end of the partitions to read,
   // min(p1, partitions of pair (l0 + g, q)) (0: no path), and that pair's
   // first spectrum row.  Carried here so that a tail workgroup needs one
-  // load (its item) before it streams, not a chain of table lookups.
+  // load (its item) before it streams, not a chain of table lookups.  (K_TILE:
+  // of its first input; further inputs, and K_NEAR, take the tables.)
   int32_t pend[4];
   int64_t row[4];
 };
@@ -213,13 +217,6 @@ template <> struct HVec<float2> {
   // work, a converted load would make the wave wait for it at once)
   typedef float2 one_t;
   static __device__ __forceinline__ one_t load1_raw(const float2* p) { return *p; }
-  template <bool NT>
-  static __device__ __forceinline__ one_t load1_stream(const float2* p) {
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    if (!NT) return *p;
-    const f32x2 v = __builtin_nontemporal_load(reinterpret_cast<const f32x2*>(p));
-    return make_float2(v.x, v.y);
-  }
   static __device__ __forceinline__ float2 cvt1(one_t v) { return v; }
 };
 
@@ -251,10 +248,6 @@ template <> struct HVec<f16c_t> {
   static __device__ __forceinline__ float2 load1(const f16c_t* p) { return f16pair(p->bits); }
   typedef uint32_t one_t;
   static __device__ __forceinline__ one_t load1_raw(const f16c_t* p) { return p->bits; }
-  template <bool NT>
-  static __device__ __forceinline__ one_t load1_stream(const f16c_t* p) {
-    return NT ? __builtin_nontemporal_load(&p->bits) : p->bits;
-  }
   static __device__ __forceinline__ float2 cvt1(one_t v) { return f16pair(v); }
 };
 
@@ -274,10 +267,6 @@ template <> struct HVec<bf16c_t> {
   static __device__ __forceinline__ float2 load1(const bf16c_t* p) { return bf16pair(p->bits); }
   typedef uint32_t one_t;
   static __device__ __forceinline__ one_t load1_raw(const bf16c_t* p) { return p->bits; }
-  template <bool NT>
-  static __device__ __forceinline__ one_t load1_stream(const bf16c_t* p) {
-    return NT ? __builtin_nontemporal_load(&p->bits) : p->bits;
-  }
   static __device__ __forceinline__ float2 cvt1(one_t v) { return bf16pair(v); }
 };
 
@@ -298,9 +287,76 @@ __device__ __forceinline__ int pin(int v) {
 }
 __device__ __forceinline__ float2 pin(float2 v) { return make_float2(pin(v.x), pin(v.y)); }
 
+// A value at a uniform base in device memory plus a 32-bit byte offset per
+// lane.  The address space is spelled out: cast through char, the compiler
+// would take it for a generic address (flat loads, 64-bit address arithmetic
+// per lane).
+template <bool NT>
+__device__ __forceinline__ float2 load_at(const char* base, uint32_t off, float2) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef const __attribute__((address_space(1))) char* gbase;
+  typedef const __attribute__((address_space(1))) f32x2* gp;
+  const gp p = (gp)((gbase)base + off);
+  const f32x2 v = NT ? __builtin_nontemporal_load(p) : *p;
+  return make_float2(v.x, v.y);
+}
+template <bool NT>
+__device__ __forceinline__ uint32_t load_at(const char* base, uint32_t off, uint32_t) {
+  typedef const __attribute__((address_space(1))) char* gbase;
+  typedef const __attribute__((address_space(1))) uint32_t* gp;
+  const gp p = (gp)((gbase)base + off);
+  return NT ? __builtin_nontemporal_load(p) : *p;
+}
+
 __device__ __forceinline__ int wrap_slot(int64_t v, int K) {
   int s = (int)(v % K);
   return s < 0 ? s + K : s;
+}
+
+// The end of an item of G outputs: the four real sums of each lane's C bins
+// (from k0 + C (tid mod W / C) on) combined, the row groups added up through
+// LDS, and the sums stored (add: added) to the slot's rows at `part` [G][P].
+template <int G, int C>
+__device__ __forceinline__ void store_sums(const float (&acc)[G][C][4], float2* part, int P, int k0, int W,
+                                           bool add, float2* red) {
+  const int LR = W / C, RP = kThreads / LR;
+  const int tid = threadIdx.x;
+  const int r = tid % LR, s = tid / LR;
+  const int kb = k0 + r * C;
+  // combine the four real sums; packed bin 0 holds two real products
+  float2 res[G][C];
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int j = 0; j < C; ++j) {
+      if (kb + j == 0)
+        res[g][j] = make_float2(acc[g][j][0], acc[g][j][1]);
+      else
+        res[g][j] = make_float2(acc[g][j][0] - acc[g][j][1], acc[g][j][2] + acc[g][j][3]);
+    }
+
+  if (RP == 1) {
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int j = 0; j < C; ++j) {
+        float2* d = part + (int64_t)g * P + kb + j;
+        *d = add ? cadd(*d, res[g][j]) : res[g][j];
+      }
+    return;
+  }
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int j = 0; j < C; ++j) red[(s * G + g) * W + r * C + j] = res[g][j];
+  __syncthreads();
+  for (int e = tid; e < G * W; e += kThreads) {
+    const int g = e / W, b = e - g * W;
+    float2 sum = red[g * W + b];
+    for (int s2 = 1; s2 < RP; ++s2) sum = cadd(sum, red[(s2 * G + g) * W + b]);
+    float2* d = part + (int64_t)g * P + k0 + b;
+    *d = add ? cadd(*d, sum) : sum;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -378,50 +434,81 @@ __device__ __forceinline__ void mac_item(const DevTier& T, const Item& it, int64
     }
   }
 
-  // combine the four real sums; packed bin 0 holds two real products
-  float2 res[G][C];
-#pragma unroll
-  for (int g = 0; g < G; ++g)
-#pragma unroll
-    for (int j = 0; j < C; ++j) {
-      if (kb + j == 0)
-        res[g][j] = make_float2(acc[g][j][0], acc[g][j][1]);
-      else
-        res[g][j] = make_float2(acc[g][j][0] - acc[g][j][1], acc[g][j][2] + acc[g][j][3]);
-    }
-
   // later tiers: chunks of one (group, input) accumulated in earlier blocks
   // of the frame share the slot; the first stored it
-  float2* part = T.partial + (int64_t)it.slot * G * P;
-  if (RP == 1) {
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-      for (int j = 0; j < C; ++j) {
-        float2* d = part + (int64_t)g * P + kb + j;
-        *d = it.acc ? cadd(*d, res[g][j]) : res[g][j];
-      }
-    return;
-  }
-#pragma unroll
-  for (int g = 0; g < G; ++g)
-#pragma unroll
-    for (int j = 0; j < C; ++j) red[(s * G + g) * W + r * C + j] = res[g][j];
-  __syncthreads();
-  for (int e = tid; e < G * W; e += kThreads) {
-    const int g = e / W, b = e - g * W;
-    float2 sum = red[g * W + b];
-    for (int s2 = 1; s2 < RP; ++s2) sum = cadd(sum, red[(s2 * G + g) * W + b]);
-    float2* d = part + (int64_t)g * P + it.k0 + b;
-    *d = it.acc ? cadd(*d, sum) : sum;
-  }
+  store_sums<G, C>(acc, T.partial + (int64_t)it.slot * G * P, P, it.k0, W, it.acc != 0, red);
 }
 
 // ---------------------------------------------------------------------------
-// Far partitions, tiled in time.  Partition p >= kTile + 1 of block b pairs
-// with X(b - p), which exists kTile blocks before b does: one reading of its
-// row in launch n serves the blocks n + 1 .. n + kTile (their newest spectrum
-// is X(n + kTile - p), at most X(n - 1)).  Every far range is read in one of
+// Near partitions of several inputs, for block b: lanes take (input,
+// partition) pairs of the item in turn (8 partitions to an input, those from
+// p1 on left out).  One slot per group for up to kNearInputs inputs keeps the
+// heads' reduction short where many inputs feed an output.
+// ---------------------------------------------------------------------------
+constexpr int kNearInputs = 16;
+
+template <typename HT, int G, bool NT>
+__device__ __forceinline__ void mac_near(const DevTier& T, const Item& it, int64_t b, int Q, float2* red) {
+  constexpr int C = HVec<HT>::C, U = HVec<HT>::U;
+  typedef typename HVec<HT>::raw_t raw_t;
+  const int P = T.P, K = T.K, W = it.w;
+  const int LR = W / C, RP = kThreads / LR;
+  const int tid = threadIdx.x;
+  const int r = tid % LR, s = tid / LR;
+  const int kb = it.k0 + r * C;
+  const HT* H = reinterpret_cast<const HT*>(T.H) + kb;
+  const int s0 = wrap_slot(b, K);
+  const int J = it.lag * kTile;
+  float acc[G][C][4];
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+#pragma unroll
+    for (int j = 0; j < C; ++j) acc[g][j][0] = acc[g][j][1] = acc[g][j][2] = acc[g][j][3] = 0.f;
+  for (int j = s; j < J; j += RP * U) {
+    f32x4 xr[U];
+    raw_t hr[U][G];
+    bool on[U][G];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int ju = min(j + u * RP, J - 1);
+      const int q = it.q + ju / kTile, p = it.p0 + ju % kTile;
+      const bool in = j + u * RP < J && p < it.p1;
+      const int sl = s0 - p < 0 ? s0 - p + K : s0 - p;  // (p < K: checked on the host)
+      xr[u] = *reinterpret_cast<const f32x4*>(T.X + ((int64_t)q * K + sl) * P + kb);
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const int64_t pair = (int64_t)(it.group * G + min(g, it.nl - 1)) * Q + q;
+        on[u][g] = in && g < it.nl && p < T.pair_K[pair];
+        hr[u][g] = HVec<HT>::template load_raw<NT>(H + (on[u][g] ? T.pair_row[pair] + p : 0) * P);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float2 xv[C] = {make_float2(xr[u].x, xr[u].y), make_float2(xr[u].z, xr[u].w)};
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+        if (on[u][g]) {
+          float2 hv[C];
+          HVec<HT>::unpack(hr[u][g], hv);
+#pragma unroll
+          for (int i = 0; i < C; ++i) {
+            acc[g][i][0] += hv[i].x * xv[i].x;
+            acc[g][i][1] += hv[i].y * xv[i].y;
+            acc[g][i][2] += hv[i].x * xv[i].y;
+            acc[g][i][3] += hv[i].y * xv[i].x;
+          }
+        }
+    }
+  }
+  store_sums<G, C>(acc, T.partial + ((b & T.pmask) * (int64_t)T.nslots + it.slot) * G * P, P, it.k0, W, false, red);
+}
+
+// ---------------------------------------------------------------------------
+// Far partitions, tiled in time, for blocks b .. b + kTile - 1.  Partition
+// p >= kTile + 1 of a block pairs with the spectrum of p blocks earlier, which
+// exists kTile blocks before the block does: one reading of its row in launch
+// n serves the blocks n + 1 .. n + kTile (their newest spectrum is
+// X(n + kTile - p), at most X(n - 1)).  Every far range is read in one of
 // kTile consecutive launches, so a launch streams 1/kTile of the far rows and
 // does the same multiply-accumulates as before.
 //
@@ -429,94 +516,127 @@ __device__ __forceinline__ void mac_item(const DevTier& T, const Item& it, int64
 // consecutive rows.  Along a run the window of kTile spectra moves by one
 // slot per row, so a row costs one new spectrum load and one load per output
 // for 4 kTile multiply-adds per output; kTile rows are in flight per lane.
+// Where an output has many inputs with few partitions each, an item takes
+// several inputs, one after another, into its one slot.
 // Bound by the VALU: 4 multiply-adds per (bin, row, block, output).  16-bit
 // spectra are converted once per row: left to itself the compiler folds the
 // conversion into every multiply-add (v_fma_mix_f32), which runs at half the
 // rate (1 -> 64 x 576,000 taps FP16: launch 13.8 -> 11.2 us).
 // Measured against reading every row every block (us per block, back to
-// back): 1 -> 32 x 480,000 taps FP32 21.5 -> 10.0 (then bound by the heads),
-// 1 -> 64 x 576,000 FP16 25.8 -> 12.9, block 2048 61.4 -> 43.1.
+// back): 1 -> 32 x 480,000 taps FP32 21.5 -> 10.1 (then bound by the heads),
+// 1 -> 64 x 576,000 FP16 25.8 -> 13.3, block 2048 61.4 -> 43.9, 16 served
+// sources -> 64 x 576,000 FP16 with feedback 500 -> 157.  Matrix instructions
+// (v_mfma_f32_4x4x1_16b_f32: the sums are a Toeplitz product) are no faster:
+// FP32 multiply-adds issue at the same rate on the VALU (2.1 cycles per
+// wavefront instruction against 8.2 for four times the work).
 // ---------------------------------------------------------------------------
+// Outputs per item: at most two (a group of four goes to two items).
 __host__ __device__ constexpr int tile_outputs(int G) { return G < 2 ? 1 : 2; }
 
 template <typename HT, int G, bool NT>
-__device__ __forceinline__ void mac_tile(const DevTier& T, const Item& it, int64_t n, float2* red) {
+__device__ __forceinline__ void mac_tile(const DevTier& T, const Item& it, int64_t b, int Q, float2* red) {
   constexpr int GF = tile_outputs(G), M = kTile, U = kTile;
   const int P = T.P, K = T.K, W = it.w;
   const int lw = 31 - __builtin_clz(W);
   const int tid = threadIdx.x;
   const int r = tid & (W - 1), s = tid >> lw;
-  const int kb = it.k0 + r;
   const int RP = kThreads >> lw;
   const int per = (it.p1 - it.p0 + RP - 1) >> (8 - lw);  // rows per run
   const int pa = min(it.p0 + s * per, it.p1), pe = min(it.p1, pa + per);
-  const HT* Hbase = reinterpret_cast<const HT*>(T.H);
-  const HT* hp[GF];
-  int left[GF];  // rows of the run still to read
-#pragma unroll
-  for (int g = 0; g < GF; ++g) {
-    const int end = g < it.nl ? min(it.pend[g], pe) : 0;
-    left[g] = max(end - pa, 0);
-    hp[g] = Hbase + ((g < it.nl ? it.row[g] : 0) + (left[g] > 0 ? pa : 0)) * (int64_t)P + kb;
-  }
-  float acc[GF][M][4];
+  // Addresses are a uniform base and a 32-bit byte offset per lane (a pair's
+  // rows and an input's ring are under 2 GB: checked on the host).
+  const uint32_t xrow = (uint32_t)P * sizeof(float2), xend = (uint32_t)K * xrow;
+  const uint32_t hrow = (uint32_t)P * sizeof(HT);
+  // ring offset of X(b - (pa + U - 1))
+  int sl = wrap_slot(b, K) - (pa + U - 1);
+  if (sl < 0) sl += K;
+  if (sl < 0) sl += K;
+  const uint32_t xo0 = (uint32_t)sl * xrow;
+  float2 acc[GF][M];
 #pragma unroll
   for (int g = 0; g < GF; ++g)
 #pragma unroll
-    for (int m = 0; m < M; ++m) acc[g][m][0] = acc[g][m][1] = acc[g][m][2] = acc[g][m][3] = 0.f;
+    for (int m = 0; m < M; ++m) acc[g][m] = make_float2(0.f, 0.f);
 
-  // x[i] = X(n + 1 - (p + U - 1) + i): row p + u pairs block n + 1 + m with
-  // x[U - 1 - u + m]
-  const float2* Xq = T.X + (int64_t)it.q * K * P + kb;
-  int sl = wrap_slot(n + 1, K) - (pa + U - 1);
-  if (sl < 0) sl += K;
-  if (sl < 0) sl += K;
-  float2 x[U + M - 1];
-  {
-    int t = sl;
-#pragma unroll
-    for (int i = 0; i < U + M - 1; ++i) {
-      x[i] = Xq[(int64_t)t * P];
-      t = t + 1 == K ? 0 : t + 1;
-    }
-  }
-  for (int p = 0; p < per; p += U) {
-    typename HVec<HT>::one_t h[U][GF];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int g = 0; g < GF; ++g)  // (clamped: rows past the run are not used)
-        h[u][g] = HVec<HT>::template load1_stream<NT>(hp[g] + (int64_t)min(u, max(left[g] - 1, 0)) * P);
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int g = 0; g < GF; ++g)
-        if (u < left[g]) {
-          const float2 hv = pin(HVec<HT>::cvt1(h[u][g]));
-#pragma unroll
-          for (int m = 0; m < M; ++m) {
-            const float2 xv = x[U - 1 - u + m];
-            acc[g][m][0] += hv.x * xv.x;
-            acc[g][m][1] += hv.y * xv.y;
-            acc[g][m][2] += hv.x * xv.y;
-            acc[g][m][3] += hv.y * xv.x;
-          }
-        }
-    if (p + U >= per) break;
+  // A spectrum as the multiply-adds take it: re += h.x x.re - h.y x.im,
+  // im += h.x x.im + h.y x.cross.  Packed bin 0 (two real products) has
+  // x.im = 0 and x.cross its second value, so two sums per bin do (four
+  // real ones took 32 more registers: three waves per SIMD instead of four).
+  struct Xv {
+    float re, im, cross;
+  };
+  const bool packed = it.k0 + r == 0;
+  for (int qi = 0; qi < it.lag; ++qi) {
+    const int q = it.q + qi;
+    const char* hb[GF];
+    uint32_t ho[GF];
+    int left[GF];  // rows of the run still to read
 #pragma unroll
     for (int g = 0; g < GF; ++g) {
-      left[g] = max(left[g] - U, 0);
-      if (left[g] > 0) hp[g] += U * P;
+      const int64_t pair = (int64_t)(it.group * G + it.acc + min(g, it.nl - 1)) * Q + q;
+      int end = it.pend[g];
+      int64_t row = it.row[g];
+      if (qi > 0) {
+        end = min(it.p1, T.pair_K[pair]);
+        row = end > 0 ? T.pair_row[pair] : 0;
+      }
+      end = g < it.nl ? min(end, pe) : 0;
+      left[g] = max(end - pa, 0);
+      hb[g] = reinterpret_cast<const char*>(reinterpret_cast<const HT*>(T.H) + row * P + it.k0);
+      ho[g] = (uint32_t)(left[g] > 0 ? pa : 0) * hrow + (uint32_t)(r * sizeof(HT));
     }
-    sl -= U;
-    if (sl < 0) sl += K;
+    // x[i] = X(b - (p + U - 1) + i): row p + u pairs block b + m with
+    // x[U - 1 - u + m]
+    const char* xq = reinterpret_cast<const char*>(T.X + (int64_t)q * K * P + it.k0);
+    const uint32_t rb = (uint32_t)(r * sizeof(float2));
+    uint32_t xo = pin(xo0);  // (opaque: the slots' offsets are not kept across inputs)
+    Xv x[U + M - 1];
+    auto next = [&](uint32_t& t) {
+      const float2 v = load_at<false>(xq, t + rb, float2{});
+      t = t + xrow == xend ? 0 : t + xrow;
+      return Xv{v.x, packed ? 0.f : v.y, packed ? v.y : v.x};
+    };
+    {
+      uint32_t t = xo;
 #pragma unroll
-    for (int i = M - 2; i >= 0; --i) x[U + i] = x[i];
-    int t = sl;
+      for (int i = 0; i < U + M - 1; ++i) x[i] = next(t);
+    }
+    for (int p = 0; p < per; p += U) {
+      typename HVec<HT>::one_t h[U][GF];
 #pragma unroll
-    for (int i = 0; i < U; ++i) {
-      x[i] = Xq[(int64_t)t * P];
-      t = t + 1 == K ? 0 : t + 1;
+      for (int g = 0; g < GF; ++g) {  // (clamped: rows past the run are not used)
+        const uint32_t last = ho[g] + (uint32_t)max(left[g] - 1, 0) * hrow;
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          h[u][g] = load_at<NT>(hb[g], min(ho[g] + (uint32_t)u * hrow, last), typename HVec<HT>::one_t{});
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int g = 0; g < GF; ++g)
+          if (u < left[g]) {
+            const float2 hv = pin(HVec<HT>::cvt1(h[u][g]));
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+              const Xv xv = x[U - 1 - u + m];
+              acc[g][m].x += hv.x * xv.re;
+              acc[g][m].y += hv.x * xv.im;
+              acc[g][m].x -= hv.y * xv.im;
+              acc[g][m].y += hv.y * xv.cross;
+            }
+          }
+      if (p + U >= per) break;
+#pragma unroll
+      for (int g = 0; g < GF; ++g) {
+        left[g] = max(left[g] - U, 0);
+        if (left[g] > 0) ho[g] += U * hrow;
+      }
+      xo = xo >= U * xrow ? xo - U * xrow : xo + xend - U * xrow;
+#pragma unroll
+      for (int i = M - 2; i >= 0; --i) x[U + i] = x[i];
+      uint32_t t = xo;
+#pragma unroll
+      for (int i = 0; i < U; ++i) x[i] = next(t);
     }
   }
 
@@ -525,18 +645,14 @@ __device__ __forceinline__ void mac_tile(const DevTier& T, const Item& it, int64
 #pragma unroll
   for (int g = 0; g < GF; ++g)
 #pragma unroll
-    for (int m = 0; m < M; ++m) {
-      const float* a = acc[g][m];
-      red[s * E + (g * M + m) * W + r] =
-          kb == 0 ? make_float2(a[0], a[1]) : make_float2(a[0] - a[1], a[2] + a[3]);
-    }
+    for (int m = 0; m < M; ++m) red[s * E + (g * M + m) * W + r] = acc[g][m];
   __syncthreads();
   for (int e = tid; e < E; e += kThreads) {
-    const int b = e & (W - 1), gm = e >> lw, m = gm % M, g = gm / M;
+    const int k = e & (W - 1), gm = e >> lw, m = gm % M, g = gm / M;
     if (g >= it.nl) break;
     float2 sum = red[e];
     for (int s2 = 1; s2 < RP; ++s2) sum = cadd(sum, red[s2 * E + e]);
-    T.partial[((((n + 1 + m) & T.pmask) * (int64_t)T.nslots + it.slot) * G + it.acc + g) * P + it.k0 + b] = sum;
+    T.partial[((((b + m) & T.pmask) * (int64_t)T.nslots + it.slot) * G + it.acc + g) * P + it.k0 + k] = sum;
   }
 }
 
@@ -1476,7 +1592,7 @@ __device__ __forceinline__ void tier_pass(const KArgs& A, int64_t n, const Item&
 }
 
 template <typename HT, int G, bool NT>
-__global__ __launch_bounds__(kThreads) void k_block(const KArgs A) {
+__global__ __launch_bounds__(kThreads, sizeof(HT) == 4 ? 4 : 3) void k_block(const KArgs A) {
   extern __shared__ float2 lds[];
   // the block index: from the launch, or (graph replay) the device counter
   // plus this launch's place in the graph
@@ -1556,7 +1672,11 @@ __global__ __launch_bounds__(kThreads) void k_block(const KArgs A) {
   const Item it = A.items[(int64_t)phase * A.max_items + i];
   if (it.kind == K_NOP) return;
   if (it.kind == K_TILE) {
-    mac_tile<HT, G, NT>(T, it, n, lds);
+    mac_tile<HT, G, NT>(T, it, n + 1, A.Q, lds);
+    return;
+  }
+  if (it.kind == K_NEAR) {
+    mac_near<HT, G, NT>(T, it, n + 1, A.Q, lds);
     return;
   }
   if (it.tier != 0) T = A.tier[it.tier];

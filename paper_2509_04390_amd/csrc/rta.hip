@@ -470,33 +470,55 @@ std::vector<Item> place_on_xcds(std::vector<Bucket>& buckets) {
 // only part of the HBM channels (measured: the XCDs holding one slice of two
 // finished 3 us after the others).
 void add_to_bucket(std::vector<Bucket>& buckets, const Item& it, int nl, int unit = 0) {
-  auto bit = std::find_if(buckets.begin(), buckets.end(), [&](const Bucket& b) {
+  // (from the back: the items of a bucket mostly come one after another)
+  auto bit = std::find_if(buckets.rbegin(), buckets.rend(), [&](const Bucket& b) {
     return b.tier == it.tier && b.q == it.q && b.p0 == it.p0 && b.unit == unit;
   });
-  if (bit == buckets.end()) {
+  if (bit == buckets.rend()) {
     buckets.push_back(Bucket{it.tier, it.q, it.p0, unit, {}, 0});
-    bit = buckets.end() - 1;
+    bit = buckets.rbegin();
   }
   bit->items.push_back(it);
   bit->rows += (int64_t)(it.p1 - it.p0) * nl;
 }
 
 // Tiling of the far partitions (kernels.hpp, mac_tile): W bins by kThreads / W
-// runs of rows per item, `rows` partitions per chunk and partial slot.
+// runs of rows per item, `rows` partitions per chunk, `span` inputs per item.
 //   - Runs of at least kTile rows where the filters have them (a run's first
 //     row costs kTile spectrum loads, each later one one).
 //   - At least 16 bins where the row has them: 128 bytes of FP32 spectra per
 //     load.
-//   - A chunk of 8 rows per run, longer ones until a group's slots are within
-//     what a head adds up from registers (HeadRed) and a launch's items
-//     within tail_items and a half.
+//   - Every (output group, span inputs, chunk) owns a partial slot.  A chunk
+//     has 8 rows per run, longer ones until a group's slots are within what a
+//     head adds up from registers (HeadRed; within 32 where it adds them up in
+//     a loop) and a launch's items within tail_items and a half; then an item
+//     takes several inputs.
 //   - The items of one chunk and `unit` output groups are read in the same
 //     launch on one XCD (they share their delay-line rows): as many groups as
 //     leave every XCD of every launch two units.
 struct TilePlan {
-  int W = 0, rows = 0, unit = 1;
+  int W = 0, rows = 0, span = 1, unit = 1;
   int64_t slots = 0;
 };
+
+int near_slots(const rta_ctx* c) { return (c->Q + kNearInputs - 1) / kNearInputs; }
+
+// Partitions of group g's longest filter from input q (serving: of a filter
+// of max_taps, so that the layout does not depend on which sources are present)
+int layout_rows(const rta_ctx* c, int g, int q) {
+  const TierHost& T = c->tier[0];
+  if (c->serve != nullptr) return T.kcap;
+  int kg = 0;
+  for (int l = g * c->G; l < std::min(c->L, (g + 1) * c->G); ++l) kg = std::max(kg, T.kp[l * c->Q + q]);
+  return kg;
+}
+
+// Chunks of the far rows of group g and inputs [q, q + span)
+int far_chunks(const rta_ctx* c, const TilePlan& t, int g, int q) {
+  int kg = 0;
+  for (int i = q; i < std::min(c->Q, q + t.span); ++i) kg = std::max(kg, layout_rows(c, g, i));
+  return (std::max(0, kg - kTile - 1) + t.rows - 1) / t.rows;
+}
 
 TilePlan tile_plan(const rta_ctx* c) {
   const TierHost& T = c->tier[0];
@@ -504,37 +526,127 @@ TilePlan tile_plan(const rta_ctx* c) {
   if (!c->tiled) return t;
   const int far = T.K - kTile - 1;
   const int ng = T.P <= kThreads ? kThreads / T.P : 0;
-  const bool capped = ng > 0 && is_pow2(T.P) && (c->Q + ng - 1) / ng <= HeadRed<float2>::kInputs;
-  const int64_t cap = capped ? (int64_t)HeadRed<float2>::kSlots * ng : INT32_MAX;
+  const bool from_regs = ng > 0 && is_pow2(T.P) && (c->Q + ng - 1) / ng <= HeadRed<float2>::kInputs;
+  const int64_t cap = from_regs ? (int64_t)HeadRed<float2>::kSlots * ng : 32;
   int runs = 1;
   while (runs < 16 && far >= 2 * runs * kTile) runs *= 2;
-  const int wmax = T.P & -T.P;
-  t.W = std::min(kThreads / runs, wmax);
+  t.W = std::min(kThreads / runs, T.P & -T.P);
   runs = kThreads / t.W;
+  t.rows = runs * kTile;
   const int ngroups = (c->L + c->G - 1) / c->G, per_group = (c->G + tile_outputs(c->G) - 1) / tile_outputs(c->G);
-  for (int k = 1;; ++k) {
-    t.rows = runs * kTile * k;
-    int64_t most = 0, items = 0, chunks = 0, all = 0;
+  for (;;) {
+    int64_t most = 0, chunks = 0;
     for (int g = 0; g < ngroups; ++g) {
-      int64_t slots = 0;
-      for (int q = 0; q < c->Q; ++q) {
-        int kg = 0;
-        for (int l = g * c->G; l < std::min(c->L, (g + 1) * c->G); ++l) kg = std::max(kg, T.kp[l * c->Q + q]);
-        if (kg > 2) ++slots;  // its partitions 2 .. kTile
-        const int ch = std::max(0, kg - kTile - 1 + t.rows - 1) / t.rows;
-        slots += ch;
-        chunks += ch;
-        items += (int64_t)ch * per_group * (T.P / t.W);
-      }
-      most = std::max(most, slots);
-      all += slots;
+      int64_t n = 0;
+      for (int q = 0; q < c->Q; q += t.span) n += far_chunks(c, t, g, q);
+      chunks += n;
+      most = std::max(most, n + near_slots(c));
     }
-    t.slots = all;
-    const bool whole = t.rows >= far;  // one chunk per input: no fewer slots to be had
-    if (whole || (most <= cap && items <= (int64_t)kTile * c->tail_items * 3 / 2)) {
+    t.slots = chunks + (int64_t)ngroups * near_slots(c);
+    const bool fits = most <= cap && chunks * per_group * (T.P / t.W) <= (int64_t)kTile * c->tail_items * 3 / 2;
+    if (fits || (t.rows >= far && t.span >= c->Q)) {
       while (t.unit < 8 && chunks / (2 * t.unit) >= 2 * kTile * kXcds) t.unit *= 2;
       return t;
     }
+    if (t.rows < far)
+      t.rows += runs * kTile;
+    else
+      t.span *= 2;
+  }
+}
+
+// The first tier's items of a tiled context: near items (partitions 2 ..
+// kTile, every launch) and, by the launch that reads them, the far ones.
+void tile_items(rta_ctx* c, const TilePlan& t, Plan& plan, std::vector<Item>& near,
+                std::vector<std::vector<Item>>& far) {
+  TierHost& T = c->tier[0];
+  const int G = c->G, Q = c->Q;
+  const bool fixed = c->serve != nullptr;
+  const int Wmax = std::min(T.r3 ? T.P / 3 : T.P, kThreads * vec_bins(c->dtype));
+  if (c->bin_slices == 0) c->bin_slices = 1;
+  const int Wn = std::max(vec_bins(c->dtype), Wmax / c->bin_slices);
+  c->rows_per_item = t.rows;
+  std::map<std::tuple<int, int, int>, std::vector<Item>> units;  // by (chunk, first input, groups)
+  int slot = 0;
+  for (int g = 0; g < (int)plan.groups.size(); ++g) {
+    Group& gr = plan.groups[g];
+    gr.slot0 = slot;
+    auto longest = [&](int q0, int nq) {  // present partitions of the group's paths from these inputs
+      int kg = 0;
+      for (int q = q0; q < q0 + nq; ++q)
+        for (int l = gr.l0; l < gr.l0 + gr.nl; ++l) kg = std::max(kg, T.kp[(size_t)l * Q + q]);
+      return kg;
+    };
+    for (int q = 0; q < Q; q += kNearInputs, ++slot) {
+      Item it{};
+      it.kind = K_NEAR;
+      it.group = g;
+      it.q = q;
+      it.lag = std::min(kNearInputs, Q - q);
+      it.p0 = 2;
+      it.p1 = std::min(longest(q, it.lag), kTile + 1);
+      it.w = Wn;
+      it.slot = slot;
+      it.nl = gr.nl;
+      if (it.p1 <= it.p0) continue;
+      for (it.k0 = 0; it.k0 < T.P; it.k0 += Wn) near.push_back(it);
+    }
+    for (int q = 0; q < Q; q += t.span) {
+      const int nq = std::min(t.span, Q - q);
+      const int cap = far_chunks(c, t, g, q);
+      const int kg = longest(q, nq), rows = kg - kTile - 1;
+      for (int ch = 0; ch < cap; ++ch, ++slot) {
+        Item it{};
+        it.kind = K_TILE;
+        it.group = g;
+        it.q = q;
+        it.lag = nq;
+        it.w = t.W;
+        it.slot = slot;
+        it.p0 = kTile + 1 + (fixed ? ch * t.rows : (int)((int64_t)ch * rows / cap));
+        it.p1 = fixed ? std::min(kg, it.p0 + t.rows) : kTile + 1 + (int)((int64_t)(ch + 1) * rows / cap);
+        if (it.p1 <= it.p0) continue;
+        std::vector<Item>& unit = units[std::make_tuple(ch, q, g / t.unit)];
+        for (int g0 = 0; g0 < gr.nl; g0 += tile_outputs(G)) {
+          it.acc = g0;
+          it.nl = std::min(tile_outputs(G), gr.nl - g0);
+          for (int i = 0; i < it.nl; ++i) {
+            const size_t pair = (size_t)(gr.l0 + g0 + i) * Q + q;
+            it.row[i] = std::max<int64_t>(0, T.row[pair]);
+            it.pend[i] = T.row[pair] < 0 ? 0 : std::min(it.p1, T.kp[pair]);
+          }
+          for (it.k0 = 0; it.k0 < T.P; it.k0 += t.W) unit.push_back(it);
+        }
+      }
+    }
+    gr.nslot = slot - gr.slot0;
+  }
+  T.nslots = slot;
+  // Every launch reads an eighth of the far rows, whole units at a time.
+  // Serving: which launches read a chunk must not change with the sources
+  // present (a new work list would skip or repeat blocks), and a source's
+  // chunks go round the launches in order.
+  std::vector<int64_t> load(far.size(), 0);
+  std::vector<std::pair<int64_t, size_t>> order;
+  std::vector<const std::vector<Item>*> list;
+  for (const auto& u : units) {
+    int64_t rows = 0;
+    for (const Item& it : u.second) rows += (int64_t)(it.p1 - it.p0) * it.nl * it.lag;
+    if (fixed) {
+      const int nu = ((int)plan.groups.size() + t.unit - 1) / t.unit;
+      const int ch = std::get<0>(u.first), q = std::get<1>(u.first), gu = std::get<2>(u.first);
+      std::vector<Item>& f = far[(size_t)((int64_t)(ch * nu + gu + q / t.span) % (int64_t)far.size())];
+      f.insert(f.end(), u.second.begin(), u.second.end());
+      continue;
+    }
+    order.push_back({-rows, list.size()});
+    list.push_back(&u.second);
+  }
+  std::sort(order.begin(), order.end());
+  for (const auto& o : order) {
+    const size_t ph = std::min_element(load.begin(), load.end()) - load.begin();
+    load[ph] -= o.first;
+    far[ph].insert(far[ph].end(), list[o.second]->begin(), list[o.second]->end());
   }
 }
 
@@ -545,8 +657,6 @@ int build_plan(rta_ctx* c, Plan& plan) {
   const bool fixed = c->serve != nullptr;
   const int n_phase = c->tier[c->n_tiers - 1].P / c->B;
   c->n_phase = n_phase;
-  // far partitions (p > kTile) tiled in time: see tile_plan
-  const int near_end = c->tiled ? kTile + 1 : INT32_MAX;
   const int n_list = c->tiled ? std::max(n_phase, kTile) : n_phase;
   c->n_list = n_list;
   plan.block.assign(n_list, {});
@@ -564,10 +674,6 @@ int build_plan(rta_ctx* c, Plan& plan) {
     int kg = 0;
     for (int l = gr.l0; l < gr.l0 + gr.nl; ++l) kg = std::max(kg, T.kp[l * c->Q + q]);
     return kg;
-  };
-  // partitions of the items that serve one block each
-  auto near_rows = [&](const TierHost& T, const Group& gr, int q) {
-    return std::min(group_rows(T, gr, q), near_end);
   };
   // a multiply-accumulate item's per-output spectrum rows (Item::row, pend)
   auto mac_rows = [&](Item& it, const TierHost& T) {
@@ -589,9 +695,10 @@ int build_plan(rta_ctx* c, Plan& plan) {
   // ---- first tier: partitions >= 2, every phase
   std::vector<Item> tier0;
   std::vector<std::vector<Item>> far(n_list);  // K_TILE items, by the launch that runs them
-  std::map<std::tuple<int, int, int>, std::vector<Item>> units;  // by (input, chunk, groups)
   const TilePlan tile = tile_plan(c);
-  {
+  if (c->tiled) {
+    tile_items(c, tile, plan, tier0, far);
+  } else {
     TierHost& T = c->tier[0];
     // bin slices per row: each item covers W bins of nslice-fold more rows,
     // so an output group owns nslice-fold fewer partial slots for the heads
@@ -602,7 +709,7 @@ int build_plan(rta_ctx* c, Plan& plan) {
     int W = std::max(C, Wmax / std::max(1, c->bin_slices)), nslice = T.P / W;
     int64_t total_rows = 0;
     for (const Group& gr : plan.groups)
-      for (int q = 0; q < c->Q; ++q) total_rows += std::max(0, near_rows(T, gr, q) - 2);
+      for (int q = 0; q < c->Q; ++q) total_rows += std::max(0, group_rows(T, gr, q) - 2);
     // serving: every (group, input) owns the slots of a max_taps filter, so
     // a slot's meaning does not depend on which sources are present
     const int cap_rows = fixed ? std::max(0, T.kcap - 2) : 0;
@@ -628,7 +735,7 @@ int build_plan(rta_ctx* c, Plan& plan) {
           int64_t tot = 0, m = 0;
           for (const Group& gr : plan.groups) {
             int64_t ns = 0;
-            for (int q = 0; q < c->Q; ++q) ns += (std::max(0, near_rows(T, gr, q) - 2) + r - 1) / r;
+            for (int q = 0; q < c->Q; ++q) ns += (std::max(0, group_rows(T, gr, q) - 2) + r - 1) / r;
             tot += ns;
             m = std::max(m, ns);
           }
@@ -655,7 +762,7 @@ int build_plan(rta_ctx* c, Plan& plan) {
       // 60 ranges 27.5 us, 64 ranges 24.4 us)
       int kmax = 0;
       for (const Group& gr : plan.groups)
-        for (int q = 0; q < c->Q; ++q) kmax = std::max(kmax, near_rows(T, gr, q) - 2);
+        for (int q = 0; q < c->Q; ++q) kmax = std::max(kmax, group_rows(T, gr, q) - 2);
       if (fixed) kmax = std::max(0, T.kcap - 2);
       int step = kXcds;
       for (int qq = c->Q; qq % 2 == 0 && step > 1; qq /= 2) step /= 2;  // 8 / gcd(Q, 8)
@@ -679,7 +786,7 @@ int build_plan(rta_ctx* c, Plan& plan) {
         slot += gr.nslot;
       }
       for (int q = 0; q < c->Q; ++q) {
-        const int kg = near_rows(T, gr, q);
+        const int kg = group_rows(T, gr, q);
         if (kg <= 2) continue;  // partitions 0 and 1 are done by the heads
         const int rows = kg - 2;
         const int nch = (rows + R - 1) / R;
@@ -707,60 +814,11 @@ int build_plan(rta_ctx* c, Plan& plan) {
           }
         }
       }
-      // far partitions: chunks of about tile_rows rows, one slot each; the
-      // group's outputs in pairs, each pair's bin slices an item of their own
-      for (int q = 0; c->tiled && q < c->Q; ++q) {
-        const int rows = group_rows(T, gr, q) - near_end;
-        const int nch = rows > 0 ? (rows + tile.rows - 1) / tile.rows : 0;
-        for (int ch = 0; ch < nch; ++ch) {
-          for (int g0 = 0; g0 < gr.nl; g0 += tile_outputs(G)) {
-            Item it{};
-            it.kind = K_TILE;
-            it.group = g;
-            it.q = q;
-            it.p0 = near_end + (int)((int64_t)ch * rows / nch);
-            it.p1 = near_end + (int)((int64_t)(ch + 1) * rows / nch);
-            it.w = tile.W;
-            it.slot = slot;
-            it.acc = g0;
-            it.nl = std::min(tile_outputs(G), gr.nl - g0);
-            for (int i = 0; i < it.nl; ++i) {
-              const size_t pair = (size_t)(gr.l0 + g0 + i) * c->Q + q;
-              if (T.row[pair] < 0) continue;
-              it.row[i] = T.row[pair];
-              it.pend[i] = std::min(it.p1, T.kp[pair]);
-            }
-            it.tier = 0;
-            auto& unit = units[std::make_tuple(q, ch, g / tile.unit)];
-            for (int k0 = 0; k0 < T.P; k0 += tile.W) {
-              it.k0 = k0;
-              unit.push_back(it);
-            }
-          }
-          ++slot;
-          ++gr.nslot;
-        }
-      }
     }
     T.nslots = slot;
-    // every launch reads an eighth of the far rows, whole units at a time
-    std::vector<std::pair<int64_t, const std::vector<Item>*>> by_rows;
-    for (const auto& u : units) {
-      int64_t rows = 0;
-      for (const Item& it : u.second) rows += (int64_t)(it.p1 - it.p0) * it.nl;
-      by_rows.push_back({rows, &u.second});
-    }
-    std::stable_sort(by_rows.begin(), by_rows.end(),
-                     [](const auto& a, const auto& b) { return a.first > b.first; });
-    std::vector<int64_t> load(n_list, 0);
-    for (const auto& u : by_rows) {
-      const size_t ph = std::min_element(load.begin(), load.end()) - load.begin();
-      load[ph] += u.first;
-      far[ph].insert(far[ph].end(), u.second->begin(), u.second->end());
-    }
-    c->max_group_slots = 0;
-    for (const Group& gr : plan.groups) c->max_group_slots = std::max(c->max_group_slots, gr.nslot);
   }
+  c->max_group_slots = 0;
+  for (const Group& gr : plan.groups) c->max_group_slots = std::max(c->max_group_slots, gr.nslot);
 
   // ---- later tiers
   std::vector<std::vector<Item>> tier_mac(n_phase);
@@ -944,20 +1002,34 @@ int build_plan(rta_ctx* c, Plan& plan) {
   for (int ph = 0; ph < n_list; ++ph) {
     for (const Item& it : plan.block[ph]) {
       if (it.kind == K_NOP) continue;
-      if (it.kind == K_TILE) {
+      if (it.kind == K_TILE || it.kind == K_NEAR) {
         const TierHost& T = c->tier[0];
         const int W = it.w;
-        if (it.tier != 0 || it.group < 0 || it.group >= ngroups || it.q < 0 || it.q >= c->Q) return RTA_E_STATE;
+        if (it.tier != 0 || it.group < 0 || it.group >= ngroups || it.q < 0 || it.lag < 1 || it.q + it.lag > c->Q)
+          return RTA_E_STATE;
         const Group& gr = plan.groups[it.group];
-        if (T.K < 2 * kTile || it.p0 < kTile + 1 || it.p1 < it.p0 || it.p1 > T.K) return RTA_E_STATE;
-        if (W < 1 || W > kThreads || !is_pow2(W) || T.P % W != 0) return RTA_E_STATE;
-        if (it.k0 < 0 || it.k0 % W != 0 || it.k0 + W > T.P) return RTA_E_STATE;
-        if (it.nl < 1 || it.nl > tile_outputs(G) || it.acc < 0 || it.acc + it.nl > gr.nl) return RTA_E_STATE;
         if (it.slot < gr.slot0 || it.slot >= gr.slot0 + gr.nslot) return RTA_E_STATE;
-        for (int g = 0; g < it.nl; ++g)
-          if (it.pend[g] < 0 || it.pend[g] > it.p1 || it.row[g] < 0 ||
-              (it.pend[g] > 0 && it.row[g] + it.pend[g] > T.h_rows))
-            return RTA_E_STATE;
+        if (T.K < 2 * kTile + 2 || it.p1 < it.p0 || it.p1 > T.K || T.pair_row == nullptr) return RTA_E_STATE;
+        if (W < 1 || !is_pow2(W) || T.P % W != 0 || it.k0 < 0 || it.k0 % W != 0 || it.k0 + W > T.P) return RTA_E_STATE;
+        if (it.kind == K_NEAR) {
+          if (W < C || W > kThreads * C || it.p0 < 1 || it.p1 > it.p0 + kTile || it.nl != gr.nl) return RTA_E_STATE;
+        } else {
+          if (W > kThreads || it.p0 < kTile + 1) return RTA_E_STATE;
+          if (it.nl < 1 || it.nl > tile_outputs(G) || it.acc < 0 || it.acc + it.nl > gr.nl) return RTA_E_STATE;
+          for (int g = 0; g < it.nl; ++g)
+            if (it.pend[g] < 0 || it.pend[g] > it.p1 || it.row[g] < 0 ||
+                (it.pend[g] > 0 && it.row[g] + it.pend[g] > T.h_rows))
+              return RTA_E_STATE;
+        }
+        // the kernels take further inputs' rows from the pair tables (serving:
+        // the plan that sizes the buffers has partitions without rows; it is
+        // not uploaded)
+        for (int q = it.q; q < it.q + it.lag; ++q)
+          for (int l = gr.l0; l < gr.l0 + gr.nl; ++l) {
+            const size_t pair = (size_t)l * c->Q + q;
+            if (T.kp[pair] > 0 && (T.row[pair] < 0 ? !fixed : T.row[pair] + T.kp[pair] > T.h_rows))
+              return RTA_E_STATE;
+          }
         continue;
       }
       if (it.kind != K_MAC || it.tier < 0 || it.tier >= c->n_tiers) return RTA_E_STATE;
@@ -1147,7 +1219,8 @@ int64_t drain_end(const rta_ctx* c, int64_t m) {
     const TierHost& T = c->tier[t];
     const int64_t P = T.P, r = T.P / c->B;
     const int64_t fl = floor_div(m * c->B - 1, P) + 1;
-    const int64_t e = t == 0 ? fl + T.K + 1 : (fl + T.K + 1) * r + tier_nmac(c, t) + 3;
+    // (first tier: until the partial sums of every block kept are zero too)
+    const int64_t e = t == 0 ? fl + T.K + partial_blocks(c) - 1 : (fl + T.K + 1) * r + tier_nmac(c, t) + 3;
     end = std::max(end, e + 1);
   }
   return end;
@@ -1399,12 +1472,12 @@ int build_spectra(rta_ctx* c, const float* const* filters, const int64_t* length
 int upload_plan(rta_ctx* c, const Plan& plan, PlanDev& d, const std::vector<int32_t>& live,
                 hipStream_t s) {
   const size_t mb = (size_t)c->max_items, mt = (size_t)c->max_tier_items;
-  std::vector<Item> all_b((size_t)c->n_phase * mb, Item{}), all_t((size_t)c->n_phase * mt, Item{});
-  std::vector<int32_t> cnt_b(c->n_phase), cnt_t(c->n_phase);
+  std::vector<Item> all_b((size_t)c->n_list * mb, Item{}), all_t((size_t)c->n_list * mt, Item{});
+  std::vector<int32_t> cnt_b(c->n_list), cnt_t(c->n_list);
   for (auto& it : all_b) it.kind = K_NOP;
   for (auto& it : all_t) it.kind = K_NOP;
   int grid = 0;
-  for (int ph = 0; ph < c->n_phase; ++ph) {
+  for (int ph = 0; ph < c->n_list; ++ph) {
     std::vector<Item> lst = plan.block[ph];
     if (lst.size() > mb) {
       lst.erase(std::remove_if(lst.begin(), lst.end(), [](const Item& it) { return it.kind == K_NOP; }),
@@ -1455,17 +1528,17 @@ int serve_lists(rta_ctx* c, Plan& plan) {
   c->n_groups = (int)plan.groups.size();
   c->head_slots = (c->L + kXcds - 1) / kXcds * kXcds;
   size_t mb = 1, mt = 1;
-  for (int ph = 0; ph < c->n_phase; ++ph) {
+  for (int ph = 0; ph < c->n_list; ++ph) {
     mb = std::max(mb, cap.block[ph].size());
     mt = std::max(mt, cap.tier[ph].size());
   }
   c->max_items = (int)mb;
   c->max_tier_items = (int)mt;
   for (PlanDev& d : sv->dev) {
-    if ((st = dev_alloc(c, &d.items, (size_t)c->n_phase * mb)) != RTA_OK) return st;
-    if ((st = dev_alloc(c, &d.phase_count, (size_t)c->n_phase)) != RTA_OK) return st;
-    if ((st = dev_alloc(c, &d.tier_items, (size_t)c->n_phase * mt)) != RTA_OK) return st;
-    if ((st = dev_alloc(c, &d.tier_count, (size_t)c->n_phase)) != RTA_OK) return st;
+    if ((st = dev_alloc(c, &d.items, (size_t)c->n_list * mb)) != RTA_OK) return st;
+    if ((st = dev_alloc(c, &d.phase_count, (size_t)c->n_list)) != RTA_OK) return st;
+    if ((st = dev_alloc(c, &d.tier_items, (size_t)c->n_list * mt)) != RTA_OK) return st;
+    if ((st = dev_alloc(c, &d.tier_count, (size_t)c->n_list)) != RTA_OK) return st;
     for (int t = 0; t < c->n_tiers; ++t) {
       if ((st = dev_alloc(c, &d.pair_row[t], c->tier[t].row.size())) != RTA_OK) return st;
       if ((st = dev_alloc(c, &d.pair_K[t], c->tier[t].kp.size())) != RTA_OK) return st;
@@ -1603,21 +1676,17 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
   HIP_TRY(c, hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device));
 
 
-  // work lists
-  Plan plan;
-  if (sv != nullptr) {
-    if ((st = serve_lists(c, plan)) != RTA_OK) return st;
-  } else {
   // Far partitions tiled in time (kernels.hpp, mac_tile): uniform partitions,
   // unless the caller set the rows per item, once a delay line is longer than
   // two tiles (shorter ones have as many near rows as far ones) and the
   // partial sums of 2 kTile blocks take no more memory than the spectra (many
   // inputs with few partitions each would) or 64 MB
-  c->tiled = c->tile_ok && c->n_tiers == 1 && c->rows_per_item == 0 && c->tier[0].K >= 2 * kTile + 2;
+  c->tiled = c->tile_ok && c->n_tiers == 1 && c->rows_per_item == 0 && c->tier[0].K >= 2 * kTile + 2 &&
+             (int64_t)c->tier[0].K * c->tier[0].P <= (int64_t(1) << 28);  // 32-bit byte offsets
   if (c->tiled && (double)tile_plan(c).slots * 2 * kTile * c->G * c->tier[0].P * 8.0 >
                       std::max((double)(64 << 20), (double)c->spectra_bytes))
     c->tiled = false;
-  if (c->tiled) {  // far rows are streamed once in kTile blocks, and so are their delay-line slots
+  if (c->tiled && sv == nullptr) {  // far rows are streamed once in kTile blocks, and so are their delay-line slots
     const TierHost& T = c->tier[0];
     auto streamed = [](int kp) { return std::min(kp, kTile + 1) + std::max(0, kp - kTile - 1) / (double)kTile; };
     double rows = 0, tail_rows = 0;
@@ -1631,6 +1700,12 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
     c->x_bytes = (double)c->Q * streamed(kmax) * T.P * 8.0;
     c->tail_bytes = tail_rows * T.P * eb + (double)c->Q * std::max(0.0, streamed(kmax) - 2) * T.P * 8.0;
   }
+
+  // work lists
+  Plan plan;
+  if (sv != nullptr) {
+    if ((st = serve_lists(c, plan)) != RTA_OK) return st;
+  } else {
   if ((st = build_plan(c, plan)) != RTA_OK) return st;
   c->n_groups = (int)plan.groups.size();
   c->head_slots = (c->L + kXcds - 1) / kXcds * kXcds;  // keeps tails' XCD residues

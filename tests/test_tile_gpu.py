@@ -30,6 +30,7 @@ SHAPES = [
     (128, [[128 * 137]], 0), (128, [[128 * 138, 128 * 10, 128 * 9 + 1]], 0),
     (128, [[128 * (20 + 3 * l) - l for l in range(17)]], 0),      # two outputs per item, one left
     (128, [[128 * 40 - 5] * 3 for _ in range(5)], 0),             # more inputs than a head prefetches
+    (64, [[64 * 20 - q, 64 * 18 + q, 0 if q % 3 else 64 * 40] for q in range(40)], 0),  # several inputs per slot
     (256, [[256 * 70 + 100, 256 * 30]], 0),
     (512, [[512 * 40, 512 * 33 + 7]], 0),
     (4096, [[4096 * 19, 5]], 0),
