@@ -177,9 +177,10 @@ __device__ __forceinline__ constexpr int brev_small(int s) {
 }
 
 // v of lane (lane ^ H) for a butterfly partner at distance H: quad
-// permutations (DPP, a VALU operand modifier) for 1 and 2, the LDS
-// crossbar's swizzle (bit mode, xor mask; no address operand) for 4 to 16,
-// the gfx950 half-wave swap (VALU) for 32.
+// permutations (DPP, a VALU operand modifier) for 1 and 2, a rotation of the
+// 16-lane row by 8 (DPP) for 8, the LDS crossbar's swizzle (bit mode, xor
+// mask; no address operand) for 4 and 16, the gfx950 half-wave swap (VALU)
+// for 32.
 template <int H>
 __device__ __forceinline__ float lane_xor(float v, int lane) {
   const int i = __float_as_int(v);
@@ -188,6 +189,8 @@ __device__ __forceinline__ float lane_xor(float v, int lane) {
     o = __builtin_amdgcn_mov_dpp(i, 0xB1, 0xF, 0xF, false);  // quad_perm [1, 0, 3, 2]
   else if constexpr (H == 2)
     o = __builtin_amdgcn_mov_dpp(i, 0x4E, 0xF, 0xF, false);  // quad_perm [2, 3, 0, 1]
+  else if constexpr (H == 8)
+    o = __builtin_amdgcn_mov_dpp(i, 0x128, 0xF, 0xF, false);  // row_ror 8
   else if constexpr (H < 32)
     o = __builtin_amdgcn_ds_swizzle(i, 0x1F | (H << 10));  // and 0x1f, or 0, xor H
   else {
@@ -255,6 +258,117 @@ __device__ __forceinline__ void fft_wave_one(const float2* __restrict__ src, flo
   const int k2 = (int)(__brev((unsigned int)lane) >> 26);
 #pragma unroll
   for (int s = 0; s < V; ++s) dst[brev_small<V>(s) + V * k2] = r[s];
+}
+
+// ---------------------------------------------------------------------------
+// The same transform (N = 64 V points, V in {1, 2, 4}) entirely in one
+// wavefront's registers, twiddles included: lane i holds x[64 v + i] in
+// register v, and afterwards X[brev_small(s) + V brev6(i)] in register s.
+// The twiddles are requested once, long before they are needed, and serve the
+// forward and (conjugated) the inverse transform.  A stage's twiddle is 1 in
+// the lanes that keep the sum, so each stage is one fused multiply-add by +-1
+// and one complex product per value, without selects: a wavefront alone on
+// its SIMD issues an instruction every 4.6 cycles, and the transform's time is
+// its instruction count.
+// ---------------------------------------------------------------------------
+template <int V>
+struct WaveTw {
+  float2 in[V > 1 ? V - 1 : 1];  // W_N^{lane k1}, of register s = k1's bit reversal (s >= 1)
+  float2 st[5];                  // stages at distance 32, 16, 8, 4, 2
+};
+template <int V>
+__device__ __forceinline__ WaveTw<V> wave_twiddles(const float2* __restrict__ tw, int lane) {
+  constexpr int N = 64 * V;
+  WaveTw<V> t;
+#pragma unroll
+  for (int s = 1; s < V; ++s) t.in[s - 1] = tw[lane * brev_small<V>(s)];
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    const int H = 32 >> i;
+    t.st[i] = tw[(lane & H) ? (lane & (H - 1)) * (N / (2 * H)) : 0];
+  }
+  return t;
+}
+template <bool INV>
+__device__ __forceinline__ float2 cmul_tw(float2 a, float2 w) {
+  return INV ? make_float2(a.x * w.x + a.y * w.y, a.y * w.x - a.x * w.y)
+             : make_float2(a.x * w.x - a.y * w.y, a.x * w.y + a.y * w.x);
+}
+template <bool INV, int V, int H>
+__device__ __forceinline__ void wave_reg_stage(float2 (&r)[V], float2 w, int lane) {
+  const float sg = (lane & H) ? -1.f : 1.f;
+#pragma unroll
+  for (int s = 0; s < V; ++s) {
+    const float2 t = make_float2(fmaf(sg, r[s].x, lane_xor<H>(r[s].x, lane)), fmaf(sg, r[s].y, lane_xor<H>(r[s].y, lane)));
+    r[s] = H > 1 ? cmul_tw<INV>(t, w) : t;
+  }
+}
+template <bool INV, int V>
+__device__ __forceinline__ void wave_fft(float2 (&r)[V], const WaveTw<V>& t, int lane) {
+  if constexpr (V == 2) {
+    const float2 p = r[0], q = r[1];
+    r[0] = cadd(p, q);
+    r[1] = csub(p, q);
+  } else if constexpr (V == 4) {
+    const float2 s02 = cadd(r[0], r[2]), d02 = csub(r[0], r[2]);
+    const float2 s13 = cadd(r[1], r[3]), d13 = csub(r[1], r[3]);
+    const float2 jd = INV ? make_float2(-d13.y, d13.x) : make_float2(d13.y, -d13.x);
+    r[0] = cadd(s02, s13);  // k1 = 0
+    r[1] = csub(s02, s13);  // k1 = 2
+    r[2] = cadd(d02, jd);   // k1 = 1
+    r[3] = csub(d02, jd);   // k1 = 3
+  }
+#pragma unroll
+  for (int s = 1; s < V; ++s) r[s] = cmul_tw<INV>(r[s], t.in[s - 1]);
+  wave_reg_stage<INV, V, 32>(r, t.st[0], lane);
+  wave_reg_stage<INV, V, 16>(r, t.st[1], lane);
+  wave_reg_stage<INV, V, 8>(r, t.st[2], lane);
+  wave_reg_stage<INV, V, 4>(r, t.st[3], lane);
+  wave_reg_stage<INV, V, 2>(r, t.st[4], lane);
+  wave_reg_stage<INV, V, 1>(r, make_float2(1.f, 0.f), lane);
+}
+// Orders a wavefront's own LDS accesses (its LDS operations execute in order;
+// this keeps the compiler from reordering them).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+// wave_fft's result to natural order in `dst` (LDS, N values).
+template <int V>
+__device__ __forceinline__ void wave_store(const float2 (&r)[V], float2* dst, int lane) {
+  const int k2 = (int)(__brev((unsigned int)lane) >> 26);
+#pragma unroll
+  for (int s = 0; s < V; ++s) dst[brev_small<V>(s) + V * k2] = r[s];
+}
+
+// Real-transform pairs in one wavefront: pair register i of lane j holds bins
+// k = 64 i + j and N - k (k = 0: bins 0 and N / 2), N / 2 pairs in all
+// (V = 1: lanes below 32).  The split and its inverse only ever combine the
+// two bins of a pair, so everything between the transforms stays in a lane's
+// registers.
+template <int V>
+__host__ __device__ constexpr int wave_pairs() { return V == 4 ? 2 : 1; }
+template <int V>
+__device__ __forceinline__ int pair_hi(int k) { return k == 0 ? 32 * V : 64 * V - k; }
+
+// Packed bins (rfft_post) of pair (k, pair_hi(k)) from the transform's values
+// za = Z[k], zb = Z[pair_hi(k)]; w = W_2N^k.
+__device__ __forceinline__ void pair_post(float2& za, float2& zb, float2 w, bool first) {
+  const float2 a = za, b = cconj(zb);
+  const float2 E = make_float2(0.5f * (a.x + b.x), 0.5f * (a.y + b.y));
+  const float2 d = csub(a, b);
+  const float2 O = make_float2(0.5f * d.y, -0.5f * d.x);  // -i d / 2
+  const float2 wO = cmul(w, O);
+  za = first ? make_float2(a.x + a.y, a.x - a.y) : cadd(E, wO);
+  zb = first ? b : cconj(csub(E, wO));
+}
+// Inverse split (irfft_pre) of a pair of packed bins.
+__device__ __forceinline__ void pair_pre(float2& ya, float2& yb, float2 w, bool first) {
+  const float2 a = ya, b = cconj(yb);
+  const float2 E = cadd(a, b);
+  const float2 O = cmul_tw<true>(csub(a, b), w);
+  ya = first ? make_float2(a.x + a.y, a.x - a.y) : make_float2(E.x - O.y, E.y + O.x);
+  yb = first ? make_float2(2.f * b.x, 2.f * b.y) : make_float2(E.x + O.y, O.x - E.y);
 }
 
 // Batched complex FFT of length N in {64, 128}: transform t is run

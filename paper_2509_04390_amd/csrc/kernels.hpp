@@ -159,6 +159,8 @@ struct KArgs {
   int32_t tails_wait;        // rta_process: multiply-accumulate workgroups
                              // start once this launch's heads are done
   int64_t n;                 // index of the block of this launch
+  int32_t slot;              // its slot in the first tier's delay line, n mod K
+  int32_t fc_slot;           // and in the feedback delay line
   const Item* tier_items;    // later tiers' transform passes [n_phase][max_tier_items]
   const int32_t* tier_count; // transform items per phase
   const int32_t* tier_slot0; // [tier][group] first partial slot of later tiers
@@ -180,8 +182,9 @@ struct KArgs {
                              // to the feedback convolution (no transform of y)
   int32_t* status;           // host-visible error word: a wait that gave up
                              // stores 1 (system scope); checked by the host
-  const int64_t* n_base;     // graph replay: the block index is *n_base + n
-                             // (null: n itself)
+  const int64_t* n_base;     // graph replay: the block index is n_base[0] + n
+                             // (null: n itself) and its slots those of
+                             // n_base[1], n_base[2] plus slot, fc_slot
   FcArgs fc;
 };
 
@@ -361,11 +364,11 @@ __device__ __forceinline__ void store_sums(const float (&acc)[G][C][4], float2* 
 
 // ---------------------------------------------------------------------------
 // Multiply-accumulate of one item's partitions into its partial-sum slot.
-// `frame` is the frame whose delay-line head is slot frame mod K (partition
-// p pairs with slot (frame - p) mod K).
+// Slot sf holds the frame's own spectrum (partition p pairs with slot
+// (sf - p) mod K).
 // ---------------------------------------------------------------------------
 template <typename HT, int G, bool NT>
-__device__ __forceinline__ void mac_item(const DevTier& T, const Item& it, int64_t frame, float2* red) {
+__device__ __forceinline__ void mac_item(const DevTier& T, const Item& it, int sf, float2* red) {
   constexpr int C = HVec<HT>::C;
   const int P = T.P;
   const int W = it.w;                                  // bins per item slice
@@ -396,7 +399,8 @@ __device__ __forceinline__ void mac_item(const DevTier& T, const Item& it, int64
   const float2* Xq = T.X + (int64_t)q * K * P + kb;
   const int step = RP % K;
   int p = it.p0 + s;
-  int slot = wrap_slot(frame - p, K);
+  int slot = sf - p % K;
+  if (slot < 0) slot += K;
   // U rows in flight per lane: every load of a pass is issued before any
   // is used (raw registers), then the pass is accumulated
   constexpr int U = HVec<HT>::U;
@@ -440,7 +444,7 @@ __device__ __forceinline__ void mac_item(const DevTier& T, const Item& it, int64
 }
 
 // ---------------------------------------------------------------------------
-// Near partitions of several inputs, for block b: lanes take (input,
+// Near partitions of several inputs, for block b (delay-line slot s0): lanes take (input,
 // partition) pairs of the item in turn (8 partitions to an input, those from
 // p1 on left out).  One slot per group for up to kNearInputs inputs keeps the
 // heads' reduction short where many inputs feed an output.
@@ -448,7 +452,7 @@ __device__ __forceinline__ void mac_item(const DevTier& T, const Item& it, int64
 constexpr int kNearInputs = 16;
 
 template <typename HT, int G, bool NT>
-__device__ __forceinline__ void mac_near(const DevTier& T, const Item& it, int64_t b, int Q, float2* red) {
+__device__ __forceinline__ void mac_near(const DevTier& T, const Item& it, int64_t b, int s0, int Q, float2* red) {
   constexpr int C = HVec<HT>::C, U = HVec<HT>::U;
   typedef typename HVec<HT>::raw_t raw_t;
   const int P = T.P, K = T.K, W = it.w;
@@ -457,7 +461,6 @@ __device__ __forceinline__ void mac_near(const DevTier& T, const Item& it, int64
   const int r = tid % LR, s = tid / LR;
   const int kb = it.k0 + r * C;
   const HT* H = reinterpret_cast<const HT*>(T.H) + kb;
-  const int s0 = wrap_slot(b, K);
   const int J = it.lag * kTile;
   float acc[G][C][4];
 #pragma unroll
@@ -504,7 +507,8 @@ __device__ __forceinline__ void mac_near(const DevTier& T, const Item& it, int64
 }
 
 // ---------------------------------------------------------------------------
-// Far partitions, tiled in time, for blocks b .. b + kTile - 1.  Partition
+// Far partitions, tiled in time, for blocks b (delay-line slot s0) ..
+// b + kTile - 1.  Partition
 // p >= kTile + 1 of a block pairs with the spectrum of p blocks earlier, which
 // exists kTile blocks before the block does: one reading of its row in launch
 // n serves the blocks n + 1 .. n + kTile (their newest spectrum is
@@ -534,7 +538,7 @@ __device__ __forceinline__ void mac_near(const DevTier& T, const Item& it, int64
 __host__ __device__ constexpr int tile_outputs(int G) { return G < 2 ? 1 : 2; }
 
 template <typename HT, int G, bool NT>
-__device__ __forceinline__ void mac_tile(const DevTier& T, const Item& it, int64_t b, int Q, float2* red) {
+__device__ __forceinline__ void mac_tile(const DevTier& T, const Item& it, int64_t b, int s0, int Q, float2* red) {
   constexpr int GF = tile_outputs(G), M = kTile, U = kTile;
   const int P = T.P, K = T.K, W = it.w;
   const int lw = 31 - __builtin_clz(W);
@@ -548,7 +552,7 @@ __device__ __forceinline__ void mac_tile(const DevTier& T, const Item& it, int64
   const uint32_t xrow = (uint32_t)P * sizeof(float2), xend = (uint32_t)K * xrow;
   const uint32_t hrow = (uint32_t)P * sizeof(HT);
   // ring offset of X(b - (pa + U - 1))
-  int sl = wrap_slot(b, K) - (pa + U - 1);
+  int sl = s0 - (pa + U - 1);
   if (sl < 0) sl += K;
   if (sl < 0) sl += K;
   const uint32_t xo0 = (uint32_t)sl * xrow;
@@ -1266,6 +1270,351 @@ __device__ __forceinline__ void head_work(const KArgs& A, int64_t n, const Group
   }
 }
 
+// ---------------------------------------------------------------------------
+// Head workgroup of block n for one output, first tiers of 64, 128 and 256
+// bins (P = B = 64 V): a wavefront per input and no workgroup barrier but one.
+//
+// A head is a chain of dependent steps on a few hundred values; with one or
+// two wavefronts per SIMD its time is the number of instructions and round
+// trips on that chain, not bandwidth.  So:
+//   - Wavefront w transforms the inputs w, w + 4, ... in registers (wave_fft);
+//     the next input's operands are requested before the current one's
+//     transform.
+//   - The split bins of a pair (k, P - k) stay in one lane from the forward
+//     split to the inverse one: spectrum out, p = 0 and p = 1 terms and this
+//     wavefront's quarter of the partial slots are added there.
+//   - The four wavefronts' sums meet once, in LDS; wavefront 0 transforms back
+//     and emits.
+//   - No divisions: the ring slot of block n comes with the launch.
+// Heads end, after the launch's first workgroup (with head_work's
+// workgroup-wide passes over LDS, a barrier each, and 64-bit divisions):
+// 1 -> 32 x 480,000 taps, B = 128 FP32 5.0 us (8.8); 4 -> 64, 128/1024/8192
+// FP16 4.4 (10.0); 3 -> 20 ragged, B = 64 BF16 4.0 (8.2).
+// ---------------------------------------------------------------------------
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));  // user buffers: 4-byte aligned
+__device__ __forceinline__ f32x2u load_pair(const float* p) {  // in device memory (see load_at)
+  return *(const __attribute__((address_space(1))) f32x2u*)p;
+}
+
+// First tiers whose heads run by wavefronts.  256 bins take 156 registers:
+// not with 16-bit spectra, whose kernels' far items run four waves per SIMD.
+template <typename HT>
+__host__ __device__ constexpr bool head_waves(int P) {
+  return P == 64 || P == 128 || (P == 256 && sizeof(HT) == 8);
+}
+template <int V>
+__host__ __device__ constexpr int head_wave_lds() { return 4 * 64 * V + 3 * 2 * wave_pairs<V>() * 64; }
+
+template <typename HT, int G, int V>
+__device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int scn, const Group& grp, int l,
+                                          float2* lds) {
+  constexpr int N = 64 * V, NP = wave_pairs<V>(), SL = V == 4 ? 4 : 8;
+  constexpr int VO = V == 4 ? 2 : 1;  // output sample pairs per lane
+  constexpr int VC = V == 4 ? 2 : 1;  // window registers with samples of this block: the last VC
+  typedef typename HVec<HT>::one_t one_t;
+  const DevTier& T = A.tier[0];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int K = T.K, B = N, Q = A.Q;  // (P = B)
+  const int sp = sn == 0 ? K - 1 : sn - 1;
+  float2* zb = lds + w * N;
+  float2* red = lds + 4 * N;
+  // pairs: lanes below 32 alone where N / 2 = 32; the other half then takes
+  // other partial slots of the same pairs
+  const int pl = V == 1 ? (lane & 31) : lane, hw = V == 1 ? lane >> 5 : 0;
+  const bool act = V > 1 || lane < 32;
+  const bool first = pl == 0;  // (pair register 0: bins 0 and N / 2)
+  int ka[NP], kb[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    ka[i] = 64 * i + pl;
+    kb[i] = pair_hi<V>(ka[i]);
+  }
+
+  // ---- requests, in the order they are needed
+  struct In {
+    f32x2u w[V], s[VC];  // window sample pairs; feedback estimate of the block's
+    int live;
+    one_t h0[2 * NP], h1[2 * NP];
+    float2 x1[2 * NP];
+  };
+  const int64_t hlen = A.hist_mask + 1;
+  const int64_t hprev = ((n - 1) * B) & A.hist_mask, hcur = (n * B) & A.hist_mask;
+  auto window = [&](int q, In& in) {
+    const float* ph = A.hist + q * hlen + hprev;
+    const float* pi = A.in + (int64_t)q * B;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const int i = 2 * (64 * v + lane);
+      const bool cur = V == 1 ? lane >= 32 : 2 * v >= V;
+      in.w[v] = load_pair(cur ? pi + (i - B) : ph + i);
+      if (v < V - VC) continue;
+      in.s[v - (V - VC)] = f32x2u{0.f, 0.f};
+      if (A.sub != nullptr) {  // microphone minus the previous block's feedback estimate
+        const float* ps = A.sub + (int64_t)q * B + max(i - B, 0);
+        // (fused: written in this launch by another workgroup, so read where
+        // every XCD sees it)
+        in.s[v - (V - VC)] = A.fc_on ? f32x2u{__hip_atomic_load(ps, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM),
+                                   __hip_atomic_load(ps + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)}
+                                         : load_pair(ps);
+      }
+    }
+    in.live = A.live != nullptr ? A.live[q] : 1;
+  };
+  auto operands = [&](int q, In& in) {
+    const char* h = reinterpret_cast<const char*>(reinterpret_cast<const HT*>(A.H01) + (int64_t)(l * Q + q) * 2 * N);
+    const char* x = reinterpret_cast<const char*>(T.X + ((int64_t)q * K + sp) * N);
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const uint32_t k = c ? kb[i] : ka[i];
+        in.h0[2 * i + c] = load_at<false>(h, k * (uint32_t)sizeof(HT), one_t{});
+        in.h1[2 * i + c] = load_at<false>(h, (N + k) * (uint32_t)sizeof(HT), one_t{});
+        in.x1[2 * i + c] = load_at<false>(x, k * 8u, float2{});
+      }
+  };
+  // (unconditional, at clamped inputs: a wavefront without one uses nothing)
+  In in;
+  const int q0 = min(w, Q - 1);
+  if (!A.fc_on) window(q0, in);
+  const WaveTw<V> tw = wave_twiddles<V>(T.tw, lane);
+  float2 tw2[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) tw2[i] = T.tw[N + ka[i]];
+  operands(q0, in);
+  // this wavefront's (half-wave's) contiguous share of the group's slots
+  const int64_t stride = (int64_t)G * N;
+  const float2* base = T.partial + (n & T.pmask) * (int64_t)T.nslots * stride + (int64_t)grp.slot0 * stride +
+                       (int64_t)(l - grp.l0) * N;
+  constexpr int parts = V == 1 ? 8 : 4;
+  const int part = V == 1 ? 2 * w + hw : w;
+  const int per = (grp.nslot + parts - 1) / parts;
+  const int s0 = min(part * per, grp.nslot), s1 = min(s0 + per, grp.nslot);
+  float2 ps[SL][2 * NP];
+  {
+    // (a valid address without slots; clamped within the share, which starts
+    // at the wavefront's first slot, `from`)
+    const int from = min((V == 1 ? 2 * w : w) * per, max(grp.nslot - 1, 0));
+    const char* src = reinterpret_cast<const char*>(grp.nslot > 0 ? base + from * stride : T.tw);
+    const uint32_t step = grp.nslot > 0 ? (uint32_t)stride * 8u : 0u;
+    const int lim = max(grp.nslot - 1 - from, 0);
+#pragma unroll
+    for (int j = 0; j < SL; ++j) {
+      const uint32_t at = (uint32_t)min(hw * per + j, lim) * step;
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        ps[j][2 * i] = load_at<false>(src, at + ka[i] * 8u, float2{});
+        ps[j][2 * i + 1] = load_at<false>(src, at + kb[i] * 8u, float2{});
+      }
+    }
+  }
+  // later tiers' ring samples of this block (wavefront 0 emits)
+  constexpr int TMAX = 2;
+  const int mo = V == 1 ? pl : VO * lane;  // this lane's first output sample pair
+  const int64_t rpos = ((n * B) & A.ring_mask) + 2 * mo;
+  float2 rv[TMAX][VO];
+#pragma unroll
+  for (int t = 0; t < TMAX; ++t)
+    if (t + 1 < A.n_tiers) {
+      const float2* p = reinterpret_cast<const float2*>(A.tier[t + 1].oring + (int64_t)l * (A.ring_mask + 1) + rpos);
+#pragma unroll
+      for (int j = 0; j < VO; ++j) rv[t][j] = p[j];
+    }
+  if (A.fc_on) {  // the block's window needs c_{n-1} of this launch's feedback heads
+    fc_wait(A, n);
+    window(q0, in);
+  }
+
+  // ---- this wavefront's inputs: window -> spectrum -> ring, terms p = 0, 1
+  float2 ya[NP], yb[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) ya[i] = yb[i] = make_float2(0.f, 0.f);
+  for (int q = w; q < Q; q += 4) {
+    In next;
+    if (V < 4 && q + 4 < Q) {  // (256 bins: too many registers)
+      window(q + 4, next);
+      operands(q + 4, next);
+    }
+    float2 r[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const bool cur = V == 1 ? lane >= 32 : 2 * v >= V;
+      const float2 x = make_float2(pin(in.w[v].x), pin(in.w[v].y));
+      r[v] = x;
+      if (v >= V - VC) {
+        const f32x2u e = in.s[v - (V - VC)];
+        // (a select: NaN of a slot that is not live stays out)
+        if (cur) r[v] = in.live == 0 ? make_float2(0.f, 0.f) : make_float2(x.x - e.x, x.y - e.y);
+      }
+      // the first output's head keeps the block's input, as windowed
+      if (l == 0 && cur) {
+        float2* ph = reinterpret_cast<float2*>(A.hist + q * hlen + hcur + 2 * (64 * v + lane) - B);
+        *ph = r[v];
+      }
+    }
+    wave_fft<false, V>(r, tw, lane);
+    wave_lds_fence();
+    wave_store<V>(r, zb, lane);
+    wave_lds_fence();
+    float2* xn = T.X + ((int64_t)q * K + sn) * N;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const bool f = first && i == 0;
+      float2 xa = zb[ka[i]], xb = zb[kb[i]];
+      pair_post(xa, xb, tw2[i], f);
+      if (l == 0 && act) {  // and its spectrum, for later launches
+        xn[ka[i]] = xa;
+        xn[kb[i]] = xb;
+      }
+      if (act) {
+        auto term = [&](one_t hr, float2 x, bool packed) {
+          const float2 h = HVec<HT>::cvt1(pin(hr));
+          return packed ? make_float2(h.x * x.x, h.y * x.y) : cmul(h, x);
+        };
+        ya[i] = cadd(ya[i], term(in.h0[2 * i], xa, f));
+        yb[i] = cadd(yb[i], term(in.h0[2 * i + 1], xb, false));
+        if (K >= 2) {
+          ya[i] = cadd(ya[i], term(in.h1[2 * i], in.x1[2 * i], f));
+          yb[i] = cadd(yb[i], term(in.h1[2 * i + 1], in.x1[2 * i + 1], false));
+        }
+      }
+    }
+    if (V < 4) {
+      in = next;
+    } else if (q + 4 < Q) {
+      window(q + 4, in);
+      operands(q + 4, in);
+    }
+  }
+  // ---- the terms p >= 2, prepared by earlier launches' tails
+#pragma unroll
+  for (int j = 0; j < SL; ++j)
+    if (s0 + j < s1) {
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        ya[i] = cadd(ya[i], pin(ps[j][2 * i]));
+        yb[i] = cadd(yb[i], pin(ps[j][2 * i + 1]));
+      }
+    }
+  for (int s = s0 + SL; s < s1; ++s)
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      ya[i] = cadd(ya[i], base[s * stride + ka[i]]);
+      yb[i] = cadd(yb[i], base[s * stride + kb[i]]);
+    }
+  if constexpr (V == 1) {
+    ya[0] = cadd(ya[0], make_float2(lane_xor<32>(ya[0].x, lane), lane_xor<32>(ya[0].y, lane)));
+    yb[0] = cadd(yb[0], make_float2(lane_xor<32>(yb[0].x, lane), lane_xor<32>(yb[0].y, lane)));
+  }
+  if (w > 0) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      red[(((w - 1) * NP + i) * 2) * 64 + lane] = ya[i];
+      red[(((w - 1) * NP + i) * 2 + 1) * 64 + lane] = yb[i];
+    }
+  }
+  __syncthreads();
+  if (w > 0) return;
+
+  // ---- inverse transform, the second half of the samples (overlap-save), the
+  //      later tiers' contributions from their output rings
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+#pragma unroll
+    for (int v = 0; v < 3; ++v) {
+      ya[i] = cadd(ya[i], red[((v * NP + i) * 2) * 64 + lane]);
+      yb[i] = cadd(yb[i], red[((v * NP + i) * 2 + 1) * 64 + lane]);
+    }
+    pair_pre(ya[i], yb[i], tw2[i], first && i == 0);
+    if (act) {
+      zb[ka[i]] = ya[i];
+      zb[kb[i]] = yb[i];
+    }
+  }
+  wave_lds_fence();
+  float2 r[V];
+#pragma unroll
+  for (int v = 0; v < V; ++v) r[v] = zb[64 * v + lane];
+  wave_fft<true, V>(r, tw, lane);
+  // samples m >= N / 2 are in the odd lanes; to natural order in LDS
+  wave_lds_fence();
+  if (lane & 1) wave_store<V>(r, zb - N / 2, lane);
+  wave_lds_fence();
+  const float scale = 1.0f / (float)(2 * N);
+  float2 y[VO];
+#pragma unroll
+  for (int j = 0; j < VO; ++j) {
+    float2 t = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int k = 0; k < TMAX; ++k)
+      if (k + 1 < A.n_tiers) t = cadd(t, pin(rv[k][j]));
+    for (int k = TMAX + 1; k < A.n_tiers; ++k)
+      t = cadd(t, *reinterpret_cast<const float2*>(A.tier[k].oring + (int64_t)l * (A.ring_mask + 1) + rpos + 2 * j));
+    const float2 v = zb[mo + j];
+    y[j] = make_float2(t.x + v.x * scale, t.y + v.y * scale);
+  }
+  if (act) {
+#pragma unroll
+    for (int j = 0; j < VO; ++j) {
+      const f32x2u o = {y[j].x, y[j].y};
+      *reinterpret_cast<f32x2u*>(A.out + (int64_t)l * B + 2 * (mo + j)) = o;
+      if (A.out2 != nullptr) *reinterpret_cast<f32x2u*>(A.out2 + (int64_t)l * B + 2 * (mo + j)) = o;
+      for (int t = 1; t < A.n_tiers; ++t)
+        *reinterpret_cast<float2*>(A.tier[t].oring + (int64_t)l * (A.ring_mask + 1) + rpos + 2 * j) =
+            make_float2(0.f, 0.f);
+    }
+  }
+  // this head's output is out: the tail workgroups of a waiting launch may
+  // start streaming (relaxed: they read nothing the heads wrote)
+  if (lane == 0) __hip_atomic_fetch_add(A.heads_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // completion (rta_process only): every head makes its output visible
+  // system-wide, the last one raises the flag
+  if (A.done_flag != nullptr) {
+    __threadfence_system();
+    if (lane == 0) {
+      const unsigned int old = __hip_atomic_fetch_add(A.head_count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_SYSTEM);
+      if (old == (unsigned int)A.n_head - 1u) {
+        __hip_atomic_store(A.head_count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(A.done_flag, n + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+      }
+    }
+  }
+  // fused feedback: this output is input l of the feedback convolution; its
+  // window [y_l(n-1), y_l(n)] goes into the feedback delay line (slot scn)
+  if (!A.fc_on) return;
+  const FcArgs& F = A.fc;
+  float* hl = F.hist + (int64_t)l * (F.hist_mask + 1);
+  const int64_t yprev = ((n - 1) * B) & F.hist_mask, ycur = (n * B) & F.hist_mask;
+  if (act)
+#pragma unroll
+    for (int j = 0; j < VO; ++j) zb[mo + j] = y[j];
+  wave_lds_fence();
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    const int m = 64 * v + lane;
+    const bool cur = V == 1 ? lane >= 32 : 2 * v >= V;
+    r[v] = cur ? zb[max(m - N / 2, 0)] : *reinterpret_cast<const float2*>(hl + yprev + 2 * min(m, N / 2 - 1));
+  }
+  if (act)
+#pragma unroll
+    for (int j = 0; j < VO; ++j) *reinterpret_cast<float2*>(hl + ycur + 2 * (mo + j)) = y[j];
+  wave_fft<false, V>(r, tw, lane);
+  wave_lds_fence();
+  wave_store<V>(r, zb, lane);
+  wave_lds_fence();
+  float2* dst = F.T.X + ((int64_t)l * F.T.K + scn) * N;
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    float2 xa = zb[ka[i]], xb = zb[kb[i]];
+    pair_post(xa, xb, tw2[i], first && i == 0);
+    if (act) {
+      dst[ka[i]] = xa;
+      dst[kb[i]] = xb;
+    }
+  }
+}
+
 // Feedback head of the fused launch n: output j of the feedback convolution
 // for block n - 1, c_j = IFFT(sum of its partial slots (its items of launch
 // n - 1) + sum_l F_{j,l,1} Y'_l(n-2) + F_{j,l,0} Y'_l(n-1)), the second half
@@ -1609,7 +1958,15 @@ __global__ __launch_bounds__(kThreads, sizeof(HT) == 4 ? 4 : 3) void k_block(con
     asm volatile("" ::"s"(nb), "s"(n0), "s"(fc), "s"(fs), "s"(fh), "s"(hs), "s"(nh), "s"(ts), "s"(np), "s"(mi),
                  "s"(tw), "s"(it), "s"(gr));
   }
-  const int64_t n = A.n_base != nullptr ? *A.n_base + A.n : A.n;
+  int64_t n = A.n;
+  int sn = A.slot, scn = A.fc_slot;
+  if (A.n_base != nullptr) {
+    n += A.n_base[0];
+    sn += (int)A.n_base[1];
+    if (sn >= A.tier[0].K) sn -= A.tier[0].K;
+    scn += (int)A.n_base[2];
+    if (A.fc_on && scn >= A.fc.T.K) scn -= A.fc.T.K;
+  }
   int b = blockIdx.x;
   if (A.fc_on) {  // grid: feedback heads | heads | transforms | tails | feedback tails
     if (b < A.fc.head_slots) {
@@ -1621,6 +1978,20 @@ __global__ __launch_bounds__(kThreads, sizeof(HT) == 4 ? 4 : 3) void k_block(con
   if (b < A.head_slots) {
     if (b < A.n_head) {  // head b: output b, in group b / G
       const Group g0 = A.groups[b / G];
+      const int P = A.tier[0].r3 ? 0 : A.tier[0].P;
+      if (P == 128) {
+        head_wave<HT, G, 2>(A, n, sn, scn, g0, b, lds);
+        return;
+      }
+      if (P == 64) {
+        head_wave<HT, G, 1>(A, n, sn, scn, g0, b, lds);
+        return;
+      }
+      if constexpr (head_waves<HT>(256))
+        if (P == 256) {
+          head_wave<HT, G, 4>(A, n, sn, scn, g0, b, lds);
+          return;
+        }
       Group hg = g0;
       hg.l0 = b;
       hg.nl = 1;
@@ -1661,7 +2032,7 @@ __global__ __launch_bounds__(kThreads, sizeof(HT) == 4 ? 4 : 3) void k_block(con
     if (it.kind == K_NOP) return;
     DevTier T = A.fc.T;
     T.partial += (n & 1) * (int64_t)T.nslots * G * T.P;
-    mac_item<HT, G, NT>(T, it, n, lds);
+    mac_item<HT, G, NT>(T, it, scn, lds);
     return;
   }
   // (the tail part of the grid is at most max_items long, and a phase's
@@ -1671,30 +2042,37 @@ __global__ __launch_bounds__(kThreads, sizeof(HT) == 4 ? 4 : 3) void k_block(con
   asm volatile("" ::"s"(T.H), "s"(T.X), "s"(T.partial), "s"(T.K), "s"(T.P), "s"(T.nslots));
   const Item it = A.items[(int64_t)phase * A.max_items + i];
   if (it.kind == K_NOP) return;
+  const int s1 = sn + 1 == T.K ? 0 : sn + 1;  // block n + 1's slot
   if (it.kind == K_TILE) {
-    mac_tile<HT, G, NT>(T, it, n + 1, A.Q, lds);
+    mac_tile<HT, G, NT>(T, it, n + 1, s1, A.Q, lds);
     return;
   }
   if (it.kind == K_NEAR) {
-    mac_near<HT, G, NT>(T, it, n + 1, A.Q, lds);
+    mac_near<HT, G, NT>(T, it, n + 1, s1, A.Q, lds);
     return;
   }
   if (it.tier != 0) T = A.tier[it.tier];
-  int64_t frame;
+  int sf;
   if (it.tier == 0) {
-    frame = n + 1;  // first-tier tails prepare the next block
-    T.partial += (frame & T.pmask) * (int64_t)T.nslots * G * T.P;
+    sf = s1;  // first-tier tails prepare the next block
+    T.partial += ((n + 1) & T.pmask) * (int64_t)T.nslots * G * T.P;
   } else {
     // later tier: the frame whose input completed in block n - lag
-    frame = (n - it.lag + 1) / T.r - 1;
+    sf = wrap_slot((n - it.lag + 1) / T.r - 1, T.K);
   }
-  mac_item<HT, G, NT>(T, it, frame, lds);
+  mac_item<HT, G, NT>(T, it, sf, lds);
 }
 
 // Graph replay's device block counter: set to v (add = 0), or advanced by v
 // (add = 1) by the graph's last node.
-__global__ void k_counter(int64_t* ctr, int64_t v, int32_t add) {
-  if (threadIdx.x == 0) *ctr = add ? *ctr + v : v;
+// ctr[0] is the block index, ctr[1] and ctr[2] its slots in delay lines of K
+// and fc_K blocks.
+__global__ void k_counter(int64_t* ctr, int64_t v, int32_t add, int32_t K, int32_t fc_K) {
+  if (threadIdx.x != 0) return;
+  const int64_t n = add ? ctr[0] + v : v;
+  ctr[0] = n;
+  ctr[1] = n % K;
+  ctr[2] = n % fc_K;
 }
 
 // Dense copy of partitions 0 and 1 of every pair for the heads:

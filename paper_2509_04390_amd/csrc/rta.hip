@@ -1132,6 +1132,8 @@ KArgs make_args(const rta_ctx* c, const float* in, float* out, int64_t n) {
   a.n_head = c->L;
   a.head_slots = c->head_slots;
   a.n = n;
+  a.slot = (int32_t)(n % c->tier[0].K);
+  a.fc_slot = 0;
   a.H01 = c->H01;
   a.head_count = c->head_count;
   a.heads_done = c->heads_done;
@@ -1179,6 +1181,7 @@ KArgs make_args(const rta_ctx* c, const float* in, float* out, int64_t n) {
     F.wait_polls = c->fc_wait_polls;
     F.wait_bias = c->fc_wait_bias;
     a.fc_on = 1;
+    a.fc_slot = (int32_t)(n % T.K);
     a.nf3 = T.r3;
     a.sub = c->d_c;
   }
@@ -1791,7 +1794,10 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
   const int fixed = head_lds(P0, 1, 1).total - 2 * P0;
   c->head_nq = std::max(1, std::min(c->Q, (6144 - fixed) / (2 * P0)));
   // With later tiers, also a transform pass's buffers (kTierLds).
-  c->lds = sizeof(float2) * std::max((size_t)head_lds(P0, 1, c->head_nq).total,
+  size_t head = (size_t)head_lds(P0, 1, c->head_nq).total;
+  if (!c->tier[0].r3 && (c->dtype == RTA_FP32 ? head_waves<float2>(P0) : head_waves<f16c_t>(P0)))
+    head = P0 == 64 ? head_wave_lds<1>() : P0 == 128 ? head_wave_lds<2>() : head_wave_lds<4>();
+  c->lds = sizeof(float2) * std::max(head,
                                      (size_t)kThreads * (c->tiled ? tile_outputs(c->G) * kTile : C * c->G));
   if (c->n_tiers > 1) c->lds = std::max(c->lds, sizeof(float2) * (size_t)kTierLds);
   if ((int64_t)c->lds + 64 > (int64_t)max_lds) return RTA_E_UNSUPPORTED;
@@ -2481,7 +2487,7 @@ int rta_graph_create(rta_ctx* c, const float* d_in, float* d_out, int32_t n_bloc
   if (n_blocks % c->n_phase != 0) return RTA_E_ARG;
   int st = device_status(c);
   if (st != RTA_OK) return st;
-  if (c->n_dev == nullptr && (st = dev_alloc(c, &c->n_dev, 1)) != RTA_OK) return st;
+  if (c->n_dev == nullptr && (st = dev_alloc(c, &c->n_dev, 3)) != RTA_OK) return st;
   hipStream_t cs = nullptr;
   HIP_TRY(c, hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
   hipGraph_t graph = nullptr;
@@ -2497,7 +2503,8 @@ int rta_graph_create(rta_ctx* c, const float* d_in, float* d_out, int32_t n_bloc
       e = hipGetLastError();
     }
     if (e == hipSuccess) {
-      hipLaunchKernelGGL(k_counter, dim3(1), dim3(64), 0, cs, c->n_dev, (int64_t)n_blocks, 1);
+      hipLaunchKernelGGL(k_counter, dim3(1), dim3(64), 0, cs, c->n_dev, (int64_t)n_blocks, 1,
+                         c->tier[0].K, c->fc != nullptr ? c->fc->tier[0].K : 1);
       e = hipGetLastError();
     }
     const hipError_t e2 = hipStreamEndCapture(cs, &graph);
@@ -2532,7 +2539,8 @@ int rta_graph_launch(rta_graph* g, void* stream) {
   if ((c->block - g->block0) % c->n_phase != 0) return RTA_E_STATE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (c->n_dev_value != c->block) {  // other launches moved the block index
-    hipLaunchKernelGGL(k_counter, dim3(1), dim3(64), 0, s, c->n_dev, c->block, 0);
+    hipLaunchKernelGGL(k_counter, dim3(1), dim3(64), 0, s, c->n_dev, c->block, 0, c->tier[0].K,
+                       c->fc != nullptr ? c->fc->tier[0].K : 1);
     HIP_TRY(c, hipGetLastError());
   }
   HIP_TRY(c, hipGraphLaunch(g->exec, s));
