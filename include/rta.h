@@ -348,9 +348,9 @@ int rta_graph_destroy(rta_graph* graph);
  *     partial sums meanwhile, then WAIT for c_{n-1} before packing their
  *     input, and after emitting y(n) they transform it into the feedback
  *     delay line.  That wait is on rta_process's latency path: it adds the
- *     feedback heads' reduction, their partitions 0 and 1 over every output
- *     and one inverse FFT (measured 14-24 us per block for 1 -> 32 outputs
- *     and 0.1-5 s paths).  The wait is bounded: if it gives up, the block
+ *     feedback heads' reduction, their partition 0 over every output and
+ *     one inverse FFT (measured about 4 us per block for 1 -> 32 outputs
+ *     and 1 s paths, B = 128).  The wait is bounded: if it gives up, the block
  *     fails with RTA_E_DEVICE (from rta_process, or from the next
  *     rta_process_device / rta_query / rta_reset call) and the context is
  *     poisoned.

@@ -123,16 +123,15 @@ struct DevTier {
 // Feedback convolution fused into the synthesis launch (Sec. III-A Eq. 3,
 // Sec. V).  Its inputs are the synthesis outputs y_l, its outputs the
 // estimates c_q that the next block subtracts from the microphones.
-struct FcArgs {
-  DevTier T;                 // its single tier (uniform partitions, P = B)
-  const Item* items;         // its multiply-accumulate items (terms p >= 2)
+struct FcArgs {              // (its single tier, uniform partitions, P = B: KArgs::tier[kFcTier])
+  const Item* items;         // its multiply-accumulate items (terms p >= 1)
   const Group* groups;       // its output groups (partial-slot layout)
   const void* H01;           // [Lf][Qf][2][P] its partitions 0 and 1
   float* hist;               // [Qf][hist_len] synthesis output history
   float* c;                  // [Lf][B] estimate c_{n-1}, written by its heads
   unsigned int* done;        // its heads done so far (monotonic, system scope)
   int64_t hist_mask;
-  int32_t n_items;           // its items per launch
+  int32_t n_items, n_list;   // its items per launch; lists (a power of two)
   int32_t tail0;             // tail index of its first item in the launch
   int32_t n_heads, head_slots;  // one head per feedback output; part of the grid
   int32_t Qf, Lf;            // its inputs (= synthesis outputs), outputs
@@ -141,8 +140,10 @@ struct FcArgs {
                              // test the give-up path: never reached)
 };
 
+constexpr int kFcTier = kMaxTiers;  // Item::tier of the fused feedback convolution's items
+
 struct KArgs {
-  DevTier tier[kMaxTiers];
+  DevTier tier[kMaxTiers + 1];  // (the last one: the fused feedback convolution's)
   const Item* items;         // [n_phase][max_items]
   const int32_t* phase_count;
   const Group* groups;
@@ -877,12 +878,15 @@ __device__ __forceinline__ void red_finish(const KArgs& A, const DevTier& T, con
 // then the workgroup proceeds.  The spin is bounded all the same; a wait that
 // gives up stores 1 in the host-visible error word, which fails the block on
 // the host.
-__device__ void fc_wait(const KArgs& A, int64_t n) {
+__device__ __forceinline__ void fc_wait(const KArgs& A, int64_t n) {
   if (threadIdx.x == 0) {
     const unsigned int target = (unsigned int)((n + 1) * A.fc.n_heads) + A.fc.wait_bias;
     bool ready = false;
     for (int it = 0; it < A.fc.wait_polls; ++it) {
-      if ((int)(__hip_atomic_load(A.fc.done, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_SYSTEM) - target) >= 0) {
+      // (relaxed: c is written and read by system-scope accesses, past the
+      // caches, so there is nothing to invalidate; an acquire here throws out
+      // the caches of the XCD that the tails stream through)
+      if ((int)(__hip_atomic_load(A.fc.done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) - target) >= 0) {
         ready = true;
         break;
       }
@@ -1157,8 +1161,8 @@ __device__ __forceinline__ void head_work(const KArgs& A, int64_t n, const Group
   // the feedback filters' B-tap partitions need, so it goes into slot n of
   // the feedback delay line as it is -- no inverse-then-forward transform
   if (A.fc_on && A.nf3) {
-    const FcArgs& F = A.fc;
-    float2* dst = F.T.X + ((int64_t)grp.l0 * F.T.K + wrap_slot(n, F.T.K)) * P;
+    const DevTier& F = A.tier[kFcTier];
+    float2* dst = F.X + ((int64_t)grp.l0 * F.K + wrap_slot(n, F.K)) * P;
     for (int k = tid; k < P; k += kThreads) dst[k] = Y[k];
   }
 
@@ -1265,7 +1269,7 @@ __device__ __forceinline__ void head_work(const KArgs& A, int64_t n, const Group
     float2* zf = fft_any<false>(Xa, Xb, P, logP, 0, tw);
     float2* xf = (zf == Xa) ? Xb : Xa;
     rfft_post(zf, xf, P, tw + P);
-    float2* dst = F.T.X + ((int64_t)l * F.T.K + wrap_slot(n, F.T.K)) * P;
+    float2* dst = A.tier[kFcTier].X + ((int64_t)l * A.tier[kFcTier].K + wrap_slot(n, A.tier[kFcTier].K)) * P;
     for (int k = tid; k < P; k += kThreads) dst[k] = xf[k];
   }
 }
@@ -1305,6 +1309,81 @@ __host__ __device__ constexpr bool head_waves(int P) {
 template <int V>
 __host__ __device__ constexpr int head_wave_lds() { return 4 * 64 * V + 3 * 2 * wave_pairs<V>() * 64; }
 
+// The four wavefronts' sums into wavefront 0's (in wavefront order); false in
+// the others, which are done.
+template <int V>
+__device__ __forceinline__ bool wave_sums(float2 (&ya)[wave_pairs<V>()], float2 (&yb)[wave_pairs<V>()], float2* red,
+                                          int w, int lane) {
+  constexpr int NP = wave_pairs<V>();
+  if (w > 0) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      red[(((w - 1) * NP + i) * 2) * 64 + lane] = ya[i];
+      red[(((w - 1) * NP + i) * 2 + 1) * 64 + lane] = yb[i];
+    }
+  }
+  __syncthreads();
+  if (w > 0) return false;
+#pragma unroll
+  for (int i = 0; i < NP; ++i)
+#pragma unroll
+    for (int v = 0; v < 3; ++v) {
+      ya[i] = cadd(ya[i], red[((v * NP + i) * 2) * 64 + lane]);
+      yb[i] = cadd(yb[i], red[((v * NP + i) * 2 + 1) * 64 + lane]);
+    }
+  return true;
+}
+// Packed bins in pairs -> the second half of the 2N samples (times 2N), pair
+// m - N/2 of them in zb[m - N/2].
+template <int V>
+__device__ __forceinline__ void wave_inverse(float2 (&ya)[wave_pairs<V>()], float2 (&yb)[wave_pairs<V>()],
+                                             float2 (&r)[V], const WaveTw<V>& tw,
+                                             const float2 (&tw2)[wave_pairs<V>()], float2* zb,
+                                             const int (&ka)[wave_pairs<V>()], const int (&kb)[wave_pairs<V>()],
+                                             bool first, bool act, int lane) {
+  constexpr int N = 64 * V, NP = wave_pairs<V>();
+  wave_lds_fence();
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    pair_pre(ya[i], yb[i], tw2[i], first && i == 0);
+    if (act) {
+      zb[ka[i]] = ya[i];
+      zb[kb[i]] = yb[i];
+    }
+  }
+  wave_lds_fence();
+#pragma unroll
+  for (int v = 0; v < V; ++v) r[v] = zb[64 * v + lane];
+  wave_fft<true, V>(r, tw, lane);
+  // samples m >= N / 2 are in the odd lanes; to natural order in LDS
+  wave_lds_fence();
+  if (lane & 1) wave_store<V>(r, zb - N / 2, lane);
+  wave_lds_fence();
+}
+// Requests the first SL partial slots of a wavefront's (V = 1: half-wave's)
+// share of a group's: `per` contiguous ones each.  Unconditional loads, clamped
+// within the group (at the twiddles where it has no slots).
+template <int V, int SL>
+__device__ __forceinline__ void share_slots(float2 (&ps)[SL][2 * wave_pairs<V>()], const float2* base,
+                                            const float2* dummy, int64_t stride, int nslot, int per, int w, int hw,
+                                            const int (&ka)[wave_pairs<V>()], const int (&kb)[wave_pairs<V>()]) {
+  const int from = min((V == 1 ? 2 * w : w) * per, max(nslot - 1, 0));
+  const char* src = reinterpret_cast<const char*>(nslot > 0 ? base + from * stride : dummy);
+  const uint32_t step = nslot > 0 ? (uint32_t)stride * 8u : 0u;
+  const int lim = max(nslot - 1 - from, 0);
+#pragma unroll
+  for (int j = 0; j < SL; ++j) {
+    const uint32_t at = (uint32_t)min(hw * per + j, lim) * step;
+#pragma unroll
+    for (int i = 0; i < wave_pairs<V>(); ++i) {
+      ps[j][2 * i] = load_at<false>(src, at + ka[i] * 8u, float2{});
+      ps[j][2 * i + 1] = load_at<false>(src, at + kb[i] * 8u, float2{});
+    }
+  }
+}
+// Waits until this wavefront's stores are acknowledged.
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 template <typename HT, int G, int V>
 __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int scn, const Group& grp, int l,
                                           float2* lds) {
@@ -1340,7 +1419,7 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
   };
   const int64_t hlen = A.hist_mask + 1;
   const int64_t hprev = ((n - 1) * B) & A.hist_mask, hcur = (n * B) & A.hist_mask;
-  auto window = [&](int q, In& in) {
+  auto window = [&](int q, In& in) __attribute__((always_inline)) {
     const float* ph = A.hist + q * hlen + hprev;
     const float* pi = A.in + (int64_t)q * B;
 #pragma unroll
@@ -1348,7 +1427,13 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
       const int i = 2 * (64 * v + lane);
       const bool cur = V == 1 ? lane >= 32 : 2 * v >= V;
       in.w[v] = load_pair(cur ? pi + (i - B) : ph + i);
-      if (v < V - VC) continue;
+    }
+    in.live = A.live != nullptr ? A.live[q] : 1;
+  };
+  auto estimate = [&](int q, In& in) __attribute__((always_inline)) {
+#pragma unroll
+    for (int v = V - VC; v < V; ++v) {
+      const int i = 2 * (64 * v + lane);
       in.s[v - (V - VC)] = f32x2u{0.f, 0.f};
       if (A.sub != nullptr) {  // microphone minus the previous block's feedback estimate
         const float* ps = A.sub + (int64_t)q * B + max(i - B, 0);
@@ -1359,9 +1444,8 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
                                          : load_pair(ps);
       }
     }
-    in.live = A.live != nullptr ? A.live[q] : 1;
   };
-  auto operands = [&](int q, In& in) {
+  auto operands = [&](int q, In& in) __attribute__((always_inline)) {
     const char* h = reinterpret_cast<const char*>(reinterpret_cast<const HT*>(A.H01) + (int64_t)(l * Q + q) * 2 * N);
     const char* x = reinterpret_cast<const char*>(T.X + ((int64_t)q * K + sp) * N);
 #pragma unroll
@@ -1377,7 +1461,8 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
   // (unconditional, at clamped inputs: a wavefront without one uses nothing)
   In in;
   const int q0 = min(w, Q - 1);
-  if (!A.fc_on) window(q0, in);
+  window(q0, in);
+  if (!A.fc_on) estimate(q0, in);
   const WaveTw<V> tw = wave_twiddles<V>(T.tw, lane);
   float2 tw2[NP];
 #pragma unroll
@@ -1392,26 +1477,10 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
   const int per = (grp.nslot + parts - 1) / parts;
   const int s0 = min(part * per, grp.nslot), s1 = min(s0 + per, grp.nslot);
   float2 ps[SL][2 * NP];
-  {
-    // (a valid address without slots; clamped within the share, which starts
-    // at the wavefront's first slot, `from`)
-    const int from = min((V == 1 ? 2 * w : w) * per, max(grp.nslot - 1, 0));
-    const char* src = reinterpret_cast<const char*>(grp.nslot > 0 ? base + from * stride : T.tw);
-    const uint32_t step = grp.nslot > 0 ? (uint32_t)stride * 8u : 0u;
-    const int lim = max(grp.nslot - 1 - from, 0);
-#pragma unroll
-    for (int j = 0; j < SL; ++j) {
-      const uint32_t at = (uint32_t)min(hw * per + j, lim) * step;
-#pragma unroll
-      for (int i = 0; i < NP; ++i) {
-        ps[j][2 * i] = load_at<false>(src, at + ka[i] * 8u, float2{});
-        ps[j][2 * i + 1] = load_at<false>(src, at + kb[i] * 8u, float2{});
-      }
-    }
-  }
+  share_slots<V, SL>(ps, base, T.tw, stride, grp.nslot, per, w, hw, ka, kb);
   // later tiers' ring samples of this block (wavefront 0 emits)
   constexpr int TMAX = 2;
-  const int mo = V == 1 ? pl : VO * lane;  // this lane's first output sample pair
+  const int mo = pl;  // this lane's output sample pairs: mo + 64 j (a store covers whole cache lines)
   const int64_t rpos = ((n * B) & A.ring_mask) + 2 * mo;
   float2 rv[TMAX][VO];
 #pragma unroll
@@ -1419,11 +1488,11 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
     if (t + 1 < A.n_tiers) {
       const float2* p = reinterpret_cast<const float2*>(A.tier[t + 1].oring + (int64_t)l * (A.ring_mask + 1) + rpos);
 #pragma unroll
-      for (int j = 0; j < VO; ++j) rv[t][j] = p[j];
+      for (int j = 0; j < VO; ++j) rv[t][j] = p[64 * j];
     }
   if (A.fc_on) {  // the block's window needs c_{n-1} of this launch's feedback heads
     fc_wait(A, n);
-    window(q0, in);
+    estimate(q0, in);
   }
 
   // ---- this wavefront's inputs: window -> spectrum -> ring, terms p = 0, 1
@@ -1434,6 +1503,7 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
     In next;
     if (V < 4 && q + 4 < Q) {  // (256 bins: too many registers)
       window(q + 4, next);
+      estimate(q + 4, next);
       operands(q + 4, next);
     }
     float2 r[V];
@@ -1468,7 +1538,7 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
         xn[kb[i]] = xb;
       }
       if (act) {
-        auto term = [&](one_t hr, float2 x, bool packed) {
+        auto term = [&](one_t hr, float2 x, bool packed) __attribute__((always_inline)) {
           const float2 h = HVec<HT>::cvt1(pin(hr));
           return packed ? make_float2(h.x * x.x, h.y * x.y) : cmul(h, x);
         };
@@ -1484,6 +1554,7 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
       in = next;
     } else if (q + 4 < Q) {
       window(q + 4, in);
+      estimate(q + 4, in);
       operands(q + 4, in);
     }
   }
@@ -1507,40 +1578,12 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
     ya[0] = cadd(ya[0], make_float2(lane_xor<32>(ya[0].x, lane), lane_xor<32>(ya[0].y, lane)));
     yb[0] = cadd(yb[0], make_float2(lane_xor<32>(yb[0].x, lane), lane_xor<32>(yb[0].y, lane)));
   }
-  if (w > 0) {
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-      red[(((w - 1) * NP + i) * 2) * 64 + lane] = ya[i];
-      red[(((w - 1) * NP + i) * 2 + 1) * 64 + lane] = yb[i];
-    }
-  }
-  __syncthreads();
-  if (w > 0) return;
+  if (!wave_sums<V>(ya, yb, red, w, lane)) return;
 
   // ---- inverse transform, the second half of the samples (overlap-save), the
   //      later tiers' contributions from their output rings
-#pragma unroll
-  for (int i = 0; i < NP; ++i) {
-#pragma unroll
-    for (int v = 0; v < 3; ++v) {
-      ya[i] = cadd(ya[i], red[((v * NP + i) * 2) * 64 + lane]);
-      yb[i] = cadd(yb[i], red[((v * NP + i) * 2 + 1) * 64 + lane]);
-    }
-    pair_pre(ya[i], yb[i], tw2[i], first && i == 0);
-    if (act) {
-      zb[ka[i]] = ya[i];
-      zb[kb[i]] = yb[i];
-    }
-  }
-  wave_lds_fence();
   float2 r[V];
-#pragma unroll
-  for (int v = 0; v < V; ++v) r[v] = zb[64 * v + lane];
-  wave_fft<true, V>(r, tw, lane);
-  // samples m >= N / 2 are in the odd lanes; to natural order in LDS
-  wave_lds_fence();
-  if (lane & 1) wave_store<V>(r, zb - N / 2, lane);
-  wave_lds_fence();
+  wave_inverse<V>(ya, yb, r, tw, tw2, zb, ka, kb, first, act, lane);
   const float scale = 1.0f / (float)(2 * N);
   float2 y[VO];
 #pragma unroll
@@ -1550,33 +1593,39 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
     for (int k = 0; k < TMAX; ++k)
       if (k + 1 < A.n_tiers) t = cadd(t, pin(rv[k][j]));
     for (int k = TMAX + 1; k < A.n_tiers; ++k)
-      t = cadd(t, *reinterpret_cast<const float2*>(A.tier[k].oring + (int64_t)l * (A.ring_mask + 1) + rpos + 2 * j));
-    const float2 v = zb[mo + j];
+      t = cadd(t, *reinterpret_cast<const float2*>(A.tier[k].oring + (int64_t)l * (A.ring_mask + 1) + rpos + 128 * j));
+    const float2 v = zb[mo + 64 * j];
     y[j] = make_float2(t.x + v.x * scale, t.y + v.y * scale);
   }
   if (act) {
 #pragma unroll
     for (int j = 0; j < VO; ++j) {
       const f32x2u o = {y[j].x, y[j].y};
-      *reinterpret_cast<f32x2u*>(A.out + (int64_t)l * B + 2 * (mo + j)) = o;
-      if (A.out2 != nullptr) *reinterpret_cast<f32x2u*>(A.out2 + (int64_t)l * B + 2 * (mo + j)) = o;
+      float* po = A.out + (int64_t)l * B + 2 * (mo + 64 * j);
+      if (A.done_flag != nullptr)  // the pinned output block (8-byte aligned): past the caches
+        __hip_atomic_store(reinterpret_cast<uint64_t*>(po), __builtin_bit_cast(uint64_t, y[j]), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+      else
+        *reinterpret_cast<f32x2u*>(po) = o;
+      if (A.out2 != nullptr) *reinterpret_cast<f32x2u*>(A.out2 + (int64_t)l * B + 2 * (mo + 64 * j)) = o;
       for (int t = 1; t < A.n_tiers; ++t)
-        *reinterpret_cast<float2*>(A.tier[t].oring + (int64_t)l * (A.ring_mask + 1) + rpos + 2 * j) =
+        *reinterpret_cast<float2*>(A.tier[t].oring + (int64_t)l * (A.ring_mask + 1) + rpos + 128 * j) =
             make_float2(0.f, 0.f);
     }
   }
   // this head's output is out: the tail workgroups of a waiting launch may
   // start streaming (relaxed: they read nothing the heads wrote)
   if (lane == 0) __hip_atomic_fetch_add(A.heads_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  // completion (rta_process only): every head makes its output visible
-  // system-wide, the last one raises the flag
+  // completion (rta_process only): each head counts itself once its output
+  // stores are acknowledged, the last one raises the flag (no release fence:
+  // it would write back the L2 first)
   if (A.done_flag != nullptr) {
-    __threadfence_system();
+    wait_stores();
     if (lane == 0) {
-      const unsigned int old = __hip_atomic_fetch_add(A.head_count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_SYSTEM);
+      const unsigned int old = __hip_atomic_fetch_add(A.head_count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       if (old == (unsigned int)A.n_head - 1u) {
         __hip_atomic_store(A.head_count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(A.done_flag, n + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(A.done_flag, n + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       }
     }
   }
@@ -1588,7 +1637,7 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
   const int64_t yprev = ((n - 1) * B) & F.hist_mask, ycur = (n * B) & F.hist_mask;
   if (act)
 #pragma unroll
-    for (int j = 0; j < VO; ++j) zb[mo + j] = y[j];
+    for (int j = 0; j < VO; ++j) zb[mo + 64 * j] = y[j];
   wave_lds_fence();
 #pragma unroll
   for (int v = 0; v < V; ++v) {
@@ -1598,12 +1647,12 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
   }
   if (act)
 #pragma unroll
-    for (int j = 0; j < VO; ++j) *reinterpret_cast<float2*>(hl + ycur + 2 * (mo + j)) = y[j];
+    for (int j = 0; j < VO; ++j) *reinterpret_cast<float2*>(hl + ycur + 2 * (mo + 64 * j)) = y[j];
   wave_fft<false, V>(r, tw, lane);
   wave_lds_fence();
   wave_store<V>(r, zb, lane);
   wave_lds_fence();
-  float2* dst = F.T.X + ((int64_t)l * F.T.K + scn) * N;
+  float2* dst = A.tier[kFcTier].X + ((int64_t)l * A.tier[kFcTier].K + scn) * N;
 #pragma unroll
   for (int i = 0; i < NP; ++i) {
     float2 xa = zb[ka[i]], xb = zb[kb[i]];
@@ -1616,14 +1665,14 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
 }
 
 // Feedback head of the fused launch n: output j of the feedback convolution
-// for block n - 1, c_j = IFFT(sum of its partial slots (its items of launch
-// n - 1) + sum_l F_{j,l,1} Y'_l(n-2) + F_{j,l,0} Y'_l(n-1)), the second half
-// of the 2B samples; then it counts itself done (system scope, after making
+// for block n - 1, c_j = IFFT(sum of its partial slots (p >= 1: its items of
+// earlier launches) + sum_l F_{j,l,0} Y'_l(n-1)), the second half of the 2B
+// samples; then it counts itself done (system scope, after making
 // c visible).  Y' are the synthesis heads' transforms of their outputs.
 template <typename HT, int G>
-__device__ __forceinline__ void fc_head_work(const KArgs& A, int64_t n, int j, float2* lds) {
+__device__ __forceinline__ void fc_head_work(const KArgs& A, int64_t n, int scn, int j, float2* lds) {
   const FcArgs& F = A.fc;
-  const DevTier& T = F.T;
+  const DevTier& T = A.tier[kFcTier];
   const int P = T.P, logP = T.logP, tid = threadIdx.x;
   const Group g0 = F.groups[j / G];
   const int gsel = j - g0.l0;
@@ -1637,21 +1686,16 @@ __device__ __forceinline__ void fc_head_work(const KArgs& A, int64_t n, int j, f
   const float2* tw = twr.n > 0 ? lds + 3 * P : stage_twiddles(T, lds + 3 * P);
   const HT* H01 = reinterpret_cast<const HT*>(F.H01);
   const int64_t stride = (int64_t)G * P;
-  const float2* base = T.partial + ((n - 1) & 1) * (int64_t)T.nslots * G * P +
+  const float2* base = T.partial + ((n - 1) & T.pmask) * (int64_t)T.nslots * G * P +
                        (int64_t)g0.slot0 * stride + (int64_t)gsel * P;
-  const int s1 = wrap_slot(n - 1, T.K), s2 = wrap_slot(n - 2, T.K);
+  const int s1 = scn == 0 ? T.K - 1 : scn - 1;
   auto term = [&](int k, int q0, int dq) {
     float2 acc = make_float2(0.f, 0.f);
 #pragma unroll 4
     for (int q = q0; q < F.Qf; q += dq) {
-      const HT* hr = H01 + ((int64_t)(j * F.Qf + q) * 2) * P + k;
-      const float2 h0 = HVec<HT>::load1(hr), h1 = HVec<HT>::load1(hr + P);
+      const float2 h0 = HVec<HT>::load1(H01 + ((int64_t)(j * F.Qf + q) * 2) * P + k);
       const float2 x0 = T.X[((int64_t)q * T.K + s1) * P + k];
-      const float2 x1 = T.X[((int64_t)q * T.K + s2) * P + k];
-      if (k == 0)
-        acc = cadd(acc, make_float2(h0.x * x0.x + h1.x * x1.x, h0.y * x0.y + h1.y * x1.y));
-      else
-        acc = cadd(acc, cadd(cmul(h0, x0), cmul(h1, x1)));
+      acc = cadd(acc, k == 0 ? make_float2(h0.x * x0.x, h0.y * x0.y) : cmul(h0, x0));
     }
     return acc;
   };
@@ -1690,6 +1734,119 @@ __device__ __forceinline__ void fc_head_work(const KArgs& A, int64_t n, int j, f
   __threadfence_system();
   __syncthreads();
   if (tid == 0) __hip_atomic_fetch_add(F.done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The same by wavefronts (see head_wave): wavefront w (V = 1: half-wave) adds
+// the p = 0 terms of the inputs w, w + 4, ... and its quarter of the partial
+// slots, wavefront 0 transforms back.  This head is on the latency path of
+// every output (they wait for c): 1 -> 32 with 1 s paths it ends after 5.8 us
+// where fc_head_work, with the p = 1 terms as well, took 17.9 (block: 22.0 ->
+// 13.4 us, 39.0 before the feedback rows were tiled in time).
+template <int V>
+__host__ __device__ constexpr int fc_share() { return V == 4 ? 6 : 12; }  // slots per share
+template <typename HT, int G, int V>
+__device__ __forceinline__ void fc_head_wave(const KArgs& A, int64_t n, int scn, int j, float2* lds) {
+  constexpr int N = 64 * V, NP = wave_pairs<V>(), U = V == 4 ? 2 : 4;
+  typedef typename HVec<HT>::one_t one_t;
+  const FcArgs& F = A.fc;
+  const DevTier& T = A.tier[kFcTier];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int pl = V == 1 ? (lane & 31) : lane, hw = V == 1 ? lane >> 5 : 0;
+  const bool first = pl == 0;
+  constexpr int parts = V == 1 ? 8 : 4;
+  const int part = V == 1 ? 2 * w + hw : w;
+  const int K = T.K, sp = scn == 0 ? K - 1 : scn - 1;
+  float2* zb = lds + w * N;
+  float2* red = lds + 4 * N;
+  const Group g0 = F.groups[j / G];
+  const WaveTw<V> tw = wave_twiddles<V>(T.tw, lane);
+  int ka[NP], kb[NP];
+  float2 tw2[NP], ya[NP], yb[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    ka[i] = 64 * i + pl;
+    kb[i] = pair_hi<V>(ka[i]);
+    tw2[i] = T.tw[N + ka[i]];
+    ya[i] = yb[i] = make_float2(0.f, 0.f);
+  }
+  // this share of the partial slots: requested first, added up last
+  const int64_t stride = (int64_t)G * N;
+  const float2* base = T.partial + ((n - 1) & T.pmask) * (int64_t)T.nslots * stride + (int64_t)g0.slot0 * stride +
+                       (int64_t)(j - g0.l0) * N;
+  const int per = (g0.nslot + parts - 1) / parts;
+  const int s0 = min(part * per, g0.nslot), s1 = min(s0 + per, g0.nslot);
+  constexpr int SL = fc_share<V>();
+  float2 ps[SL][2 * NP];
+  share_slots<V, SL>(ps, base, T.tw, stride, g0.nslot, per, w, hw, ka, kb);
+  // p = 0, U inputs in flight
+  const char* H = reinterpret_cast<const char*>(reinterpret_cast<const HT*>(F.H01) + (int64_t)j * F.Qf * 2 * N);
+  const char* X = reinterpret_cast<const char*>(T.X + (int64_t)sp * N);
+  const uint32_t hstep = 2 * N * (uint32_t)sizeof(HT);
+  const int64_t xstep = (int64_t)K * N * sizeof(float2);
+  for (int q = part; q < F.Qf; q += parts * U) {
+    one_t h[U][2 * NP];
+    float2 x[U][2 * NP];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int qu = min(q + parts * u, F.Qf - 1);
+      const char* xq = X + qu * xstep;
+#pragma unroll
+      for (int i = 0; i < 2 * NP; ++i) {
+        const uint32_t k = (i & 1) ? kb[i / 2] : ka[i / 2];
+        h[u][i] = load_at<false>(H, (uint32_t)qu * hstep + k * (uint32_t)sizeof(HT), one_t{});
+        x[u][i] = load_at<false>(xq, k * 8u, float2{});
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (q + parts * u < F.Qf) {
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+          const float2 a = HVec<HT>::cvt1(h[u][2 * i]), b = HVec<HT>::cvt1(h[u][2 * i + 1]);
+          ya[i] = cadd(ya[i], first && i == 0 ? make_float2(a.x * x[u][2 * i].x, a.y * x[u][2 * i].y)
+                                              : cmul(a, x[u][2 * i]));
+          yb[i] = cadd(yb[i], cmul(b, x[u][2 * i + 1]));
+        }
+      }
+  }
+#pragma unroll
+  for (int k = 0; k < SL; ++k)
+    if (s0 + k < s1) {
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        ya[i] = cadd(ya[i], ps[k][2 * i]);
+        yb[i] = cadd(yb[i], ps[k][2 * i + 1]);
+      }
+    }
+#pragma unroll 4
+  for (int s = s0 + SL; s < s1; ++s)
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      ya[i] = cadd(ya[i], base[s * stride + ka[i]]);
+      yb[i] = cadd(yb[i], base[s * stride + kb[i]]);
+    }
+  if constexpr (V == 1) {
+    ya[0] = cadd(ya[0], make_float2(lane_xor<32>(ya[0].x, lane), lane_xor<32>(ya[0].y, lane)));
+    yb[0] = cadd(yb[0], make_float2(lane_xor<32>(yb[0].x, lane), lane_xor<32>(yb[0].y, lane)));
+  }
+  if (!wave_sums<V>(ya, yb, red, w, lane)) return;
+  float2 r[V];
+  wave_inverse<V>(ya, yb, r, tw, tw2, zb, ka, kb, first, V > 1 || lane < 32, lane);
+  const float scale = 1.0f / (float)(2 * N);
+  float* cj = F.c + (int64_t)j * A.B;
+  if (lane < 32 * V)
+#pragma unroll
+    for (int i = 0; i < (V == 4 ? 2 : 1); ++i) {
+      const int m = lane + 64 * i;
+      const float2 v = zb[m];
+      __hip_atomic_store(cj + 2 * m, v.x * scale, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store(cj + 2 * m + 1, v.y * scale, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+  // c went past the caches: once the stores are acknowledged it is visible
+  // everywhere (a release fence would write back the whole L2 as well)
+  wait_stores();
+  if (lane == 0) __hip_atomic_fetch_add(F.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---------------------------------------------------------------------------
@@ -1941,8 +2098,13 @@ __device__ __forceinline__ void tier_pass(const KArgs& A, int64_t n, const Item&
 }
 
 template <typename HT, int G, bool NT>
-__global__ __launch_bounds__(kThreads, sizeof(HT) == 4 ? 4 : 3) void k_block(const KArgs A) {
+__global__ __launch_bounds__(kThreads, sizeof(HT) == 4 ? 4 : 3) void k_block(const KArgs args) {
   extern __shared__ float2 lds[];
+  // the arguments where the launch put them (their only parameter starts the
+  // segment): a parameter that some use keeps from being promoted would be
+  // copied to scratch as a whole
+  (void)args;
+  const KArgs& A = *(const KArgs*)__builtin_amdgcn_kernarg_segment_ptr();
   // the block index: from the launch, or (graph replay) the device counter
   // plus this launch's place in the graph
   // Kernel-argument fields are read where first used, after the branch
@@ -1965,12 +2127,27 @@ __global__ __launch_bounds__(kThreads, sizeof(HT) == 4 ? 4 : 3) void k_block(con
     sn += (int)A.n_base[1];
     if (sn >= A.tier[0].K) sn -= A.tier[0].K;
     scn += (int)A.n_base[2];
-    if (A.fc_on && scn >= A.fc.T.K) scn -= A.fc.T.K;
+    if (A.fc_on && scn >= A.tier[kFcTier].K) scn -= A.tier[kFcTier].K;
   }
   int b = blockIdx.x;
   if (A.fc_on) {  // grid: feedback heads | heads | transforms | tails | feedback tails
     if (b < A.fc.head_slots) {
-      if (b < A.fc.n_heads) fc_head_work<HT, G>(A, n, b, lds);
+      if (b >= A.fc.n_heads) return;
+      const int P = A.tier[kFcTier].r3 ? 0 : A.tier[kFcTier].P;
+      if (P == 128) {
+        fc_head_wave<HT, G, 2>(A, n, scn, b, lds);
+        return;
+      }
+      if (P == 64) {
+        fc_head_wave<HT, G, 1>(A, n, scn, b, lds);
+        return;
+      }
+      if constexpr (head_waves<HT>(256))
+        if (P == 256) {
+          fc_head_wave<HT, G, 4>(A, n, scn, b, lds);
+          return;
+        }
+      fc_head_work<HT, G>(A, n, scn, b, lds);
       return;
     }
     b -= A.fc.head_slots;
@@ -2025,37 +2202,38 @@ __global__ __launch_bounds__(kThreads, sizeof(HT) == 4 ? 4 : 3) void k_block(con
     }
     __syncthreads();
   }
-  if (A.fc_on && i >= A.fc.tail0) {  // feedback terms p >= 2 for c_n
-    const int j = i - A.fc.tail0;
-    if (j >= A.fc.n_items) return;
-    const Item it = A.fc.items[j];
-    if (it.kind == K_NOP) return;
-    DevTier T = A.fc.T;
-    T.partial += (n & 1) * (int64_t)T.nslots * G * T.P;
-    mac_item<HT, G, NT>(T, it, scn, lds);
-    return;
-  }
   // (the tail part of the grid is at most max_items long, and a phase's
   // list is padded to max_items with K_NOP).  The first tier's fields are
   // read before the item arrives: most items are first-tier ones.
   DevTier T = A.tier[0];
   asm volatile("" ::"s"(T.H), "s"(T.X), "s"(T.partial), "s"(T.K), "s"(T.P), "s"(T.nslots));
-  const Item it = A.items[(int64_t)phase * A.max_items + i];
+  const Item* list = A.items + (int64_t)phase * A.max_items + i;
+  if (A.fc_on && i >= A.fc.tail0) {  // the feedback convolution's items
+    const int k = i - A.fc.tail0;
+    if (k >= A.fc.n_items) return;
+    list = A.fc.items + (int64_t)((int)n & (A.fc.n_list - 1)) * A.fc.n_items + k;
+  }
+  const Item it = *list;
   if (it.kind == K_NOP) return;
-  const int s1 = sn + 1 == T.K ? 0 : sn + 1;  // block n + 1's slot
+  if (it.tier != 0) T = A.tier[it.tier];
+  // the synthesis tails prepare block n + 1, the feedback's the terms p >= 1
+  // of c_n (delay-line slots up to n - 1)
+  const bool fc = it.tier == kFcTier;
+  const int64_t b1 = fc ? n : n + 1;
+  const int s1 = fc ? scn : sn + 1 == A.tier[0].K ? 0 : sn + 1;  // its delay-line slot
+  const int Q = fc ? A.fc.Qf : A.Q;
   if (it.kind == K_TILE) {
-    mac_tile<HT, G, NT>(T, it, n + 1, s1, A.Q, lds);
+    mac_tile<HT, G, NT>(T, it, b1, s1, Q, lds);
     return;
   }
   if (it.kind == K_NEAR) {
-    mac_near<HT, G, NT>(T, it, n + 1, s1, A.Q, lds);
+    mac_near<HT, G, NT>(T, it, b1, s1, Q, lds);
     return;
   }
-  if (it.tier != 0) T = A.tier[it.tier];
   int sf;
-  if (it.tier == 0) {
-    sf = s1;  // first-tier tails prepare the next block
-    T.partial += ((n + 1) & T.pmask) * (int64_t)T.nslots * G * T.P;
+  if (it.tier == 0 || fc) {
+    sf = s1;
+    T.partial += (b1 & T.pmask) * (int64_t)T.nslots * G * T.P;
   } else {
     // later tier: the frame whose input completed in block n - lag
     sf = wrap_slot((n - it.lag + 1) / T.r - 1, T.K);

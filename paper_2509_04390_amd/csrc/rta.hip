@@ -128,7 +128,6 @@ struct rta_ctx {
   TierHost tier[kMaxTiers];
   int G = 1, rows_per_item = 0, n_phase = 1, max_items = 0, n_items = 0;
   int n_list = 1;              // work lists per phase period: n_phase, or kTile when tiled
-  bool tile_ok = true;         // far partitions may be tiled in time (see build_plan)
   bool tiled = false;
   int tail_items = 512, tier_rows = 16;
   int max_group_slots = 0;     // first tier: the most partial slots of one output group
@@ -179,6 +178,8 @@ struct rta_ctx {
   int fc_wait_polls = 1 << 24;  // bound of the synthesis heads' wait for it
   uint32_t fc_wait_bias = 0;    // nonzero only to test the give-up path
   int min_ring = 1;             // first tier's delay line has at least this many slots
+  int tail_p0 = 2;              // first partition of the tails' items (1: a feedback convolution
+                                // fused into a launch, see k_block)
 
   std::vector<int32_t> block_count_host;  // k_block items per phase (active list)
   const int32_t* live = nullptr;  // serving: [Q] live mask of the active list
@@ -487,7 +488,9 @@ void add_to_bucket(std::vector<Bucket>& buckets, const Item& it, int nl, int uni
 //   - Runs of at least kTile rows where the filters have them (a run's first
 //     row costs kTile spectrum loads, each later one one).
 //   - At least 16 bins where the row has them: 128 bytes of FP32 spectra per
-//     load.
+//     load; fewer (and more runs) where a launch would have less than 256 items
+//     of several steps (1 s feedback paths of 32 outputs into one microphone:
+//     16 items of 18 us each on the launch's critical path).
 //   - Every (output group, span inputs, chunk) owns a partial slot.  A chunk
 //     has 8 rows per run, longer ones until a group's slots are within what a
 //     head adds up from registers (HeadRed; within 32 where it adds them up in
@@ -527,7 +530,12 @@ TilePlan tile_plan(const rta_ctx* c) {
   const int far = T.K - kTile - 1;
   const int ng = T.P <= kThreads ? kThreads / T.P : 0;
   const bool from_regs = ng > 0 && is_pow2(T.P) && (c->Q + ng - 1) / ng <= HeadRed<float2>::kInputs;
-  const int64_t cap = from_regs ? (int64_t)HeadRed<float2>::kSlots * ng : 32;
+  int64_t cap = from_regs ? (int64_t)HeadRed<float2>::kSlots * ng : 32;
+  if (c->tail_p0 == 1 && !T.r3) {  // what fc_head_wave requests up front
+    if (T.P == 64) cap = 8 * fc_share<1>();
+    if (T.P == 128) cap = 4 * fc_share<2>();
+    if (T.P == 256) cap = 4 * fc_share<4>();
+  }
   int runs = 1;
   while (runs < 16 && far >= 2 * runs * kTile) runs *= 2;
   t.W = std::min(kThreads / runs, T.P & -T.P);
@@ -545,6 +553,13 @@ TilePlan tile_plan(const rta_ctx* c) {
     t.slots = chunks + (int64_t)ngroups * near_slots(c);
     const bool fits = most <= cap && chunks * per_group * (T.P / t.W) <= (int64_t)kTile * c->tail_items * 3 / 2;
     if (fits || (t.rows >= far && t.span >= c->Q)) {
+      // few, long items: narrower ones with more and shorter runs
+      auto steps = [&] { return (std::min(t.rows, far) + runs * kTile - 1) / (runs * kTile) * t.span; };
+      const int wmin = c->dtype == RTA_FP32 ? 4 : 8;  // 32 bytes per load
+      while (t.W > wmin && steps() > 1 && chunks * per_group * (T.P / t.W) < (int64_t)kTile * 256) {
+        t.W /= 2;
+        runs *= 2;
+      }
       while (t.unit < 8 && chunks / (2 * t.unit) >= 2 * kTile * kXcds) t.unit *= 2;
       return t;
     }
@@ -563,8 +578,13 @@ void tile_items(rta_ctx* c, const TilePlan& t, Plan& plan, std::vector<Item>& ne
   const int G = c->G, Q = c->Q;
   const bool fixed = c->serve != nullptr;
   const int Wmax = std::min(T.r3 ? T.P / 3 : T.P, kThreads * vec_bins(c->dtype));
-  if (c->bin_slices == 0) c->bin_slices = 1;
-  const int Wn = std::max(vec_bins(c->dtype), Wmax / c->bin_slices);
+  if (c->bin_slices == 0 || c->min_ring > 1) c->bin_slices = 1;  // (a feedback convolution's few near rows)
+  // near items: bins few enough that one round of row loads covers their
+  // inputs (each round waits for the pair tables, then for the rows)
+  const int near_in = std::min(Q, kNearInputs);
+  int Wn = Wmax / c->bin_slices;
+  while (Wn > 4 * vec_bins(c->dtype) && near_in * kTile * Wn > kThreads * vec_bins(c->dtype) * kUnroll) Wn /= 2;
+  Wn = std::max(vec_bins(c->dtype), Wn);
   c->rows_per_item = t.rows;
   std::map<std::tuple<int, int, int>, std::vector<Item>> units;  // by (chunk, first input, groups)
   int slot = 0;
@@ -583,7 +603,7 @@ void tile_items(rta_ctx* c, const TilePlan& t, Plan& plan, std::vector<Item>& ne
       it.group = g;
       it.q = q;
       it.lag = std::min(kNearInputs, Q - q);
-      it.p0 = 2;
+      it.p0 = c->tail_p0;
       it.p1 = std::min(longest(q, it.lag), kTile + 1);
       it.w = Wn;
       it.slot = slot;
@@ -692,7 +712,8 @@ int build_plan(rta_ctx* c, Plan& plan) {
     }
   };
 
-  // ---- first tier: partitions >= 2, every phase
+  // ---- first tier: partitions >= tail_p0 (2), every phase
+  const int pb = c->tail_p0;
   std::vector<Item> tier0;
   std::vector<std::vector<Item>> far(n_list);  // K_TILE items, by the launch that runs them
   const TilePlan tile = tile_plan(c);
@@ -709,10 +730,10 @@ int build_plan(rta_ctx* c, Plan& plan) {
     int W = std::max(C, Wmax / std::max(1, c->bin_slices)), nslice = T.P / W;
     int64_t total_rows = 0;
     for (const Group& gr : plan.groups)
-      for (int q = 0; q < c->Q; ++q) total_rows += std::max(0, group_rows(T, gr, q) - 2);
+      for (int q = 0; q < c->Q; ++q) total_rows += std::max(0, group_rows(T, gr, q) - pb);
     // serving: every (group, input) owns the slots of a max_taps filter, so
     // a slot's meaning does not depend on which sources are present
-    const int cap_rows = fixed ? std::max(0, T.kcap - 2) : 0;
+    const int cap_rows = fixed ? std::max(0, T.kcap - pb) : 0;
     if (fixed) total_rows = (int64_t)ngroups * c->Q * cap_rows;
     int R = c->rows_per_item;
     if (R <= 0) {
@@ -735,7 +756,7 @@ int build_plan(rta_ctx* c, Plan& plan) {
           int64_t tot = 0, m = 0;
           for (const Group& gr : plan.groups) {
             int64_t ns = 0;
-            for (int q = 0; q < c->Q; ++q) ns += (std::max(0, group_rows(T, gr, q) - 2) + r - 1) / r;
+            for (int q = 0; q < c->Q; ++q) ns += (std::max(0, group_rows(T, gr, q) - pb) + r - 1) / r;
             tot += ns;
             m = std::max(m, ns);
           }
@@ -762,8 +783,8 @@ int build_plan(rta_ctx* c, Plan& plan) {
       // 60 ranges 27.5 us, 64 ranges 24.4 us)
       int kmax = 0;
       for (const Group& gr : plan.groups)
-        for (int q = 0; q < c->Q; ++q) kmax = std::max(kmax, group_rows(T, gr, q) - 2);
-      if (fixed) kmax = std::max(0, T.kcap - 2);
+        for (int q = 0; q < c->Q; ++q) kmax = std::max(kmax, group_rows(T, gr, q) - pb);
+      if (fixed) kmax = std::max(0, T.kcap - pb);
       int step = kXcds;
       for (int qq = c->Q; qq % 2 == 0 && step > 1; qq /= 2) step /= 2;  // 8 / gcd(Q, 8)
       if ((kmax + R - 1) / R >= kXcds)  // the largest R' <= R giving a multiple of step
@@ -787,12 +808,12 @@ int build_plan(rta_ctx* c, Plan& plan) {
       }
       for (int q = 0; q < c->Q; ++q) {
         const int kg = group_rows(T, gr, q);
-        if (kg <= 2) continue;  // partitions 0 and 1 are done by the heads
-        const int rows = kg - 2;
+        if (kg <= pb) continue;  // the partitions before are done by the heads
+        const int rows = kg - pb;
         const int nch = (rows + R - 1) / R;
         for (int ch = 0; ch < nch; ++ch) {
-          const int p0 = fixed ? 2 + ch * R : 2 + (int)((int64_t)ch * rows / nch);
-          const int p1 = fixed ? std::min(kg, 2 + (ch + 1) * R) : 2 + (int)((int64_t)(ch + 1) * rows / nch);
+          const int p0 = fixed ? pb + ch * R : pb + (int)((int64_t)ch * rows / nch);
+          const int p1 = fixed ? std::min(kg, pb + (ch + 1) * R) : pb + (int)((int64_t)(ch + 1) * rows / nch);
           const int it_slot = fixed ? gr.slot0 + q * nch_cap + ch : slot;
           for (int sl = 0; sl < nslice; ++sl) {
             Item it{};
@@ -1012,7 +1033,7 @@ int build_plan(rta_ctx* c, Plan& plan) {
         if (T.K < 2 * kTile + 2 || it.p1 < it.p0 || it.p1 > T.K || T.pair_row == nullptr) return RTA_E_STATE;
         if (W < 1 || !is_pow2(W) || T.P % W != 0 || it.k0 < 0 || it.k0 % W != 0 || it.k0 + W > T.P) return RTA_E_STATE;
         if (it.kind == K_NEAR) {
-          if (W < C || W > kThreads * C || it.p0 < 1 || it.p1 > it.p0 + kTile || it.nl != gr.nl) return RTA_E_STATE;
+          if (W < C || W > kThreads * C || it.p0 < c->tail_p0 || it.p1 > it.p0 + kTile || it.nl != gr.nl) return RTA_E_STATE;
         } else {
           if (W > kThreads || it.p0 < kTile + 1) return RTA_E_STATE;
           if (it.nl < 1 || it.nl > tile_outputs(G) || it.acc < 0 || it.acc + it.nl > gr.nl) return RTA_E_STATE;
@@ -1037,7 +1058,7 @@ int build_plan(rta_ctx* c, Plan& plan) {
       const TierHost& T = c->tier[it.tier];
       const int W = it.w;
       if (it.q < 0 || it.q >= c->Q) return RTA_E_STATE;
-      if (it.p0 < (it.tier == 0 ? 2 : 0) || it.p1 < it.p0 || it.p1 > T.K) return RTA_E_STATE;
+      if (it.p0 < (it.tier == 0 ? c->tail_p0 : 0) || it.p1 < it.p0 || it.p1 > T.K) return RTA_E_STATE;
       if (W < C || W > kThreads * C || (W & (W - 1)) != 0 || T.P % W != 0) return RTA_E_STATE;
       if (it.k0 < 0 || it.k0 % W != 0 || it.k0 + W > T.P) return RTA_E_STATE;
       if (it.nl != plan.groups[it.group].nl) return RTA_E_STATE;
@@ -1150,21 +1171,22 @@ KArgs make_args(const rta_ctx* c, const float* in, float* out, int64_t n) {
     const rta_ctx* f = c->fc;
     const TierHost& T = f->tier[0];
     FcArgs& F = a.fc;
-    F.T.H = T.H;
-    F.T.pair_row = T.pair_row;
-    F.T.pair_K = T.pair_K;
-    F.T.X = T.X;
-    F.T.partial = T.partial;
-    F.T.tw = T.tw;
-    F.T.oring = nullptr;
-    F.T.offset = 0;
-    F.T.P = T.P;
-    F.T.logP = T.logP;
-    F.T.r3 = T.r3;
-    F.T.K = T.K;
-    F.T.nslots = std::max(1, T.nslots);
-    F.T.pmask = partial_blocks(f) - 1;
-    F.T.r = 1;
+    DevTier& D = a.tier[kFcTier];
+    D.H = T.H;
+    D.pair_row = T.pair_row;
+    D.pair_K = T.pair_K;
+    D.X = T.X;
+    D.partial = T.partial;
+    D.tw = T.tw;
+    D.oring = nullptr;
+    D.offset = 0;
+    D.P = T.P;
+    D.logP = T.logP;
+    D.r3 = T.r3;
+    D.K = T.K;
+    D.nslots = std::max(1, T.nslots);
+    D.pmask = partial_blocks(f) - 1;
+    D.r = 1;
     F.items = f->items;
     F.groups = f->groups;
     F.H01 = f->H01;
@@ -1172,7 +1194,8 @@ KArgs make_args(const rta_ctx* c, const float* in, float* out, int64_t n) {
     F.c = c->d_c;
     F.done = c->fc_done;
     F.hist_mask = f->hist_len - 1;
-    F.n_items = f->block_count_host.empty() ? 0 : f->block_count_host[0];
+    F.n_items = f->max_items;
+    F.n_list = f->n_list;
     F.tail0 = c->grid_items;
     F.n_heads = f->L;
     F.head_slots = (f->L + kXcds - 1) / kXcds * kXcds;
@@ -1684,7 +1707,7 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
   // two tiles (shorter ones have as many near rows as far ones) and the
   // partial sums of 2 kTile blocks take no more memory than the spectra (many
   // inputs with few partitions each would) or 64 MB
-  c->tiled = c->tile_ok && c->n_tiers == 1 && c->rows_per_item == 0 && c->tier[0].K >= 2 * kTile + 2 &&
+  c->tiled = c->n_tiers == 1 && c->rows_per_item == 0 && c->tier[0].K >= 2 * kTile + 2 &&
              (int64_t)c->tier[0].K * c->tier[0].P <= (int64_t(1) << 28);  // 32-bit byte offsets
   if (c->tiled && (double)tile_plan(c).slots * 2 * kTile * c->G * c->tier[0].P * 8.0 >
                       std::max((double)(64 << 20), (double)c->spectra_bytes))
@@ -1730,6 +1753,8 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
     cnt_b[ph] = (int32_t)plan.block[ph].size();
     cnt_t[ph] = (int32_t)plan.tier[ph].size();
   }
+  if (c->tail_p0 == 1)  // runs in another context's launch, as its tier kFcTier
+    for (Item& it : all_b) it.tier = kFcTier;
   c->tier_count_host = cnt_t;
   c->block_count_host = cnt_b;
   if ((st = dev_alloc(c, &c->items, all_b.size())) != RTA_OK) return st;
@@ -2198,11 +2223,11 @@ int create_ctx(rta_ctx** out, double fs, int32_t block, const std::vector<int>& 
                const std::vector<int>& count, int32_t n_in, int32_t n_out,
                const float* const* filters, const int64_t* lengths, int32_t spectra,
                uint32_t flags, const rta_tuning* tuning, const rta_serve_config* cfg,
-               int min_ring = 1) {
+               int min_ring = 1, int tail_p0 = 2) {
   rta_ctx* c = new (std::nothrow) rta_ctx();
   if (c == nullptr) return RTA_E_NOMEM;
   c->min_ring = min_ring;
-  c->tile_ok = min_ring == 1;
+  c->tail_p0 = tail_p0;
   c->fs = fs;
   c->B = block;
   c->Q = n_in;
@@ -2649,19 +2674,30 @@ int rta_set_feedback(rta_ctx* c, const float* const* fb, const int64_t* lengths,
   }
   c->fc_fused = false;
   if (fb != nullptr) {
-    // same outputs per group as this context, so its items can run in this
-    // context's launch; at least 3 delay-line slots (this launch writes slot
-    // n while its heads read n-1 and n-2)
+    // It runs inside this context's launch (fused) when both store the same
+    // spectrum type and the launch's LDS fits; its items then prepare the terms
+    // p >= 1 (its newest spectrum is one block old when they run).  Same
+    // outputs per group as this context either way; at least 3 delay-line
+    // slots (this launch writes slot n while its heads read n-1 and its items
+    // n-1 and older).
+    const int P = c->tier[0].P, C = vec_bins(c->dtype);
+    const size_t fc_head = sizeof(float2) * (size_t)std::max(3 * P + tw_lds_len(P) + red_scratch(P), 4 * P + 6 * 128);
+    const size_t fc_tail = sizeof(float2) * (size_t)kThreads * std::max(tile_outputs(c->G) * kTile, C * c->G);
+    c->lds_fused = std::max(c->lds, std::max(fc_head, fc_tail));
+    int max_lds = 0;
+    HIP_TRY(c, hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device));
+    const bool fused = spectra == c->dtype && (int64_t)c->lds_fused + 64 <= (int64_t)max_lds;
     rta_tuning tu{};
     tu.outputs_per_group = c->G;
-    // its one head per output reduces all of that output's partial slots on
+    // its one head per output adds up all of that output's partial slots on
     // the synthesis heads' critical path: 512 items in 8 bin slices keep them
-    // to about 64 while its items stay as small as the synthesis tails'
+    // to about 64 while its items stay as small as the synthesis tails' (not
+    // tiled in time; tiled, the plan keeps the slots down by itself)
     tu.tail_items = 512;
     tu.bin_slices = 8;
     rta_ctx* fc = nullptr;
     int st = create_ctx(&fc, c->fs, c->B, size, count, c->L, c->Q, ft.data(), lt.data(), spectra,
-                        c->flags & RTA_FLAG_NF3, &tu, nullptr, 3);
+                        c->flags & RTA_FLAG_NF3, &tu, nullptr, 3, fused ? 1 : 2);
     if (st != RTA_OK) return st;
     c->fc = fc;
     if (c->d_y == nullptr) {
@@ -2669,15 +2705,10 @@ int rta_set_feedback(rta_ctx* c, const float* const* fb, const int64_t* lengths,
       if ((st = dev_alloc(c, &c->d_c, (size_t)c->Q * c->B)) != RTA_OK) return st;
       if ((st = dev_alloc(c, &c->fc_done, 1)) != RTA_OK) return st;
     }
-    // fused when both store the same spectrum type and the launch's LDS fits
-    const int P = c->tier[0].P, C = vec_bins(c->dtype);
-    const size_t fc_head = sizeof(float2) * (size_t)(3 * P + tw_lds_len(P) + red_scratch(P));
-    const size_t fc_tail = sizeof(float2) * (size_t)kThreads * C * c->G;
-    c->lds_fused = std::max(c->lds, std::max(fc_head, fc_tail));
-    int max_lds = 0;
-    HIP_TRY(c, hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device));
-    c->fc_fused = fc->dtype == c->dtype && fc->G == c->G && fc->n_tiers == 1 && fc->tier[0].K >= 3 &&
-                  fc->tier[0].P == P && (int64_t)c->lds_fused + 64 <= (int64_t)max_lds;
+    c->fc_fused = fused;
+    if (fused && (fc->dtype != c->dtype || fc->G != c->G || fc->n_tiers != 1 || fc->tier[0].K < 3 ||
+                  fc->tier[0].P != P || !is_pow2(fc->n_list)))
+      return RTA_E_STATE;
     if (c->fc_fused && c->lds_fused > 65536)
       HIP_TRY(c, hipFuncSetAttribute(reinterpret_cast<const void*>(block_kernel(c->dtype, c->G, c->nt)),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)c->lds_fused));

@@ -85,3 +85,24 @@ def test_a_bad_block_is_heard_for_its_partitions_only(rta, bad):
     # block at + K's window still begins with the bad block; partition K - 1
     # pairs block at + K with the spectrum of [x(at), x(at + 1)]
     assert np.array_equal(y[:, (at + K + 1) * B:], yb[:, (at + K + 1) * B:])
+
+
+@pytest.mark.parametrize("B,rows", [(32, 18), (64, 17), (64, 18), (64, 41), (128, 19), (128, 130), (256, 30), (512, 20)])
+@pytest.mark.parametrize("Q,L,spectra,limit", [(1, 6, "fp32", FP32_DB), (3, 2, "fp32", FP32_DB), (1, 3, "fp16", FP16_DB)])
+def test_tiled_feedback_paths(rta, B, rows, Q, L, spectra, limit):
+    """Feedback paths around and beyond the first tiled length, of unequal
+    lengths, in a loop of small gain (rooms of about 30 per path)."""
+    filt = make_filters(760 + B, [[3 * B + 7 * l + q for l in range(L)] for q in range(Q)])
+    fb = make_filters(761 + rows, [[B * rows - 11 * l - q for l in range(L)] for q in range(Q)])
+    fb = [[(5e-5 * f).astype(np.float32) for f in row] for row in fb]
+    if spectra == "fp16":  # normal numbers in 16 bits, the same loop gain
+        fb = [[64 * f for f in row] for row in fb]
+        filt = [[f / 64 for f in row] for row in filt]
+    n = (rows + 24) * B
+    x = workloads.white_noise(762, Q, n)
+    say(f"B={B} rows={rows} Q={Q} L={L} {spectra}")
+    with rta.Convolver(filt, B, spectra=spectra) as cv:
+        cv.set_feedback(fb, spectra=spectra)
+        assert cv.info()["feedback_fused"] == 1
+        y = cv.run_device(x)
+    check_db(y, oracle.feedback_loop(x, filt, fb, B)[0], limit, f"feedback rows={rows}")
