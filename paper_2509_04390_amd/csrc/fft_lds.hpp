@@ -96,6 +96,93 @@ __device__ float2* fft_stockham(float2* a, float2* b, int N, int logN,
   return a;
 }
 
+// The same for N >= 512: radix 8 (radix 4 where the exponent asks for it), a
+// third to a half of the passes.  A workgroup alone on its compute unit spends
+// a pass on round trips (LDS, barrier, twiddles from L2), not on arithmetic.
+// Between passes an element lies at index i ^ ((i >> 4) & 15): the first
+// passes write with strides of 8 and 64 elements, which would otherwise hit
+// one or two of the 16 bank pairs.
+__device__ __forceinline__ int lds_swz(int i, bool on) { return on ? i ^ ((i >> 4) & 15) : i; }
+template <bool INV>
+__device__ __forceinline__ float2* fft_stockham8(float2* a, float2* b, int N, int logN,
+                                                 const float2* __restrict__ tw, int nb) {
+  constexpr float kH = 0.70710678118654752440f;  // sqrt(1/2)
+  const int tid = threadIdx.x, nt = blockDim.x;
+  auto mulj = [](float2 v) { return INV ? make_float2(-v.y, v.x) : make_float2(v.y, -v.x); };  // times -+i
+  int Ns = 1, rem = logN;
+  while (rem > 0) {
+    const int lr = rem == 2 || rem == 4 ? 2 : 3;
+    const bool sin = Ns > 1, sout = rem > lr;
+    const int per = N >> lr, lper = logN - lr;
+    const int ts = N / (Ns << lr);
+    for (int w = tid; w < nb << lper; w += nt) {
+      const int bb = w >> lper, j = w & (per - 1);
+      const float2* ab = a + bb * N;
+      float2* bbuf = b + bb * N;
+      const int k = j & (Ns - 1);
+      const int base = ((j - k) << lr) + k;
+      if (lr == 3) {
+        float2 v[8], t[8];
+        if (Ns > 1)
+#pragma unroll
+          for (int r = 1; r < 8; ++r) t[r] = tw[r * k * ts];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) v[r] = ab[lds_swz(j + r * per, sin)];
+        if (Ns > 1)
+#pragma unroll
+          for (int r = 1; r < 8; ++r) v[r] = INV ? make_float2(v[r].x * t[r].x + v[r].y * t[r].y, v[r].y * t[r].x - v[r].x * t[r].y) : cmul(v[r], t[r]);
+        // two 4-point transforms of the even and odd inputs
+        float2 e[2][4];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const float2 s02 = cadd(v[h], v[h + 4]), d02 = csub(v[h], v[h + 4]);
+          const float2 s13 = cadd(v[h + 2], v[h + 6]), d13 = csub(v[h + 2], v[h + 6]);
+          const float2 jd = mulj(d13);
+          e[h][0] = cadd(s02, s13);
+          e[h][1] = cadd(d02, jd);
+          e[h][2] = csub(s02, s13);
+          e[h][3] = csub(d02, jd);
+        }
+        // times W_8^r
+        const float2 o1 = e[1][1], o3 = e[1][3];
+        const float2 w1 = INV ? make_float2(kH * (o1.x - o1.y), kH * (o1.x + o1.y))
+                              : make_float2(kH * (o1.x + o1.y), kH * (o1.y - o1.x));
+        const float2 w2 = mulj(e[1][2]);
+        const float2 w3 = INV ? make_float2(-kH * (o3.x + o3.y), kH * (o3.x - o3.y))
+                              : make_float2(kH * (o3.y - o3.x), -kH * (o3.x + o3.y));
+        const float2 o[4] = {e[1][0], w1, w2, w3};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          bbuf[lds_swz(base + r * Ns, sout)] = cadd(e[0][r], o[r]);
+          bbuf[lds_swz(base + (r + 4) * Ns, sout)] = csub(e[0][r], o[r]);
+        }
+      } else {
+        float2 v[4], t[4];
+        if (Ns > 1)
+#pragma unroll
+          for (int r = 1; r < 4; ++r) t[r] = tw[r * k * ts];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = ab[lds_swz(j + r * per, sin)];
+        if (Ns > 1)
+#pragma unroll
+          for (int r = 1; r < 4; ++r) v[r] = INV ? make_float2(v[r].x * t[r].x + v[r].y * t[r].y, v[r].y * t[r].x - v[r].x * t[r].y) : cmul(v[r], t[r]);
+        const float2 s02 = cadd(v[0], v[2]), d02 = csub(v[0], v[2]);
+        const float2 s13 = cadd(v[1], v[3]), d13 = csub(v[1], v[3]);
+        const float2 jd = mulj(d13);
+        bbuf[lds_swz(base, sout)] = cadd(s02, s13);
+        bbuf[lds_swz(base + Ns, sout)] = cadd(d02, jd);
+        bbuf[lds_swz(base + 2 * Ns, sout)] = csub(s02, s13);
+        bbuf[lds_swz(base + 3 * Ns, sout)] = csub(d02, jd);
+      }
+    }
+    Ns <<= lr;
+    rem -= lr;
+    __syncthreads();
+    float2* x = a; a = b; b = x;
+  }
+  return a;
+}
+
 // Batched complex FFT of length N = 3 * 2^m (the 3B-point real transforms of
 // the n_f = 3 n_x variant run as N = 3B/2-point complex ones): a radix-3
 // Stockham stage first (sub-transform length 1, no twiddles), then radix-4
@@ -392,14 +479,16 @@ __device__ __forceinline__ float2* fft_wave(float2* a, float2* b, int N, const f
 
 // Complex FFT of length N = 2^logN (r3 = 0) or N = 3 * 2^logN (r3 = 1):
 // lengths 64 and 128 (blocks of 64 and 128 samples) by wavefronts with lane
-// shuffles, the others by the LDS Stockham routines.  (Longer wave variants,
-// 4 or 8 values per lane, raised the block kernel to 164 VGPRs for every
-// workgroup, the bandwidth-bound tails included.)
-template <bool INV>
+// shuffles, the others by the LDS Stockham routines, radix 8 from 512 on
+// (1 -> 32 x 480,000 taps, block 2048: a transform 6.4 -> 4.5 us).  R8 = false: radix 4
+// throughout, as the filter spectra are built (an FP32 rounding of the
+// transform that differs moves some 16-bit spectrum values to their neighbour).
+template <bool INV, bool R8 = true>
 __device__ __forceinline__ float2* fft_any(float2* a, float2* b, int N, int logN, int r3,
                                            const float2* __restrict__ tw, int nb = 1) {
   if (r3) return fft_stockham3<INV>(a, b, N, logN, tw, nb);
   if (N == 64 || N == 128) return fft_wave<INV>(a, b, N, tw, nb);
+  if (R8 && N >= 512) return fft_stockham8<INV>(a, b, N, logN, tw, nb);
   return fft_stockham<INV>(a, b, N, logN, tw, nb);
 }
 
@@ -409,8 +498,9 @@ __device__ __forceinline__ float2* fft_any(float2* a, float2* b, int N, int logN
 __device__ __forceinline__ void rfft_post(const float2* Z, float2* X, int P,
                                           const float2* __restrict__ tw2, int nb = 1) {
   const int per = (P >> 1) + 1;
+#pragma unroll 4
   for (int w = threadIdx.x; w < nb * per; w += blockDim.x) {
-    const int bb = w / per, k = w - bb * per;
+    const int bb = nb == 1 ? 0 : w / per, k = w - bb * per;
     const float2* Zb = Z + bb * P;
     float2* Xb = X + bb * P;
     if (k == 0) {
@@ -435,8 +525,9 @@ __device__ __forceinline__ void rfft_post(const float2* Z, float2* X, int P,
 __device__ __forceinline__ void irfft_pre(const float2* X, float2* Z, int P,
                                           const float2* __restrict__ tw2, int nb = 1) {
   const int per = (P >> 1) + 1;
+#pragma unroll 4
   for (int w = threadIdx.x; w < nb * per; w += blockDim.x) {
-    const int bb = w / per, k = w - bb * per;
+    const int bb = nb == 1 ? 0 : w / per, k = w - bb * per;
     const float2* Xb = X + bb * P;
     float2* Zb = Z + bb * P;
     if (k == 0) {

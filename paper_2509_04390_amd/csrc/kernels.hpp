@@ -710,6 +710,16 @@ __device__ __forceinline__ const float2* stage_twiddles(const DevTier& T, float2
   return dst;
 }
 
+// Elements of one thread that a head of more than 256 bins has in flight.
+// A loop with one element's round trip per turn made these heads 34 us of a
+// 39 us launch at 2,048 bins (1 -> 32 x 480,000 taps); 24 of 26 now, with the
+// radix-8 transforms.
+// (16-bit kernels have 128 registers: fewer there.)
+template <typename HT>
+constexpr int kHeadUnroll = sizeof(HT) == 8 ? 8 : 4;
+template <typename HT>
+constexpr int kWinUnroll = sizeof(HT) == 8 ? 4 : 2;
+
 // Sum the first tier's partial slots of a whole output group, all its
 // outputs at once (elements e = g P + k are contiguous within a slot), and
 // add the p = 1 term sum_q H_{l,q,1} X_q(n-1), which needs no new spectrum.
@@ -720,14 +730,14 @@ __device__ __forceinline__ const float2* stage_twiddles(const DevTier& T, float2
 // red_scratch(E) float2.  Ends with a barrier.
 template <typename HT, int G>
 __device__ __forceinline__ void head_reduce(const KArgs& A, const DevTier& T, const Group& grp, int64_t n,
-                            float2* Y, float2* scratch) {
+                            float2* Y, float2* scratch, int slot1) {
   const int P = T.P;
   const int E = grp.nl * P;
   const int64_t stride = (int64_t)G * P;
   const float2* base = T.partial + (int64_t)grp.slot0 * stride;
   const int tid = threadIdx.x;
   const bool has_p1 = T.K >= 2;
-  const int slot1 = wrap_slot(n - 1, T.K);
+  constexpr int kHeadU = kHeadUnroll<HT>;
   const HT* H01 = reinterpret_cast<const HT*>(A.H01);
   // inputs q0, q0 + dq, ... of the p = 1 term of element e
   auto p1_term = [&](int e, int q0, int dq) {
@@ -745,11 +755,41 @@ __device__ __forceinline__ void head_reduce(const KArgs& A, const DevTier& T, co
   };
   const int span = red_span(E);
   if (span == kThreads) {
-    for (int e = tid; e < E; e += kThreads) {
-      float2 acc = p1_term(e, 0, 1);
-#pragma unroll 16
-      for (int sl = 0; sl < grp.nslot; ++sl) acc = cadd(acc, base[sl * stride + e]);
-      Y[e] = acc;
+    // several elements of a thread at a time: every load of a step is requested
+    // before any is added up (one output: e is the bin)
+    const int l = grp.l0;
+    for (int e0 = tid; e0 < E; e0 += kHeadU * kThreads) {
+      float2 acc[kHeadU];
+#pragma unroll
+      for (int i = 0; i < kHeadU; ++i) acc[i] = make_float2(0.f, 0.f);
+      for (int q = 0; has_p1 && q < A.Q; ++q) {
+        const HT* h = H01 + ((int64_t)(l * A.Q + q) * 2 + 1) * P;
+        const float2* x = T.X + ((int64_t)q * T.K + slot1) * P;
+        typename HVec<HT>::one_t hr[kHeadU];
+        float2 xr[kHeadU];
+#pragma unroll
+        for (int i = 0; i < kHeadU; ++i) {
+          const int e = min(e0 + i * kThreads, E - 1);
+          hr[i] = HVec<HT>::load1_raw(h + e);
+          xr[i] = x[e];
+        }
+#pragma unroll
+        for (int i = 0; i < kHeadU; ++i) {
+          const float2 h1 = HVec<HT>::cvt1(hr[i]);
+          acc[i] = cadd(acc[i], e0 == 0 && i == 0 ? make_float2(h1.x * xr[i].x, h1.y * xr[i].y) : cmul(h1, xr[i]));
+        }
+      }
+#pragma unroll 2
+      for (int sl = 0; sl < grp.nslot; ++sl) {
+        float2 v[kHeadU];
+#pragma unroll
+        for (int i = 0; i < kHeadU; ++i) v[i] = base[sl * stride + min(e0 + i * kThreads, E - 1)];
+#pragma unroll
+        for (int i = 0; i < kHeadU; ++i) acc[i] = cadd(acc[i], v[i]);
+      }
+#pragma unroll
+      for (int i = 0; i < kHeadU; ++i)
+        if (e0 + i * kThreads < E) Y[e0 + i * kThreads] = acc[i];
     }
     __syncthreads();
     return;
@@ -794,7 +834,7 @@ __device__ __forceinline__ bool red_fits(int E, int nslot, int Q, int HRslots, i
 }
 template <typename HT, int G>
 __device__ __forceinline__ void red_issue(const KArgs& A, const DevTier& T, const Group& grp,
-                                          int64_t n, HeadRed<HT>& r, bool on) {
+                                          int slot1, HeadRed<HT>& r, bool on) {
   const int P = T.P;
   const int E = grp.nl * P;
   const int64_t stride = (int64_t)G * P;
@@ -819,7 +859,6 @@ __device__ __forceinline__ void red_issue(const KArgs& A, const DevTier& T, cons
 #pragma unroll
   for (int i = 0; i < HeadRed<HT>::kSlots; ++i) r.s[i] = src[min(s0 + i, last) * step];
   if (!on || T.K < 2) return;
-  const int slot1 = wrap_slot(n - 1, T.K);
   const HT* H01 = reinterpret_cast<const HT*>(A.H01);
   const int g = e / P, k = e - g * P;
   const int l = grp.l0 + g;
@@ -920,7 +959,8 @@ __host__ __device__ inline HeadLds head_lds(int P, int G, int nq) {
 // of the partial-sum reduction, the critical path under the tails' streaming,
 // independent of G.
 template <typename HT, int G>
-__device__ __forceinline__ void head_work(const KArgs& A, int64_t n, const Group& grp, int gsel, float2* lds) {
+__device__ __forceinline__ void head_work(const KArgs& A, int64_t n, int sn, int scn, const Group& grp, int gsel,
+                                          float2* lds) {
   const int tid = threadIdx.x;
   const DevTier& T = A.tier[0];
   // P bins per row, half the window of 2P samples: P = B (n_f = 2B), or
@@ -961,6 +1001,7 @@ __device__ __forceinline__ void head_work(const KArgs& A, int64_t n, const Group
   //    partial-sum loads of step 1.  (Sizes beyond the register budget fall
   //    back to loading in place.)
   constexpr int WMAX = 2, HMAX = 4, RMAX = 1, TMAX = 2;
+  constexpr int kHeadU = kHeadUnroll<HT>, kWinU = kWinUnroll<HT>;
   const int E = grp.nl * P;
   const int nb0 = min(A.head_nq, A.Q);
   const int ept = (E + kThreads - 1) / kThreads;       // output elements per thread
@@ -973,7 +1014,8 @@ __device__ __forceinline__ void head_work(const KArgs& A, int64_t n, const Group
   // heads are still computing, so it is not prefetched)
   const bool pre_w = nb0 * P <= WMAX * kThreads && !A.fc_on;
   const bool pre_h = ept * nb0 <= HMAX;
-  const bool pre_r = A.n_tiers - 1 <= TMAX && eo <= RMAX * kThreads;
+  // (16-bit kernels: loaded where they are added, for want of registers)
+  const bool pre_r = sizeof(HT) == 8 && A.n_tiers - 1 <= TMAX && eo <= RMAX * kThreads;
   // Window sample pair m of input q, [w_2m, w_2m+1]: both from the history
   // (2m < cur) or both from this block's input (cur is even).  The source is
   // selected per lane and read with unconditional loads (clamped indices,
@@ -1008,10 +1050,6 @@ __device__ __forceinline__ void head_work(const KArgs& A, int64_t n, const Group
     if (2 * (e % P) < cur) return r.w;
     const float2 v = make_float2(r.w.x - r.s.x, r.w.y - r.s.y);
     return r.live == 0 ? make_float2(0.f, 0.f) : v;  // a select: NaN input stays out
-  };
-  auto h0_at = [&](int e, int q) {
-    const int g = e / P, k = e - g * P;
-    return HVec<HT>::load1(H01 + ((int64_t)((grp.l0 + g) * A.Q + q) * 2) * P + k);
   };
   WinRaw wv[WMAX];
   typename HVec<HT>::one_t hv[HMAX];
@@ -1061,9 +1099,10 @@ __device__ __forceinline__ void head_work(const KArgs& A, int64_t n, const Group
   const bool split = red_fits(E, grp.nslot, A.Q, HeadRed<HT>::kSlots, HeadRed<HT>::kInputs);
   // (issued on both paths: one straight-line sequence of loads after the
   // window's, whatever the shape)
-  red_issue<HT, G>(A, Tcur, grp, n, red, split);
+  const int slot1 = sn == 0 ? T.K - 1 : sn - 1;
+  red_issue<HT, G>(A, Tcur, grp, slot1, red, split);
   if (!split) {
-    head_reduce<HT, G>(A, Tcur, grp, n, Y, scratch);
+    head_reduce<HT, G>(A, Tcur, grp, n, Y, scratch, slot1);
     // nothing left in flight on this path, so that the compiler's count of
     // loads still outstanding where the paths meet is the split path's
     __builtin_amdgcn_s_waitcnt(0);
@@ -1075,7 +1114,7 @@ __device__ __forceinline__ void head_work(const KArgs& A, int64_t n, const Group
   if (A.fc_on) fc_wait(A, n);
 
   // 2. the term p = 0: window -> real FFT -> ring slot n mod K, times H_{l,q,0}
-  const int slot0 = wrap_slot(n, T.K);
+  const int slot0 = sn;
   // window sample pair e of inputs q0, q0 + 1, ... into LDS; the first group
   // also stores the block's input samples (as windowed: feedback estimate
   // subtracted, silent inputs zero) into the history for later launches
@@ -1118,17 +1157,21 @@ __device__ __forceinline__ void head_work(const KArgs& A, int64_t n, const Group
         Y[e] = cadd(Y[e], (k == 0) ? make_float2(h0.x * x0.x, h0.y * x0.y) : cmul(h0, x0));
       }
     } else {
-      for (int e = tid; e < E; e += kThreads) {
-        const int k = e % P;
-        float2 acc = Y[e];
-#pragma unroll 4
+      for (int e0 = tid; e0 < E; e0 += kHeadU * kThreads)
         for (int b = 0; b < nb; ++b) {
-          const float2 h0 = h0_at(e, q0 + b);
-          const float2 x0 = x[b * P + k];
-          acc = cadd(acc, (k == 0) ? make_float2(h0.x * x0.x, h0.y * x0.y) : cmul(h0, x0));
+          const HT* h = H01 + (int64_t)(grp.l0 * A.Q + q0 + b) * 2 * P;
+          typename HVec<HT>::one_t hr[kHeadU];
+#pragma unroll
+          for (int i = 0; i < kHeadU; ++i) hr[i] = HVec<HT>::load1_raw(h + min(e0 + i * kThreads, E - 1));
+#pragma unroll
+          for (int i = 0; i < kHeadU; ++i) {
+            const int e = e0 + i * kThreads;
+            if (e >= E) continue;
+            const float2 h0 = HVec<HT>::cvt1(hr[i]);
+            const float2 x0 = x[b * P + e];
+            Y[e] = cadd(Y[e], (e == 0) ? make_float2(h0.x * x0.x, h0.y * x0.y) : cmul(h0, x0));
+          }
         }
-        Y[e] = acc;
-      }
     }
     __syncthreads();
   };
@@ -1146,13 +1189,22 @@ __device__ __forceinline__ void head_work(const KArgs& A, int64_t n, const Group
         put(0, e, win_value(e, r));
       }
     }
-  } else {
-    for (int e = tid; e < nb0 * P; e += kThreads) put(0, e, win_value(e, win_load(e, 0)));
   }
+  auto windows = [&](int q0, int nb) __attribute__((always_inline)) {
+    for (int e0 = tid; e0 < nb * P; e0 += kWinU * kThreads) {
+      WinRaw r[kWinU];
+#pragma unroll
+      for (int i = 0; i < kWinU; ++i) r[i] = win_load(min(e0 + i * kThreads, nb * P - 1), q0);
+#pragma unroll
+      for (int i = 0; i < kWinU; ++i)
+        if (e0 + i * kThreads < nb * P) put(q0, e0 + i * kThreads, win_value(e0 + i * kThreads, r[i]));
+    }
+  };
+  if (!pre_w) windows(0, nb0);
   chunk(0, nb0, true);
   for (int q0 = A.head_nq; q0 < A.Q; q0 += A.head_nq) {
     const int nb = min(A.head_nq, A.Q - q0);
-    for (int e = tid; e < nb * P; e += kThreads) put(q0, e, win_value(e, win_load(e, q0)));
+    windows(q0, nb);
     chunk(q0, nb, false);
   }
 
@@ -1162,7 +1214,7 @@ __device__ __forceinline__ void head_work(const KArgs& A, int64_t n, const Group
   // the feedback delay line as it is -- no inverse-then-forward transform
   if (A.fc_on && A.nf3) {
     const DevTier& F = A.tier[kFcTier];
-    float2* dst = F.X + ((int64_t)grp.l0 * F.K + wrap_slot(n, F.K)) * P;
+    float2* dst = F.X + ((int64_t)grp.l0 * F.K + scn) * P;
     for (int k = tid; k < P; k += kThreads) dst[k] = Y[k];
   }
 
@@ -1269,7 +1321,7 @@ __device__ __forceinline__ void head_work(const KArgs& A, int64_t n, const Group
     float2* zf = fft_any<false>(Xa, Xb, P, logP, 0, tw);
     float2* xf = (zf == Xa) ? Xb : Xa;
     rfft_post(zf, xf, P, tw + P);
-    float2* dst = A.tier[kFcTier].X + ((int64_t)l * A.tier[kFcTier].K + wrap_slot(n, A.tier[kFcTier].K)) * P;
+    float2* dst = A.tier[kFcTier].X + ((int64_t)l * A.tier[kFcTier].K + scn) * P;
     for (int k = tid; k < P; k += kThreads) dst[k] = xf[k];
   }
 }
@@ -2172,7 +2224,7 @@ __global__ __launch_bounds__(kThreads, sizeof(HT) == 4 ? 4 : 3) void k_block(con
       Group hg = g0;
       hg.l0 = b;
       hg.nl = 1;
-      head_work<HT, G>(A, n, hg, b - g0.l0, lds);
+      head_work<HT, G>(A, n, sn, scn, hg, b - g0.l0, lds);
     }
     return;
   }
@@ -2348,7 +2400,7 @@ __global__ __launch_bounds__(kThreads) void k_spectra(const float* taps, const S
                        i1 < row.len ? taps[row.src + i1] : 0.f);
   }
   __syncthreads();
-  float2* z = fft_any<false>(a, b, P, logP, r3, tw);
+  float2* z = fft_any<false, false>(a, b, P, logP, r3, tw);
   float2* x = (z == a) ? b : a;
   rfft_post(z, x, P, tw + P);
   for (int k = threadIdx.x; k < P; k += kThreads) store_bin(H, row.dst * P + k, x[k], range);

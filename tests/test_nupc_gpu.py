@@ -140,3 +140,19 @@ def test_nupc_workload_log_sweep_fp16_sampled(rta):
                           rng.integers(0, n, 60)])
     ref = oracle.direct_at(x, filt, idx)
     check_db(y[:, idx], ref, FP16_DB, "nupc workload sweep fp16")
+
+
+@pytest.mark.parametrize("tier_rows", [1, 5, 16, 40])
+@pytest.mark.parametrize("flags", [0, 1])
+def test_later_tier_item_widths(rta, tier_rows, flags):
+    """Later-tier items of one to several rounds of rows, whole rows and bin
+    slices, spread and in one block (RTA_FLAG_SPIKE)."""
+    B, scheme = 32, [(32, 20), (256, 12), (2048, 0)]
+    lens = [[30000, 12000, 700], [9000, 30001, 0]]
+    filt = make_filters(880, lens)
+    n = 34000 // B * B
+    x = workloads.white_noise(881, 2, n)
+    with rta.Convolver(filt, B, scheme=scheme, flags=flags, tuning=rta.make_tuning(tier_rows=tier_rows)) as cv:
+        y = cv.run_device(x)
+    idx = np.unique(np.r_[0, n - 1, np.random.default_rng(tier_rows).integers(0, n, 300)])
+    check_db(y[:, idx], oracle.direct_at(x, filt, idx), FP32_DB, f"tier_rows={tier_rows} flags={flags}")
