@@ -376,10 +376,13 @@ __device__ __forceinline__ WaveTw<V> wave_twiddles(const float2* __restrict__ tw
   }
   return t;
 }
+// (explicit fused multiply-adds: left to the compiler, which of the two
+// products is fused may differ from kernel to kernel, and the spectra that
+// graph replay computes for several blocks must be the heads' bit for bit)
 template <bool INV>
 __device__ __forceinline__ float2 cmul_tw(float2 a, float2 w) {
-  return INV ? make_float2(a.x * w.x + a.y * w.y, a.y * w.x - a.x * w.y)
-             : make_float2(a.x * w.x - a.y * w.y, a.x * w.y + a.y * w.x);
+  return INV ? make_float2(fmaf(a.x, w.x, a.y * w.y), fmaf(a.y, w.x, -(a.x * w.y)))
+             : make_float2(fmaf(a.x, w.x, -(a.y * w.y)), fmaf(a.y, w.x, a.x * w.y));
 }
 template <bool INV, int V, int H>
 __device__ __forceinline__ void wave_reg_stage(float2 (&r)[V], float2 w, int lane) {
@@ -445,7 +448,7 @@ __device__ __forceinline__ void pair_post(float2& za, float2& zb, float2 w, bool
   const float2 E = make_float2(0.5f * (a.x + b.x), 0.5f * (a.y + b.y));
   const float2 d = csub(a, b);
   const float2 O = make_float2(0.5f * d.y, -0.5f * d.x);  // -i d / 2
-  const float2 wO = cmul(w, O);
+  const float2 wO = cmul_tw<false>(O, w);
   za = first ? make_float2(a.x + a.y, a.x - a.y) : cadd(E, wO);
   zb = first ? b : cconj(csub(E, wO));
 }

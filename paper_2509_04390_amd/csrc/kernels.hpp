@@ -162,6 +162,10 @@ struct KArgs {
   int64_t n;                 // index of the block of this launch
   int32_t slot;              // its slot in the first tier's delay line, n mod K
   int32_t fc_slot;           // and in the feedback delay line
+  int32_t batch;             // graph replay: blocks of this launch (0: one block with
+                             // both parts)
+  int32_t batch_part;        // 1: their tails, 2: their heads
+  int32_t batch_stride;      // workgroups per block (tails: a multiple of 8)
   const Item* tier_items;    // later tiers' transform passes [n_phase][max_tier_items]
   const int32_t* tier_count; // transform items per phase
   const int32_t* tier_slot0; // [tier][group] first partial slot of later tiers
@@ -1438,7 +1442,7 @@ __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)
 
 template <typename HT, int G, int V>
 __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int scn, const Group& grp, int l,
-                                          float2* lds) {
+                                          const float* inp, float* outp, bool keep, float2* lds) {
   constexpr int N = 64 * V, NP = wave_pairs<V>(), SL = V == 4 ? 4 : 8;
   constexpr int VO = V == 4 ? 2 : 1;  // output sample pairs per lane
   constexpr int VC = V == 4 ? 2 : 1;  // window registers with samples of this block: the last VC
@@ -1473,7 +1477,7 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
   const int64_t hprev = ((n - 1) * B) & A.hist_mask, hcur = (n * B) & A.hist_mask;
   auto window = [&](int q, In& in) __attribute__((always_inline)) {
     const float* ph = A.hist + q * hlen + hprev;
-    const float* pi = A.in + (int64_t)q * B;
+    const float* pi = inp + (int64_t)q * B;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       const int i = 2 * (64 * v + lane);
@@ -1570,7 +1574,7 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
         if (cur) r[v] = in.live == 0 ? make_float2(0.f, 0.f) : make_float2(x.x - e.x, x.y - e.y);
       }
       // the first output's head keeps the block's input, as windowed
-      if (l == 0 && cur) {
+      if (keep && cur) {
         float2* ph = reinterpret_cast<float2*>(A.hist + q * hlen + hcur + 2 * (64 * v + lane) - B);
         *ph = r[v];
       }
@@ -1585,7 +1589,7 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
       const bool f = first && i == 0;
       float2 xa = zb[ka[i]], xb = zb[kb[i]];
       pair_post(xa, xb, tw2[i], f);
-      if (l == 0 && act) {  // and its spectrum, for later launches
+      if (keep && act) {  // and its spectrum, for later launches
         xn[ka[i]] = xa;
         xn[kb[i]] = xb;
       }
@@ -1653,7 +1657,7 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
 #pragma unroll
     for (int j = 0; j < VO; ++j) {
       const f32x2u o = {y[j].x, y[j].y};
-      float* po = A.out + (int64_t)l * B + 2 * (mo + 64 * j);
+      float* po = outp + (int64_t)l * B + 2 * (mo + 64 * j);
       if (A.done_flag != nullptr)  // the pinned output block (8-byte aligned): past the caches
         __hip_atomic_store(reinterpret_cast<uint64_t*>(po), __builtin_bit_cast(uint64_t, y[j]), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_SYSTEM);
@@ -2182,6 +2186,35 @@ __global__ __launch_bounds__(kThreads, sizeof(HT) == 4 ? 4 : 3) void k_block(con
     if (A.fc_on && scn >= A.tier[kFcTier].K) scn -= A.tier[kFcTier].K;
   }
   int b = blockIdx.x;
+  const float* inp = A.in;
+  float* outp = A.out;
+  bool keep = true;  // the first output's head stores the block's input and spectrum
+  if (A.batch > 0) {
+    // several blocks (their spectra are in the delay line, k_batch_in): which
+    // one, and the position within it
+    int j;
+    if (A.batch_part == 1 && A.batch % kTile == 0) {
+      // blocks kTile apart read the same far rows: side by side, on one XCD
+      const int R = A.batch / kTile, ph = b / (A.batch_stride * R);
+      b -= ph * A.batch_stride * R;
+      const int r = (b >> 3) % R, i8 = (b >> 3) / R;
+      j = ((ph - (int)n) & (kTile - 1)) + kTile * r;
+      b = i8 * 8 + (b & 7);
+    } else {
+      j = b / A.batch_stride;
+      b -= j * A.batch_stride;
+    }
+    n += j;
+    sn += j;
+    if (sn >= A.tier[0].K) sn -= A.tier[0].K;
+    inp += (int64_t)j * A.Q * A.B;
+    outp += (int64_t)j * A.L * A.B;
+    keep = false;
+    if (A.batch_part == 1) {
+      if (b >= A.max_items) return;
+      b += A.head_slots + A.tier_slots;
+    }
+  }
   if (A.fc_on) {  // grid: feedback heads | heads | transforms | tails | feedback tails
     if (b < A.fc.head_slots) {
       if (b >= A.fc.n_heads) return;
@@ -2209,16 +2242,16 @@ __global__ __launch_bounds__(kThreads, sizeof(HT) == 4 ? 4 : 3) void k_block(con
       const Group g0 = A.groups[b / G];
       const int P = A.tier[0].r3 ? 0 : A.tier[0].P;
       if (P == 128) {
-        head_wave<HT, G, 2>(A, n, sn, scn, g0, b, lds);
+        head_wave<HT, G, 2>(A, n, sn, scn, g0, b, inp, outp, keep && b == 0, lds);
         return;
       }
       if (P == 64) {
-        head_wave<HT, G, 1>(A, n, sn, scn, g0, b, lds);
+        head_wave<HT, G, 1>(A, n, sn, scn, g0, b, inp, outp, keep && b == 0, lds);
         return;
       }
       if constexpr (head_waves<HT>(256))
         if (P == 256) {
-          head_wave<HT, G, 4>(A, n, sn, scn, g0, b, lds);
+          head_wave<HT, G, 4>(A, n, sn, scn, g0, b, inp, outp, keep && b == 0, lds);
           return;
         }
       Group hg = g0;
@@ -2228,9 +2261,9 @@ __global__ __launch_bounds__(kThreads, sizeof(HT) == 4 ? 4 : 3) void k_block(con
     }
     return;
   }
-  // later tiers' transform passes of this phase, then the tails (uniform
-  // partitions: one phase, no 64-bit division)
-  const int phase = A.n_phase == 1 ? 0 : (int)(n % A.n_phase);
+  // later tiers' transform passes of this phase, then the tails (the period
+  // of the lists is a power of two)
+  const int phase = (int)n & (A.n_phase - 1);
   b -= A.head_slots;
   if (b < A.tier_slots) {
     if (b < A.tier_count[phase])
@@ -2291,6 +2324,53 @@ __global__ __launch_bounds__(kThreads, sizeof(HT) == 4 ? 4 : 3) void k_block(con
     sf = wrap_slot((n - it.lag + 1) / T.r - 1, T.K);
   }
   mac_item<HT, G, NT>(T, it, sf, lds);
+}
+
+// Graph replay of several blocks at once: the spectra of A.batch blocks from
+// their input into the delay line (which then holds the whole run besides what
+// its blocks pair with), and the input history.  One wavefront per (block,
+// input), with head_wave's transform, so that the spectra are the same bits.
+template <int V>
+__global__ __launch_bounds__(64) void k_batch_in(const KArgs args) {
+  constexpr int N = 64 * V, NP = wave_pairs<V>(), B = N;
+  __shared__ float2 zb[N];
+  (void)args;
+  const KArgs& A = *(const KArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  const DevTier& T = A.tier[0];
+  const int lane = threadIdx.x, j = blockIdx.x / A.Q, q = blockIdx.x % A.Q;
+  const int64_t n = A.n + A.n_base[0] + j;
+  int sn = A.slot + (int)A.n_base[1];
+  if (sn >= T.K) sn -= T.K;
+  sn += j;
+  if (sn >= T.K) sn -= T.K;
+  float* hist = A.hist + q * (A.hist_mask + 1);
+  const float* cur = A.in + ((int64_t)j * A.Q + q) * B;
+  const float* prev = j > 0 ? cur - (int64_t)A.Q * B : hist + (((n - 1) * B) & A.hist_mask);
+  float2* keep = reinterpret_cast<float2*>(hist + ((n * B) & A.hist_mask));
+  const WaveTw<V> tw = wave_twiddles<V>(T.tw, lane);
+  float2 r[V];
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    const int i = 2 * (64 * v + lane);
+    const f32x2u x = load_pair(i < B ? prev + i : cur + (i - B));
+    r[v] = make_float2(x.x, x.y);
+    if (i >= B) keep[(i - B) / 2] = r[v];
+  }
+  wave_fft<false, V>(r, tw, lane);
+  wave_store<V>(r, zb, lane);
+  wave_lds_fence();
+  const int pl = V == 1 ? (lane & 31) : lane;
+  float2* xn = T.X + ((int64_t)q * T.K + sn) * N;
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    const int ka = 64 * i + pl, kb = pair_hi<V>(ka);
+    float2 xa = zb[ka], xb = zb[kb];
+    pair_post(xa, xb, T.tw[N + ka], ka == 0);
+    if (V > 1 || lane < 32) {
+      xn[ka] = xa;
+      xn[kb] = xb;
+    }
+  }
 }
 
 // Graph replay's device block counter: set to v (add = 0), or advanced by v
