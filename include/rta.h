@@ -313,8 +313,8 @@ int rta_process_device(rta_ctx* ctx, const float* d_in, float* d_out,
  *   rta_graph_launch: processes the context's next n_blocks blocks from the
  *     current contents of d_in into d_out, stream-ordered on `stream`
  *     (NULL: the null stream), exactly as n_blocks rta_process_device()
- *     calls would (bit-identical output).  Uniform partitions of 64, 128 or
- *     256 samples (256: FP32 spectra) without feedback paths run up to 16
+ *     calls would (bit-identical output).  Uniform partitions of 16 to 256
+ *     samples (256: FP32 spectra) without feedback paths run up to 16
  *     blocks at once if d_in and d_out do not overlap: all their input has
  *     been read before the first of their output is written.  Mixing with rta_process[_device]
  *     is allowed as long as the context's block index is a multiple of

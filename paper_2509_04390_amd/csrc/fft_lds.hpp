@@ -348,9 +348,10 @@ __device__ __forceinline__ void fft_wave_one(const float2* __restrict__ src, flo
 }
 
 // ---------------------------------------------------------------------------
-// The same transform (N = 64 V points, V in {1, 2, 4}) entirely in one
-// wavefront's registers, twiddles included: lane i holds x[64 v + i] in
-// register v, and afterwards X[brev_small(s) + V brev6(i)] in register s.
+// The same transform (N = 64 V points, V in {1, 2, 4}; or N = 16, 32 by as many
+// lanes, the wavefront holding copies) entirely in one wavefront's registers,
+// twiddles included: lane i holds x[64 v + i] in register v, and afterwards
+// X[brev_small(s) + V brev(i)] in register s.
 // The twiddles are requested once, long before they are needed, and serve the
 // forward and (conjugated) the inverse transform.  A stage's twiddle is 1 in
 // the lanes that keep the sum, so each stage is one fused multiply-add by +-1
@@ -358,21 +359,26 @@ __device__ __forceinline__ void fft_wave_one(const float2* __restrict__ src, flo
 // its SIMD issues an instruction every 4.6 cycles, and the transform's time is
 // its instruction count.
 // ---------------------------------------------------------------------------
-template <int V>
+template <int N>
+__host__ __device__ constexpr int wave_values() { return N >= 64 ? N / 64 : 1; }
+template <int N>  // this lane's place in its transform
+__device__ __forceinline__ int wave_lane(int lane) { return N < 64 ? lane & (N - 1) : lane; }
+template <int N>
 struct WaveTw {
+  static constexpr int V = wave_values<N>();
   float2 in[V > 1 ? V - 1 : 1];  // W_N^{lane k1}, of register s = k1's bit reversal (s >= 1)
   float2 st[5];                  // stages at distance 32, 16, 8, 4, 2
 };
-template <int V>
-__device__ __forceinline__ WaveTw<V> wave_twiddles(const float2* __restrict__ tw, int lane) {
-  constexpr int N = 64 * V;
-  WaveTw<V> t;
+template <int N>
+__device__ __forceinline__ WaveTw<N> wave_twiddles(const float2* __restrict__ tw, int lane) {
+  constexpr int V = wave_values<N>();
+  WaveTw<N> t;
 #pragma unroll
   for (int s = 1; s < V; ++s) t.in[s - 1] = tw[lane * brev_small<V>(s)];
 #pragma unroll
   for (int i = 0; i < 5; ++i) {
     const int H = 32 >> i;
-    t.st[i] = tw[(lane & H) ? (lane & (H - 1)) * (N / (2 * H)) : 0];
+    if (H < N) t.st[i] = tw[(lane & H) ? (lane & (H - 1)) * (N / (2 * H)) : 0];
   }
   return t;
 }
@@ -393,8 +399,9 @@ __device__ __forceinline__ void wave_reg_stage(float2 (&r)[V], float2 w, int lan
     r[s] = H > 1 ? cmul_tw<INV>(t, w) : t;
   }
 }
-template <bool INV, int V>
-__device__ __forceinline__ void wave_fft(float2 (&r)[V], const WaveTw<V>& t, int lane) {
+template <bool INV, int N>
+__device__ __forceinline__ void wave_fft(float2 (&r)[wave_values<N>()], const WaveTw<N>& t, int lane) {
+  constexpr int V = wave_values<N>();
   if constexpr (V == 2) {
     const float2 p = r[0], q = r[1];
     r[0] = cadd(p, q);
@@ -410,8 +417,8 @@ __device__ __forceinline__ void wave_fft(float2 (&r)[V], const WaveTw<V>& t, int
   }
 #pragma unroll
   for (int s = 1; s < V; ++s) r[s] = cmul_tw<INV>(r[s], t.in[s - 1]);
-  wave_reg_stage<INV, V, 32>(r, t.st[0], lane);
-  wave_reg_stage<INV, V, 16>(r, t.st[1], lane);
+  if constexpr (N >= 64) wave_reg_stage<INV, V, 32>(r, t.st[0], lane);
+  if constexpr (N >= 32) wave_reg_stage<INV, V, 16>(r, t.st[1], lane);
   wave_reg_stage<INV, V, 8>(r, t.st[2], lane);
   wave_reg_stage<INV, V, 4>(r, t.st[3], lane);
   wave_reg_stage<INV, V, 2>(r, t.st[4], lane);
@@ -424,22 +431,33 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 // wave_fft's result to natural order in `dst` (LDS, N values).
-template <int V>
-__device__ __forceinline__ void wave_store(const float2 (&r)[V], float2* dst, int lane) {
-  const int k2 = (int)(__brev((unsigned int)lane) >> 26);
+template <int N>
+__device__ __forceinline__ void wave_store(const float2 (&r)[wave_values<N>()], float2* dst, int lane) {
+  constexpr int V = wave_values<N>();
+  const int k2 = (int)(__brev((unsigned int)wave_lane<N>(lane)) >> (N >= 64 ? 26 : N == 32 ? 27 : 28));
 #pragma unroll
   for (int s = 0; s < V; ++s) dst[brev_small<V>(s) + V * k2] = r[s];
 }
 
 // Real-transform pairs in one wavefront: pair register i of lane j holds bins
 // k = 64 i + j and N - k (k = 0: bins 0 and N / 2), N / 2 pairs in all
-// (V = 1: lanes below 32).  The split and its inverse only ever combine the
+// (N <= 64: lanes below N / 2, the others copies).  The split and its inverse only ever combine the
 // two bins of a pair, so everything between the transforms stays in a lane's
 // registers.
-template <int V>
-__host__ __device__ constexpr int wave_pairs() { return V == 4 ? 2 : 1; }
-template <int V>
-__device__ __forceinline__ int pair_hi(int k) { return k == 0 ? 32 * V : 64 * V - k; }
+template <int N>
+__host__ __device__ constexpr int wave_pairs() { return N == 256 ? 2 : 1; }
+template <int N>  // lanes that hold different pairs
+__host__ __device__ constexpr int pair_lanes() { return N >= 128 ? 64 : N / 2; }
+template <int N>
+__device__ __forceinline__ int pair_hi(int k) { return k == 0 ? N / 2 : N - k; }
+// The sum over a wavefront's copies of each pair (in every copy).
+template <int N>
+__device__ __forceinline__ float2 sum_copies(float2 v, int lane) {
+  if constexpr (pair_lanes<N>() < 64) v = cadd(v, make_float2(lane_xor<32>(v.x, lane), lane_xor<32>(v.y, lane)));
+  if constexpr (pair_lanes<N>() < 32) v = cadd(v, make_float2(lane_xor<16>(v.x, lane), lane_xor<16>(v.y, lane)));
+  if constexpr (pair_lanes<N>() < 16) v = cadd(v, make_float2(lane_xor<8>(v.x, lane), lane_xor<8>(v.y, lane)));
+  return v;
+}
 
 // Packed bins (rfft_post) of pair (k, pair_hi(k)) from the transform's values
 // za = Z[k], zb = Z[pair_hi(k)]; w = W_2N^k.

@@ -1331,8 +1331,8 @@ __device__ __forceinline__ void head_work(const KArgs& A, int64_t n, int sn, int
 }
 
 // ---------------------------------------------------------------------------
-// Head workgroup of block n for one output, first tiers of 64, 128 and 256
-// bins (P = B = 64 V): a wavefront per input and no workgroup barrier but one.
+// Head workgroup of block n for one output, first tiers of 16 to 256 bins
+// (P = B = N): a wavefront per input and no workgroup barrier but one.
 //
 // A head is a chain of dependent steps on a few hundred values; with one or
 // two wavefronts per SIMD its time is the number of instructions and round
@@ -1349,7 +1349,8 @@ __device__ __forceinline__ void head_work(const KArgs& A, int64_t n, int sn, int
 // Heads end, after the launch's first workgroup (with head_work's
 // workgroup-wide passes over LDS, a barrier each, and 64-bit divisions):
 // 1 -> 32 x 480,000 taps, B = 128 FP32 5.0 us (8.8); 4 -> 64, 128/1024/8192
-// FP16 4.4 (10.0); 3 -> 20 ragged, B = 64 BF16 4.0 (8.2).
+// FP16 4.4 (10.0); 3 -> 20 ragged, B = 64 BF16 4.0 (8.2).  Blocks of 16 and 32
+// (1 -> 5 x 95,745 taps, B = 16 FP32): 9.2 -> 5.0 us per block.
 // ---------------------------------------------------------------------------
 typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));  // user buffers: 4-byte aligned
 __device__ __forceinline__ f32x2u load_pair(const float* p) {  // in device memory (see load_at)
@@ -1360,17 +1361,19 @@ __device__ __forceinline__ f32x2u load_pair(const float* p) {  // in device memo
 // not with 16-bit spectra, whose kernels' far items run four waves per SIMD.
 template <typename HT>
 __host__ __device__ constexpr bool head_waves(int P) {
-  return P == 64 || P == 128 || (P == 256 && sizeof(HT) == 8);
+  return P == 16 || P == 32 || P == 64 || P == 128 || (P == 256 && sizeof(HT) == 8);
 }
-template <int V>
-__host__ __device__ constexpr int head_wave_lds() { return 4 * 64 * V + 3 * 2 * wave_pairs<V>() * 64; }
+__host__ __device__ constexpr int head_wave_lds(int N) { return 4 * N + 3 * 2 * (N == 256 ? 2 : 1) * 64; }
+// Shares of an output's partial slots: one per wavefront and copy of the pairs.
+template <int N>
+__host__ __device__ constexpr int slot_shares() { return 4 * (64 / pair_lanes<N>()); }
 
 // The four wavefronts' sums into wavefront 0's (in wavefront order); false in
 // the others, which are done.
-template <int V>
-__device__ __forceinline__ bool wave_sums(float2 (&ya)[wave_pairs<V>()], float2 (&yb)[wave_pairs<V>()], float2* red,
+template <int N>
+__device__ __forceinline__ bool wave_sums(float2 (&ya)[wave_pairs<N>()], float2 (&yb)[wave_pairs<N>()], float2* red,
                                           int w, int lane) {
-  constexpr int NP = wave_pairs<V>();
+  constexpr int NP = wave_pairs<N>();
   if (w > 0) {
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
@@ -1391,13 +1394,13 @@ __device__ __forceinline__ bool wave_sums(float2 (&ya)[wave_pairs<V>()], float2 
 }
 // Packed bins in pairs -> the second half of the 2N samples (times 2N), pair
 // m - N/2 of them in zb[m - N/2].
-template <int V>
-__device__ __forceinline__ void wave_inverse(float2 (&ya)[wave_pairs<V>()], float2 (&yb)[wave_pairs<V>()],
-                                             float2 (&r)[V], const WaveTw<V>& tw,
-                                             const float2 (&tw2)[wave_pairs<V>()], float2* zb,
-                                             const int (&ka)[wave_pairs<V>()], const int (&kb)[wave_pairs<V>()],
+template <int N>
+__device__ __forceinline__ void wave_inverse(float2 (&ya)[wave_pairs<N>()], float2 (&yb)[wave_pairs<N>()],
+                                             float2 (&r)[wave_values<N>()], const WaveTw<N>& tw,
+                                             const float2 (&tw2)[wave_pairs<N>()], float2* zb,
+                                             const int (&ka)[wave_pairs<N>()], const int (&kb)[wave_pairs<N>()],
                                              bool first, bool act, int lane) {
-  constexpr int N = 64 * V, NP = wave_pairs<V>();
+  constexpr int V = wave_values<N>(), NP = wave_pairs<N>();
   wave_lds_fence();
 #pragma unroll
   for (int i = 0; i < NP; ++i) {
@@ -1409,21 +1412,20 @@ __device__ __forceinline__ void wave_inverse(float2 (&ya)[wave_pairs<V>()], floa
   }
   wave_lds_fence();
 #pragma unroll
-  for (int v = 0; v < V; ++v) r[v] = zb[64 * v + lane];
-  wave_fft<true, V>(r, tw, lane);
+  for (int v = 0; v < V; ++v) r[v] = zb[64 * v + wave_lane<N>(lane)];
+  wave_fft<true, N>(r, tw, lane);
   // samples m >= N / 2 are in the odd lanes; to natural order in LDS
   wave_lds_fence();
-  if (lane & 1) wave_store<V>(r, zb - N / 2, lane);
+  if (lane & 1) wave_store<N>(r, zb - N / 2, lane);
   wave_lds_fence();
 }
-// Requests the first SL partial slots of a wavefront's (V = 1: half-wave's)
-// share of a group's: `per` contiguous ones each.  Unconditional loads, clamped
+// Requests the first SL partial slots of this lane's share of a group's: `per` contiguous ones each.  Unconditional loads, clamped
 // within the group (at the twiddles where it has no slots).
-template <int V, int SL>
-__device__ __forceinline__ void share_slots(float2 (&ps)[SL][2 * wave_pairs<V>()], const float2* base,
+template <int N, int SL>
+__device__ __forceinline__ void share_slots(float2 (&ps)[SL][2 * wave_pairs<N>()], const float2* base,
                                             const float2* dummy, int64_t stride, int nslot, int per, int w, int hw,
-                                            const int (&ka)[wave_pairs<V>()], const int (&kb)[wave_pairs<V>()]) {
-  const int from = min((V == 1 ? 2 * w : w) * per, max(nslot - 1, 0));
+                                            const int (&ka)[wave_pairs<N>()], const int (&kb)[wave_pairs<N>()]) {
+  const int from = min(w * (slot_shares<N>() / 4) * per, max(nslot - 1, 0));
   const char* src = reinterpret_cast<const char*>(nslot > 0 ? base + from * stride : dummy);
   const uint32_t step = nslot > 0 ? (uint32_t)stride * 8u : 0u;
   const int lim = max(nslot - 1 - from, 0);
@@ -1431,7 +1433,7 @@ __device__ __forceinline__ void share_slots(float2 (&ps)[SL][2 * wave_pairs<V>()
   for (int j = 0; j < SL; ++j) {
     const uint32_t at = (uint32_t)min(hw * per + j, lim) * step;
 #pragma unroll
-    for (int i = 0; i < wave_pairs<V>(); ++i) {
+    for (int i = 0; i < wave_pairs<N>(); ++i) {
       ps[j][2 * i] = load_at<false>(src, at + ka[i] * 8u, float2{});
       ps[j][2 * i + 1] = load_at<false>(src, at + kb[i] * 8u, float2{});
     }
@@ -1440,10 +1442,10 @@ __device__ __forceinline__ void share_slots(float2 (&ps)[SL][2 * wave_pairs<V>()
 // Waits until this wavefront's stores are acknowledged.
 __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-template <typename HT, int G, int V>
+template <typename HT, int G, int N>
 __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int scn, const Group& grp, int l,
                                           const float* inp, float* outp, bool keep, float2* lds) {
-  constexpr int N = 64 * V, NP = wave_pairs<V>(), SL = V == 4 ? 4 : 8;
+  constexpr int V = wave_values<N>(), NP = wave_pairs<N>(), PL = pair_lanes<N>(), SL = V == 4 ? 4 : 8;
   constexpr int VO = V == 4 ? 2 : 1;  // output sample pairs per lane
   constexpr int VC = V == 4 ? 2 : 1;  // window registers with samples of this block: the last VC
   typedef typename HVec<HT>::one_t one_t;
@@ -1454,16 +1456,16 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
   const int sp = sn == 0 ? K - 1 : sn - 1;
   float2* zb = lds + w * N;
   float2* red = lds + 4 * N;
-  // pairs: lanes below 32 alone where N / 2 = 32; the other half then takes
+  // pairs: lanes below PL; the others hold copies of the transform and take
   // other partial slots of the same pairs
-  const int pl = V == 1 ? (lane & 31) : lane, hw = V == 1 ? lane >> 5 : 0;
-  const bool act = V > 1 || lane < 32;
+  const int li = wave_lane<N>(lane), pl = lane & (PL - 1), hw = lane / PL;
+  const bool act = lane < PL;
   const bool first = pl == 0;  // (pair register 0: bins 0 and N / 2)
   int ka[NP], kb[NP];
 #pragma unroll
   for (int i = 0; i < NP; ++i) {
     ka[i] = 64 * i + pl;
-    kb[i] = pair_hi<V>(ka[i]);
+    kb[i] = pair_hi<N>(ka[i]);
   }
 
   // ---- requests, in the order they are needed
@@ -1480,8 +1482,8 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
     const float* pi = inp + (int64_t)q * B;
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-      const int i = 2 * (64 * v + lane);
-      const bool cur = V == 1 ? lane >= 32 : 2 * v >= V;
+      const int i = 2 * (64 * v + li);
+      const bool cur = V == 1 ? li >= N / 2 : 2 * v >= V;
       in.w[v] = load_pair(cur ? pi + (i - B) : ph + i);
     }
     in.live = A.live != nullptr ? A.live[q] : 1;
@@ -1489,7 +1491,7 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
   auto estimate = [&](int q, In& in) __attribute__((always_inline)) {
 #pragma unroll
     for (int v = V - VC; v < V; ++v) {
-      const int i = 2 * (64 * v + lane);
+      const int i = 2 * (64 * v + li);
       in.s[v - (V - VC)] = f32x2u{0.f, 0.f};
       if (A.sub != nullptr) {  // microphone minus the previous block's feedback estimate
         const float* ps = A.sub + (int64_t)q * B + max(i - B, 0);
@@ -1519,21 +1521,21 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
   const int q0 = min(w, Q - 1);
   window(q0, in);
   if (!A.fc_on) estimate(q0, in);
-  const WaveTw<V> tw = wave_twiddles<V>(T.tw, lane);
+  const WaveTw<N> tw = wave_twiddles<N>(T.tw, lane);
   float2 tw2[NP];
 #pragma unroll
   for (int i = 0; i < NP; ++i) tw2[i] = T.tw[N + ka[i]];
   operands(q0, in);
-  // this wavefront's (half-wave's) contiguous share of the group's slots
+  // this lane's contiguous share of the group's slots
   const int64_t stride = (int64_t)G * N;
   const float2* base = T.partial + (n & T.pmask) * (int64_t)T.nslots * stride + (int64_t)grp.slot0 * stride +
                        (int64_t)(l - grp.l0) * N;
-  constexpr int parts = V == 1 ? 8 : 4;
-  const int part = V == 1 ? 2 * w + hw : w;
+  constexpr int parts = slot_shares<N>();
+  const int part = w * (parts / 4) + hw;
   const int per = (grp.nslot + parts - 1) / parts;
   const int s0 = min(part * per, grp.nslot), s1 = min(s0 + per, grp.nslot);
   float2 ps[SL][2 * NP];
-  share_slots<V, SL>(ps, base, T.tw, stride, grp.nslot, per, w, hw, ka, kb);
+  share_slots<N, SL>(ps, base, T.tw, stride, grp.nslot, per, w, hw, ka, kb);
   // later tiers' ring samples of this block (wavefront 0 emits)
   constexpr int TMAX = 2;
   const int mo = pl;  // this lane's output sample pairs: mo + 64 j (a store covers whole cache lines)
@@ -1565,7 +1567,7 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
     float2 r[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-      const bool cur = V == 1 ? lane >= 32 : 2 * v >= V;
+      const bool cur = V == 1 ? li >= N / 2 : 2 * v >= V;
       const float2 x = make_float2(pin(in.w[v].x), pin(in.w[v].y));
       r[v] = x;
       if (v >= V - VC) {
@@ -1574,14 +1576,14 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
         if (cur) r[v] = in.live == 0 ? make_float2(0.f, 0.f) : make_float2(x.x - e.x, x.y - e.y);
       }
       // the first output's head keeps the block's input, as windowed
-      if (keep && cur) {
-        float2* ph = reinterpret_cast<float2*>(A.hist + q * hlen + hcur + 2 * (64 * v + lane) - B);
+      if (keep && cur && (N >= 64 || lane < N)) {
+        float2* ph = reinterpret_cast<float2*>(A.hist + q * hlen + hcur + 2 * (64 * v + li) - B);
         *ph = r[v];
       }
     }
-    wave_fft<false, V>(r, tw, lane);
+    wave_fft<false, N>(r, tw, lane);
     wave_lds_fence();
-    wave_store<V>(r, zb, lane);
+    wave_store<N>(r, zb, lane);
     wave_lds_fence();
     float2* xn = T.X + ((int64_t)q * K + sn) * N;
 #pragma unroll
@@ -1630,16 +1632,17 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
       ya[i] = cadd(ya[i], base[s * stride + ka[i]]);
       yb[i] = cadd(yb[i], base[s * stride + kb[i]]);
     }
-  if constexpr (V == 1) {
-    ya[0] = cadd(ya[0], make_float2(lane_xor<32>(ya[0].x, lane), lane_xor<32>(ya[0].y, lane)));
-    yb[0] = cadd(yb[0], make_float2(lane_xor<32>(yb[0].x, lane), lane_xor<32>(yb[0].y, lane)));
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    ya[i] = sum_copies<N>(ya[i], lane);
+    yb[i] = sum_copies<N>(yb[i], lane);
   }
-  if (!wave_sums<V>(ya, yb, red, w, lane)) return;
+  if (!wave_sums<N>(ya, yb, red, w, lane)) return;
 
   // ---- inverse transform, the second half of the samples (overlap-save), the
   //      later tiers' contributions from their output rings
   float2 r[V];
-  wave_inverse<V>(ya, yb, r, tw, tw2, zb, ka, kb, first, act, lane);
+  wave_inverse<N>(ya, yb, r, tw, tw2, zb, ka, kb, first, act, lane);
   const float scale = 1.0f / (float)(2 * N);
   float2 y[VO];
 #pragma unroll
@@ -1697,16 +1700,16 @@ __device__ __forceinline__ void head_wave(const KArgs& A, int64_t n, int sn, int
   wave_lds_fence();
 #pragma unroll
   for (int v = 0; v < V; ++v) {
-    const int m = 64 * v + lane;
-    const bool cur = V == 1 ? lane >= 32 : 2 * v >= V;
+    const int m = 64 * v + li;
+    const bool cur = V == 1 ? li >= N / 2 : 2 * v >= V;
     r[v] = cur ? zb[max(m - N / 2, 0)] : *reinterpret_cast<const float2*>(hl + yprev + 2 * min(m, N / 2 - 1));
   }
   if (act)
 #pragma unroll
     for (int j = 0; j < VO; ++j) *reinterpret_cast<float2*>(hl + ycur + 2 * (mo + 64 * j)) = y[j];
-  wave_fft<false, V>(r, tw, lane);
+  wave_fft<false, N>(r, tw, lane);
   wave_lds_fence();
-  wave_store<V>(r, zb, lane);
+  wave_store<N>(r, zb, lane);
   wave_lds_fence();
   float2* dst = A.tier[kFcTier].X + ((int64_t)l * A.tier[kFcTier].K + scn) * N;
 #pragma unroll
@@ -1792,37 +1795,37 @@ __device__ __forceinline__ void fc_head_work(const KArgs& A, int64_t n, int scn,
   if (tid == 0) __hip_atomic_fetch_add(F.done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// The same by wavefronts (see head_wave): wavefront w (V = 1: half-wave) adds
-// the p = 0 terms of the inputs w, w + 4, ... and its quarter of the partial
-// slots, wavefront 0 transforms back.  This head is on the latency path of
+// The same by wavefronts (see head_wave): every share (a
+// wavefront's, or a part of its lanes) adds the p = 0 terms of some inputs and
+// some of the partial slots, wavefront 0 transforms back.  This head is on the latency path of
 // every output (they wait for c): 1 -> 32 with 1 s paths it ends after 5.8 us
 // where fc_head_work, with the p = 1 terms as well, took 17.9 (block: 22.0 ->
 // 13.4 us, 39.0 before the feedback rows were tiled in time).
-template <int V>
-__host__ __device__ constexpr int fc_share() { return V == 4 ? 6 : 12; }  // slots per share
-template <typename HT, int G, int V>
+template <int N>
+__host__ __device__ constexpr int fc_share() { return N == 256 ? 6 : 12; }  // slots per share
+template <typename HT, int G, int N>
 __device__ __forceinline__ void fc_head_wave(const KArgs& A, int64_t n, int scn, int j, float2* lds) {
-  constexpr int N = 64 * V, NP = wave_pairs<V>(), U = V == 4 ? 2 : 4;
+  constexpr int V = wave_values<N>(), NP = wave_pairs<N>(), PL = pair_lanes<N>(), U = V == 4 ? 2 : 4;
   typedef typename HVec<HT>::one_t one_t;
   const FcArgs& F = A.fc;
   const DevTier& T = A.tier[kFcTier];
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int pl = V == 1 ? (lane & 31) : lane, hw = V == 1 ? lane >> 5 : 0;
+  const int pl = lane & (PL - 1), hw = lane / PL;
   const bool first = pl == 0;
-  constexpr int parts = V == 1 ? 8 : 4;
-  const int part = V == 1 ? 2 * w + hw : w;
+  constexpr int parts = slot_shares<N>();
+  const int part = w * (parts / 4) + hw;
   const int K = T.K, sp = scn == 0 ? K - 1 : scn - 1;
   float2* zb = lds + w * N;
   float2* red = lds + 4 * N;
   const Group g0 = F.groups[j / G];
-  const WaveTw<V> tw = wave_twiddles<V>(T.tw, lane);
+  const WaveTw<N> tw = wave_twiddles<N>(T.tw, lane);
   int ka[NP], kb[NP];
   float2 tw2[NP], ya[NP], yb[NP];
 #pragma unroll
   for (int i = 0; i < NP; ++i) {
     ka[i] = 64 * i + pl;
-    kb[i] = pair_hi<V>(ka[i]);
+    kb[i] = pair_hi<N>(ka[i]);
     tw2[i] = T.tw[N + ka[i]];
     ya[i] = yb[i] = make_float2(0.f, 0.f);
   }
@@ -1832,9 +1835,9 @@ __device__ __forceinline__ void fc_head_wave(const KArgs& A, int64_t n, int scn,
                        (int64_t)(j - g0.l0) * N;
   const int per = (g0.nslot + parts - 1) / parts;
   const int s0 = min(part * per, g0.nslot), s1 = min(s0 + per, g0.nslot);
-  constexpr int SL = fc_share<V>();
+  constexpr int SL = fc_share<N>();
   float2 ps[SL][2 * NP];
-  share_slots<V, SL>(ps, base, T.tw, stride, g0.nslot, per, w, hw, ka, kb);
+  share_slots<N, SL>(ps, base, T.tw, stride, g0.nslot, per, w, hw, ka, kb);
   // p = 0, U inputs in flight
   const char* H = reinterpret_cast<const char*>(reinterpret_cast<const HT*>(F.H01) + (int64_t)j * F.Qf * 2 * N);
   const char* X = reinterpret_cast<const char*>(T.X + (int64_t)sp * N);
@@ -1882,16 +1885,17 @@ __device__ __forceinline__ void fc_head_wave(const KArgs& A, int64_t n, int scn,
       ya[i] = cadd(ya[i], base[s * stride + ka[i]]);
       yb[i] = cadd(yb[i], base[s * stride + kb[i]]);
     }
-  if constexpr (V == 1) {
-    ya[0] = cadd(ya[0], make_float2(lane_xor<32>(ya[0].x, lane), lane_xor<32>(ya[0].y, lane)));
-    yb[0] = cadd(yb[0], make_float2(lane_xor<32>(yb[0].x, lane), lane_xor<32>(yb[0].y, lane)));
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    ya[i] = sum_copies<N>(ya[i], lane);
+    yb[i] = sum_copies<N>(yb[i], lane);
   }
-  if (!wave_sums<V>(ya, yb, red, w, lane)) return;
+  if (!wave_sums<N>(ya, yb, red, w, lane)) return;
   float2 r[V];
-  wave_inverse<V>(ya, yb, r, tw, tw2, zb, ka, kb, first, V > 1 || lane < 32, lane);
+  wave_inverse<N>(ya, yb, r, tw, tw2, zb, ka, kb, first, lane < PL, lane);
   const float scale = 1.0f / (float)(2 * N);
   float* cj = F.c + (int64_t)j * A.B;
-  if (lane < 32 * V)
+  if (lane < PL)
 #pragma unroll
     for (int i = 0; i < (V == 4 ? 2 : 1); ++i) {
       const int m = lane + 64 * i;
@@ -2218,20 +2222,18 @@ __global__ __launch_bounds__(kThreads, sizeof(HT) == 4 ? 4 : 3) void k_block(con
   if (A.fc_on) {  // grid: feedback heads | heads | transforms | tails | feedback tails
     if (b < A.fc.head_slots) {
       if (b >= A.fc.n_heads) return;
-      const int P = A.tier[kFcTier].r3 ? 0 : A.tier[kFcTier].P;
-      if (P == 128) {
-        fc_head_wave<HT, G, 2>(A, n, scn, b, lds);
-        return;
+      switch (A.tier[kFcTier].r3 ? 0 : A.tier[kFcTier].P) {
+        case 128: fc_head_wave<HT, G, 128>(A, n, scn, b, lds); return;
+        case 64: fc_head_wave<HT, G, 64>(A, n, scn, b, lds); return;
+        case 32: fc_head_wave<HT, G, 32>(A, n, scn, b, lds); return;
+        case 16: fc_head_wave<HT, G, 16>(A, n, scn, b, lds); return;
+        case 256:
+          if constexpr (head_waves<HT>(256)) {
+            fc_head_wave<HT, G, 256>(A, n, scn, b, lds);
+            return;
+          }
+        default: break;
       }
-      if (P == 64) {
-        fc_head_wave<HT, G, 1>(A, n, scn, b, lds);
-        return;
-      }
-      if constexpr (head_waves<HT>(256))
-        if (P == 256) {
-          fc_head_wave<HT, G, 4>(A, n, scn, b, lds);
-          return;
-        }
       fc_head_work<HT, G>(A, n, scn, b, lds);
       return;
     }
@@ -2240,20 +2242,18 @@ __global__ __launch_bounds__(kThreads, sizeof(HT) == 4 ? 4 : 3) void k_block(con
   if (b < A.head_slots) {
     if (b < A.n_head) {  // head b: output b, in group b / G
       const Group g0 = A.groups[b / G];
-      const int P = A.tier[0].r3 ? 0 : A.tier[0].P;
-      if (P == 128) {
-        head_wave<HT, G, 2>(A, n, sn, scn, g0, b, inp, outp, keep && b == 0, lds);
-        return;
+      switch (A.tier[0].r3 ? 0 : A.tier[0].P) {
+        case 128: head_wave<HT, G, 128>(A, n, sn, scn, g0, b, inp, outp, keep && b == 0, lds); return;
+        case 64: head_wave<HT, G, 64>(A, n, sn, scn, g0, b, inp, outp, keep && b == 0, lds); return;
+        case 32: head_wave<HT, G, 32>(A, n, sn, scn, g0, b, inp, outp, keep && b == 0, lds); return;
+        case 16: head_wave<HT, G, 16>(A, n, sn, scn, g0, b, inp, outp, keep && b == 0, lds); return;
+        case 256:
+          if constexpr (head_waves<HT>(256)) {
+            head_wave<HT, G, 256>(A, n, sn, scn, g0, b, inp, outp, keep && b == 0, lds);
+            return;
+          }
+        default: break;
       }
-      if (P == 64) {
-        head_wave<HT, G, 1>(A, n, sn, scn, g0, b, inp, outp, keep && b == 0, lds);
-        return;
-      }
-      if constexpr (head_waves<HT>(256))
-        if (P == 256) {
-          head_wave<HT, G, 4>(A, n, sn, scn, g0, b, inp, outp, keep && b == 0, lds);
-          return;
-        }
       Group hg = g0;
       hg.l0 = b;
       hg.nl = 1;
@@ -2330,9 +2330,9 @@ __global__ __launch_bounds__(kThreads, sizeof(HT) == 4 ? 4 : 3) void k_block(con
 // their input into the delay line (which then holds the whole run besides what
 // its blocks pair with), and the input history.  One wavefront per (block,
 // input), with head_wave's transform, so that the spectra are the same bits.
-template <int V>
+template <int N>
 __global__ __launch_bounds__(64) void k_batch_in(const KArgs args) {
-  constexpr int N = 64 * V, NP = wave_pairs<V>(), B = N;
+  constexpr int V = wave_values<N>(), NP = wave_pairs<N>(), PL = pair_lanes<N>(), B = N;
   __shared__ float2 zb[N];
   (void)args;
   const KArgs& A = *(const KArgs*)__builtin_amdgcn_kernarg_segment_ptr();
@@ -2347,26 +2347,26 @@ __global__ __launch_bounds__(64) void k_batch_in(const KArgs args) {
   const float* cur = A.in + ((int64_t)j * A.Q + q) * B;
   const float* prev = j > 0 ? cur - (int64_t)A.Q * B : hist + (((n - 1) * B) & A.hist_mask);
   float2* keep = reinterpret_cast<float2*>(hist + ((n * B) & A.hist_mask));
-  const WaveTw<V> tw = wave_twiddles<V>(T.tw, lane);
+  const WaveTw<N> tw = wave_twiddles<N>(T.tw, lane);
   float2 r[V];
 #pragma unroll
   for (int v = 0; v < V; ++v) {
-    const int i = 2 * (64 * v + lane);
+    const int i = 2 * (64 * v + wave_lane<N>(lane));
     const f32x2u x = load_pair(i < B ? prev + i : cur + (i - B));
     r[v] = make_float2(x.x, x.y);
-    if (i >= B) keep[(i - B) / 2] = r[v];
+    if (i >= B && (N >= 64 || lane < N)) keep[(i - B) / 2] = r[v];
   }
-  wave_fft<false, V>(r, tw, lane);
-  wave_store<V>(r, zb, lane);
+  wave_fft<false, N>(r, tw, lane);
+  wave_store<N>(r, zb, lane);
   wave_lds_fence();
-  const int pl = V == 1 ? (lane & 31) : lane;
+  const int pl = lane & (PL - 1);
   float2* xn = T.X + ((int64_t)q * T.K + sn) * N;
 #pragma unroll
   for (int i = 0; i < NP; ++i) {
-    const int ka = 64 * i + pl, kb = pair_hi<V>(ka);
+    const int ka = 64 * i + pl, kb = pair_hi<N>(ka);
     float2 xa = zb[ka], xb = zb[kb];
     pair_post(xa, xb, T.tw[N + ka], ka == 0);
-    if (V > 1 || lane < 32) {
+    if (lane < PL) {
       xn[ka] = xa;
       xn[kb] = xb;
     }

@@ -536,9 +536,11 @@ TilePlan tile_plan(const rta_ctx* c) {
   const bool from_regs = ng > 0 && is_pow2(T.P) && (c->Q + ng - 1) / ng <= HeadRed<float2>::kInputs;
   int64_t cap = from_regs ? (int64_t)HeadRed<float2>::kSlots * ng : 32;
   if (c->tail_p0 == 1 && !T.r3) {  // what fc_head_wave requests up front
-    if (T.P == 64) cap = 8 * fc_share<1>();
-    if (T.P == 128) cap = 4 * fc_share<2>();
-    if (T.P == 256) cap = 4 * fc_share<4>();
+    if (T.P == 16) cap = slot_shares<16>() * fc_share<16>();
+    if (T.P == 32) cap = slot_shares<32>() * fc_share<32>();
+    if (T.P == 64) cap = slot_shares<64>() * fc_share<64>();
+    if (T.P == 128) cap = slot_shares<128>() * fc_share<128>();
+    if (T.P == 256) cap = slot_shares<256>() * fc_share<256>();
   }
   int runs = 1;
   while (runs < 16 && far >= 2 * runs * kTile) runs *= 2;
@@ -1848,7 +1850,7 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
   // With later tiers, also a transform pass's buffers (kTierLds).
   size_t head = (size_t)head_lds(P0, 1, c->head_nq).total;
   if (!c->tier[0].r3 && (c->dtype == RTA_FP32 ? head_waves<float2>(P0) : head_waves<f16c_t>(P0)))
-    head = P0 == 64 ? head_wave_lds<1>() : P0 == 128 ? head_wave_lds<2>() : head_wave_lds<4>();
+    head = head_wave_lds(P0);
   c->lds = sizeof(float2) * std::max(head,
                                      (size_t)kThreads * (c->tiled ? tile_outputs(c->G) * kTile : C * c->G));
   if (c->n_tiers > 1) c->lds = std::max(c->lds, sizeof(float2) * (size_t)kTierLds);
@@ -2533,9 +2535,11 @@ static hipError_t graph_batch(rta_ctx* c, const float* d_in, float* d_out, int32
   a.batch = nb;
   const dim3 in_grid((unsigned)nb * c->Q);
   switch (c->tier[0].P) {
-    case 64: hipLaunchKernelGGL(k_batch_in<1>, in_grid, dim3(64), 0, s, a); break;
-    case 128: hipLaunchKernelGGL(k_batch_in<2>, in_grid, dim3(64), 0, s, a); break;
-    default: hipLaunchKernelGGL(k_batch_in<4>, in_grid, dim3(64), 0, s, a); break;
+    case 16: hipLaunchKernelGGL(k_batch_in<16>, in_grid, dim3(64), 0, s, a); break;
+    case 32: hipLaunchKernelGGL(k_batch_in<32>, in_grid, dim3(64), 0, s, a); break;
+    case 64: hipLaunchKernelGGL(k_batch_in<64>, in_grid, dim3(64), 0, s, a); break;
+    case 128: hipLaunchKernelGGL(k_batch_in<128>, in_grid, dim3(64), 0, s, a); break;
+    default: hipLaunchKernelGGL(k_batch_in<256>, in_grid, dim3(64), 0, s, a); break;
   }
   hipError_t e = hipGetLastError();
   const BlockKernel k = block_kernel(c->dtype, c->G, c->nt);

@@ -1,5 +1,5 @@
 """Graph replay that runs several blocks at once (uniform partitions tiled in
-time, 64, 128 and 256 bins): bit for bit what one rta_process_device call per
+time, 16 to 256 bins): bit for bit what one rta_process_device call per
 block gives, for runs of whole and partial batches, replayed and mixed with
 single blocks and resets, and with input and output in the same buffer."""
 import numpy as np
@@ -24,6 +24,7 @@ def rta():
 
 @pytest.mark.parametrize("M", [1, 5, 8, 16, 21, 64])
 @pytest.mark.parametrize("B,lens,spectra", [(64, [[64 * 18, 64 * 30, 0], [64 * 33 + 5, 700, 64 * 19]], "fp32"),
+                                            (16, [[16 * 20, 16 * 300 + 7]], "fp32"), (32, [[32 * 25], [32 * 18]], "bf16"),
                                             (128, [[128 * 45 + 1, 128 * 20]], "fp16"),
                                             (256, [[256 * 40]], "fp32")])
 def test_runs_of_blocks_equal_single_blocks(rta, B, lens, spectra, M):

@@ -1,4 +1,4 @@
-"""Heads that run by wavefronts (first tiers of 64, 128 and 256 bins): inputs
+"""Heads that run by wavefronts (first tiers of 16 to 256 bins): inputs
 beyond one round of the four wavefronts, partial slots beyond what is
 prefetched, later tiers' rings, the separate and the fused feedback
 convolution, and unaligned device buffers, against the FP64 oracle."""
@@ -21,7 +21,7 @@ def rta():
     return mod
 
 
-@pytest.mark.parametrize("B", [64, 128, 256])
+@pytest.mark.parametrize("B", [16, 32, 64, 128, 256])
 @pytest.mark.parametrize("Q,rows", [(1, 1), (1, 70), (4, 30), (5, 9), (9, 4)])
 def test_inputs_and_slots(rta, B, Q, rows):
     """rows partitions read one to an item: up to 68 slots per input."""
@@ -38,7 +38,7 @@ def test_inputs_and_slots(rta, B, Q, rows):
     check_db(y, oracle.direct(x, filt, 0, n), FP32_DB, f"B={B} Q={Q} rows={rows}")
 
 
-@pytest.mark.parametrize("B,scheme", [(64, [(64, 12), (512, 0)]), (128, [(128, 15), (1024, 14), (8192, 0)]),
+@pytest.mark.parametrize("B,scheme", [(16, [(16, 8), (64, 3), (256, 0)]), (32, [(32, 12), (256, 0)]), (64, [(64, 12), (512, 0)]), (128, [(128, 15), (1024, 14), (8192, 0)]),
                                       (256, [(256, 15), (2048, 0)]),
                                       (64, [(64, 12), (256, 8), (512, 8), (1024, 0)])])
 def test_rings_and_feedback(rta, B, scheme):
@@ -61,7 +61,7 @@ def test_rings_and_feedback(rta, B, scheme):
             check_db(y, ref, FP32_DB if fused else -60.0, f"feedback {spectra}")
 
 
-@pytest.mark.parametrize("B", [64, 128, 256])
+@pytest.mark.parametrize("B", [16, 32, 64, 128, 256])
 def test_unaligned_device_buffers(rta, B):
     import torch
     filt = make_filters(830, [[B * 20, B * 3], [B * 7, B]])
