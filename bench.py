@@ -13,9 +13,10 @@ Printed on one JSON line:
   latency       p50/p99/max of synchronous host-memory rta_process() calls
                 (PCIe copies included) issued one every B/fs as an audio
                 callback would, against the deadline B/fs; also back to back;
-  roofline      algorithmic bytes per launch of the block kernel k_block
-                (every spectrum row once, every delay-line slot once, the
-                input and output blocks) / its mean duration from HIP events
+  roofline      bytes that a launch of the block kernel k_block streams
+                (spectrum rows and delay-line slots, far ones once in eight
+                blocks under uniform partitions, the input and output
+                blocks) / its mean duration from HIP events
                 on the launch stream, vs 8 TB/s;
   cpu_baseline  the FP64 oracle (single-partition FFT overlap-save) timed on
                 the host cores over the workload's whole signal (independent
