@@ -2741,6 +2741,7 @@ int rta_set_feedback(rta_ctx* c, const float* const* fb, const int64_t* lengths,
   }
   HIP_TRY(c, hipDeviceSynchronize());
   c->config_gen += 1;  // graphs captured so far no longer match
+  c->n_dev_value = -1;  // and the device counter holds a slot of the old feedback delay line
   if (c->fc) {
     free_all(c->fc);
     delete c->fc;

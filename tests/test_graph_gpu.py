@@ -152,3 +152,38 @@ def test_autotune_cache_round_trip(rta, tmp_path):
     with rta.Convolver(filt, B, scheme=None if len(s2) == 1 else s2, tuning=t2) as cv:
         y = cv.run(x)
     check_db(y, oracle.direct(x, filt, 0, x.shape[1]), FP32_DB, "cached tuning")
+
+
+@pytest.mark.parametrize("rows", [(5, 40), (40, 5)])
+def test_replay_after_new_feedback_paths(rta, rows):
+    """Feedback paths replaced between two graphs, the second replayed at the
+    block index where the first one ended: the device counter's place in the
+    feedback delay line is that of the new paths (3 slots at least, so the two
+    lengths disagree about it)."""
+    import torch
+    B, M = 32, 16
+    filt = make_filters(540, [[900, 1300]])
+    fbs = [[[(0.02 * f).astype(np.float32) for f in r] for r in make_filters(541 + k, [[B * n, B * n - 5]])]
+           for k, n in enumerate(rows)]
+    xb = blocks_of(padded_signal(543, 1, 3 * M, B, 0), B)
+    with rta.Convolver(filt, B) as cv:
+        cv.set_feedback(fbs[1])
+        ref = direct(cv, xb)
+        cv.set_feedback(fbs[0])
+        gin = torch.empty((M, 1, B), dtype=torch.float32, device="cuda")
+        gout = torch.empty((M, 2, B), dtype=torch.float32, device="cuda")
+        gin.copy_(xb[:M])
+        with cv.graph(gin, gout, M) as g:
+            g.launch()
+            torch.cuda.synchronize()
+        cv.set_feedback(fbs[1])
+        yb = torch.empty_like(ref)
+        with cv.graph(gin, gout, M) as g:
+            for b in range(M):
+                cv.process_device(xb[b], yb[b])
+            for k in (1, 2):
+                gin.copy_(xb[k * M:(k + 1) * M])
+                g.launch()
+                yb[k * M:(k + 1) * M].copy_(gout)
+            torch.cuda.synchronize()
+    assert torch.equal(yb, ref)
