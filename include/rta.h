@@ -270,10 +270,11 @@ int rta_autotune_cached(const char* cache_path, double fs, int32_t block,
 /* Process one block, host memory in and out, synchronously.
  *   in   [n_in][block] FP32 host array (row-major), read during the call.
  *   out  [n_out][block] FP32 host array, valid on return.
- * The input is copied into the context's pinned, device-mapped buffer and
- * one kernel is launched on the context's own stream.  Its output
- * workgroups read that buffer and write the output block straight into a
- * second pinned buffer over PCIe (no DMA copies); the last of them raises a
+ * The input is copied into one of the context's two pinned, device-mapped
+ * input blocks (in turn: with later tiers the launch may still read it when
+ * the call returns) and one kernel is launched on the context's own stream.
+ * Its output workgroups read that block and write the output block straight into
+ * another pinned buffer over PCIe (no DMA copies); the last of them raises a
  * flag in pinned memory, on which the call spins before copying the output
  * to `out`.  The multiply-accumulate of partitions >= 2 for the next block,
  * in the same launch, keeps running after the call returns; the next call is

@@ -10,7 +10,8 @@
 //     [Q][hist_len]; per later tier an output ring [L][ring_len];
 //   - the tail work list, built once at creation and checked against every
 //     buffer bound;
-//   - pinned, device-mapped input/output/flag buffers for rta_process.
+//   - pinned, device-mapped buffers for rta_process: two input blocks, the
+//     output block, the flag.
 // Each block is one k_block launch on a stream; the block index is kept on
 // the host and passed by value.
 #include <hip/hip_runtime.h>
@@ -165,10 +166,12 @@ struct rta_ctx {
   int64_t n_dev_value = -1;    // what it holds once enqueued work is done (-1: unknown)
   int64_t config_gen = 0;      // bumped when the launch configuration changes
 
-  float* h_in = nullptr;       // pinned host staging, mapped into the device
+  float* h_in = nullptr;       // pinned host staging, mapped into the device: two input
+                               // blocks (see rta_process)
   float* h_out = nullptr;
   int64_t* h_flag = nullptr;
   int32_t* h_status = nullptr; // pinned error word the kernels may set
+  int in_half = 0;             // the input block that the next rta_process writes
   float* m_in = nullptr;       // device addresses of the four
   float* m_out = nullptr;
   int64_t* m_flag = nullptr;
@@ -1815,7 +1818,7 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
 
   // rta_process I/O and completion flag: pinned host memory that the kernel
   // reads and writes directly over PCIe (no DMA copies on the latency path)
-  if (hipHostMalloc(reinterpret_cast<void**>(&c->h_in), sizeof(float) * (size_t)c->Q * c->B,
+  if (hipHostMalloc(reinterpret_cast<void**>(&c->h_in), sizeof(float) * 2 * (size_t)c->Q * c->B,
                     hipHostMallocMapped) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void**>(&c->h_out), sizeof(float) * (size_t)c->L * c->B,
                     hipHostMallocMapped) != hipSuccess ||
@@ -2462,10 +2465,17 @@ int rta_process(rta_ctx* c, const float* in, float* out) {
   if (c->poisoned) return RTA_E_DEVICE;
   using clk = std::chrono::steady_clock;
   const clk::time_point ta = clk::now();
-  std::memcpy(c->h_in, in, sizeof(float) * (size_t)c->Q * c->B);
+  // Two pinned input blocks in turn.  The flag says that the heads of a launch
+  // are done, not that its later tiers' transforms are, which read the block's
+  // input too and may start as the last heads end: the next call must not write
+  // over it.  The call after that may: its predecessor's launch has begun, so
+  // this one has ended.
+  const int64_t half = (int64_t)c->in_half * c->Q * c->B;
+  std::memcpy(c->h_in + half, in, sizeof(float) * (size_t)c->Q * c->B);
   const int64_t want = c->block + 1;
   const clk::time_point tb = clk::now();
-  int st = launch_block(c, c->m_in, c->m_out, c->stream, true);
+  int st = launch_block(c, c->m_in + half, c->m_out, c->stream, true);
+  c->in_half ^= 1;
   if (st != RTA_OK) return st;
   // spin until the last head has raised the flag; the tail workgroups of the
   // same launch keep running.  No runtime call on the normal path: only once

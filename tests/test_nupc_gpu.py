@@ -156,3 +156,18 @@ def test_later_tier_item_widths(rta, tier_rows, flags):
         y = cv.run_device(x)
     idx = np.unique(np.r_[0, n - 1, np.random.default_rng(tier_rows).integers(0, n, 300)])
     check_db(y[:, idx], oracle.direct_at(x, filt, idx), FP32_DB, f"tier_rows={tier_rows} flags={flags}")
+
+
+@pytest.mark.parametrize("L", [8, 600])
+def test_host_blocks_back_to_back(rta, L):
+    """Host blocks with no pause between the calls, few outputs and more than
+    run at once (the later tiers' transforms then start as the last outputs
+    end, after the call they belong to has returned): bit for bit the
+    device-resident run."""
+    B, scheme = 64, [(64, 12), (512, 0)]
+    filt = make_filters(890, [[2600 - l for l in range(L)]] * 2)
+    x = workloads.white_noise(891, 2, 200 * B)
+    with rta.Convolver(filt, B, scheme=scheme) as cv:
+        y = cv.run_device(x)
+        cv.reset()
+        assert np.array_equal(cv.run(x), y)
