@@ -289,6 +289,10 @@ int dev_alloc(rta_ctx* c, T** p, size_t count) {
 }
 
 size_t spectra_elem_bytes(int dtype) { return dtype == RTA_FP32 ? 8 : 4; }
+// Heads of P bins run by wavefronts (k_block's choice)
+bool wave_heads(int dtype, int P, int r3) {
+  return !r3 && (dtype == RTA_FP32 ? head_waves<float2>(P) : head_waves<f16c_t>(P));
+}
 int vec_bins(int) { return 2; }  // bins per lane and row in the multiply-accumulate (HVec<>::C)
 
 // W_P^j (j < P) then W_2P^k (k < P), FP64 evaluated then rounded to FP32.
@@ -1670,9 +1674,8 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
     T.K = std::max(t == 0 ? c->min_ring : 1, kmax);
     // contexts whose graphs may run kBatch blocks at once: the delay line holds
     // all of them besides what the first one pairs with
-    c->batch_ok = sv == nullptr && c->n_tiers == 1 && c->min_ring == 1 && c->rows_per_item == 0 && !T.r3 &&
-                  kmax >= 2 * kTile + 2 &&
-                  (c->dtype == RTA_FP32 ? head_waves<float2>(T.P) : head_waves<f16c_t>(T.P));
+    c->batch_ok = sv == nullptr && c->n_tiers == 1 && c->min_ring == 1 && c->rows_per_item == 0 &&
+                  kmax >= 2 * kTile + 2 && wave_heads(c->dtype, T.P, T.r3);
     if (c->batch_ok) T.K += kBatch;
     off += (int64_t)T.count * T.span;
     if (sv != nullptr) {
@@ -1851,9 +1854,8 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
   const int fixed = head_lds(P0, 1, 1).total - 2 * P0;
   c->head_nq = std::max(1, std::min(c->Q, (6144 - fixed) / (2 * P0)));
   // With later tiers, also a transform pass's buffers (kTierLds).
-  size_t head = (size_t)head_lds(P0, 1, c->head_nq).total;
-  if (!c->tier[0].r3 && (c->dtype == RTA_FP32 ? head_waves<float2>(P0) : head_waves<f16c_t>(P0)))
-    head = head_wave_lds(P0);
+  const size_t head = (size_t)(wave_heads(c->dtype, P0, c->tier[0].r3) ? head_wave_lds(P0)
+                                                                       : head_lds(P0, 1, c->head_nq).total);
   c->lds = sizeof(float2) * std::max(head,
                                      (size_t)kThreads * (c->tiled ? tile_outputs(c->G) * kTile : C * c->G));
   if (c->n_tiers > 1) c->lds = std::max(c->lds, sizeof(float2) * (size_t)kTierLds);
@@ -2766,7 +2768,9 @@ int rta_set_feedback(rta_ctx* c, const float* const* fb, const int64_t* lengths,
     // slots (this launch writes slot n while its heads read n-1 and its items
     // n-1 and older).
     const int P = c->tier[0].P, C = vec_bins(c->dtype);
-    const size_t fc_head = sizeof(float2) * (size_t)std::max(3 * P + tw_lds_len(P) + red_scratch(P), 4 * P + 6 * 128);
+    const size_t fc_head = sizeof(float2) * (size_t)(wave_heads(c->dtype, P, c->tier[0].r3)
+                                                         ? head_wave_lds(P)
+                                                         : 3 * P + tw_lds_len(P) + red_scratch(P));
     const size_t fc_tail = sizeof(float2) * (size_t)kThreads * std::max(tile_outputs(c->G) * kTile, C * c->G);
     c->lds_fused = std::max(c->lds, std::max(fc_head, fc_tail));
     int max_lds = 0;

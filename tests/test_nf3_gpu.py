@@ -144,3 +144,20 @@ def test_nf3_rejections(rta):
         x = padded_signal(762, 1, 10, B, 1000)
         y = cv.run(x)   # the context is untouched by the refused call
     check_db(y, oracle.direct(x, h, 0, x.shape[1]), FP32_DB, "n_f=3B after a refused call")
+
+
+@pytest.mark.parametrize("B,flags,spectra,limit", [(4096, 2, "fp32", FP32_DB), (4096, 2, "fp16", -60.0),
+                                                   (2048, 2, "fp32", FP32_DB), (4096, 0, "fp32", FP32_DB)])
+def test_fused_feedback_of_the_largest_blocks(rta, B, flags, spectra, limit):
+    """The feedback heads of 4,096-sample blocks with 3B-point transforms
+    (6,144 bins) fit in LDS: n_f = 3B takes feedback paths fused or not at all."""
+    h = weak(make_filters(770, [[3 * B + 5, B]]), 0.1)
+    f = weak(make_filters(771, [[2 * B + 9, 700]]), 0.002)
+    m = workloads.white_noise(772, 1, 12 * B)
+    with rta.Convolver(h, B, spectra=spectra, flags=flags) as cv:
+        cv.set_feedback(f, spectra=spectra)
+        assert cv.info()["feedback_fused"] == 1
+        y = cv.run_device(m)
+    l_ref, c_ref, mt_ref = oracle.feedback_loop(m, h, f, B)
+    bound = limit if spectra == "fp32" else fused_bound(limit, c_ref, mt_ref)[0]
+    check_db(y, l_ref, bound, f"fused feedback B={B} flags={flags} {spectra}")
