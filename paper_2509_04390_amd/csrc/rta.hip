@@ -1026,7 +1026,10 @@ int build_plan(rta_ctx* c, Plan& plan) {
   for (int ph = 0; ph < n_list; ++ph) {
     std::vector<Bucket> buckets;
     for (const Item& it : far[ph]) add_to_bucket(buckets, it, it.nl, 1 + it.group / tile.unit);
-    for (const Item& it : tier0) add_to_bucket(buckets, it, plan.groups[it.group].nl);
+    // (near items, of up to kNearInputs inputs each: a bucket of them all would
+    // put the near rows of every output on one XCD)
+    for (const Item& it : tier0)
+      add_to_bucket(buckets, it, plan.groups[it.group].nl, c->tiled ? it.group * kXcds / ngroups : 0);
     if (c->n_tiers > 1)
       for (const Item& it : tier_mac[ph]) add_to_bucket(buckets, it, plan.groups[it.group].nl);
     plan.block[ph] = place_on_xcds(buckets);
