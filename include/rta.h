@@ -195,7 +195,11 @@ int rta_create(rta_ctx** out, double fs, int32_t block,
  *   tail_rows          partitions per first-tier item; overrides tail_items,
  *                      and has every row read every block (else uniform
  *                      partitions of 18 rows or more are read once for eight
- *                      blocks from the ninth row on).
+ *                      blocks from the ninth row on, while the partial sums of
+ *                      the 16 blocks kept for it take no more memory than the
+ *                      spectra or 64 MB and an input's delay line holds at
+ *                      most 2^28 bins; a context that does not fit in device
+ *                      memory with them is made without).
  *   tier_rows          partitions per later-tier item (default 16).
  *   bin_slices         S in {1, 2, 4, 8}: first-tier items cover 1/S of a
  *                      partition row's bins over S times more rows, so each

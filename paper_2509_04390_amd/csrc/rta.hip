@@ -134,6 +134,7 @@ struct rta_ctx {
   int n_list = 1;              // work lists per phase period: n_phase, or kTile when tiled
   bool tiled = false;
   bool batch_ok = false;       // graphs run kBatch blocks at once
+  int max_sums = 2 * kBatch;   // blocks whose partial sums it may keep (see create_ctx)
   int tail_items = 512, tier_rows = 16;
   int max_group_slots = 0;     // first tier: the most partial slots of one output group
   int spectra_loads = 0;       // 0 default, 1 non-temporal, 2 ordinary
@@ -1616,6 +1617,34 @@ int serve_lists(rta_ctx* c, Plan& plan) {
   return RTA_OK;
 }
 
+// Far partitions tiled in time (kernels.hpp, mac_tile): uniform partitions,
+// unless the caller set the rows per item, once a delay line is longer than
+// two tiles (shorter ones have as many near rows as far ones).  Graphs run
+// kBatch blocks at once where the heads run by wavefronts; the delay line then
+// holds all of them besides what the first one pairs with.  Either only while
+// the partial sums of all blocks kept take no more memory than the spectra
+// (many inputs with few partitions each would) or 64 MB.
+void choose_tiling(rta_ctx* c) {
+  TierHost& T = c->tier[0];
+  const int64_t ring = int64_t(1) << 28;  // 32-bit byte offsets into an input's ring
+  c->tiled = c->max_sums >= 2 * kTile && c->rows_per_item == 0 && T.parts >= 2 * kTile + 2 &&
+             (int64_t)T.K * T.P <= ring;
+  if (!c->tiled) return;
+  const double sums = (double)tile_plan(c).slots * c->G * T.P * 8.0;  // of a block
+  const double limit = std::max((double)(64 << 20), (double)c->spectra_bytes);
+  c->tiled = sums * 2 * kTile <= limit;
+  c->batch_ok = c->tiled && c->max_sums >= 2 * kBatch && c->serve == nullptr && c->min_ring == 1 &&
+                wave_heads(c->dtype, T.P, T.r3) && sums * 2 * kBatch <= limit &&
+                (int64_t)(T.K + kBatch) * T.P <= ring;
+  if (c->batch_ok) T.K += kBatch;
+}
+
+// Partial sums of a tier's `slots` slots (the first tier's go by block index).
+int alloc_partial(rta_ctx* c, TierHost& T, int64_t slots) {
+  const size_t bufs = &T == &c->tier[0] ? partial_blocks(c) : 1;
+  return dev_alloc(c, &T.partial, bufs * (size_t)std::max<int64_t>(1, slots) * c->G * T.P);
+}
+
 int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>& count,
                 const float* const* filters, const int64_t* lengths) {
   int st;
@@ -1675,11 +1704,6 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
     T.count = count[t] > 0 ? count[t] : kmax;
     T.parts = kmax;
     T.K = std::max(t == 0 ? c->min_ring : 1, kmax);
-    // contexts whose graphs may run kBatch blocks at once: the delay line holds
-    // all of them besides what the first one pairs with
-    c->batch_ok = sv == nullptr && c->n_tiers == 1 && c->min_ring == 1 && c->rows_per_item == 0 &&
-                  kmax >= 2 * kTile + 2 && wave_heads(c->dtype, T.P, T.r3);
-    if (c->batch_ok) T.K += kBatch;
     off += (int64_t)T.count * T.span;
     if (sv != nullptr) {
       T.kcap = kmax;
@@ -1690,6 +1714,7 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
     }
     const double per_block = (double)c->B / T.span;  // a tier's frame recurs every P/B blocks
     c->spectra_bytes += rows * T.P * (int64_t)eb;
+    if (c->n_tiers == 1) choose_tiling(c);
     c->h_bytes += (double)rows * T.P * eb * per_block;
     c->cmacs += (double)rows * T.P * per_block;
     c->x_bytes += (double)c->Q * kmax * T.P * 8.0 * per_block;
@@ -1701,6 +1726,9 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
     T.h_rows = std::max<int64_t>(1, rows);
     if ((st = dev_alloc(c, reinterpret_cast<char**>(&T.H), (size_t)T.h_rows * T.P * eb)) != RTA_OK)
       return st;
+    // (tiled: before the spectra are built, so that a context that has to do
+    // with fewer sums finds out early)
+    if (c->tiled && (st = alloc_partial(c, T, tile_plan(c).slots)) != RTA_OK) return st;
     if ((st = dev_alloc(c, &T.pair_row, T.row.size())) != RTA_OK) return st;
     if ((st = dev_alloc(c, &T.pair_K, T.kp.size())) != RTA_OK) return st;
     if ((st = dev_alloc(c, &T.X, (size_t)c->Q * T.K * T.P)) != RTA_OK) return st;
@@ -1734,22 +1762,9 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
   HIP_TRY(c, launch_gather(c->dtype, c->tier[0], c->L * c->Q, c->H01, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
 
-  // outputs per group: as requested, halved until a head's LDS fits
   int max_lds = 0;
   HIP_TRY(c, hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device));
 
-
-  // Far partitions tiled in time (kernels.hpp, mac_tile): uniform partitions,
-  // unless the caller set the rows per item, once a delay line is longer than
-  // two tiles (shorter ones have as many near rows as far ones) and the
-  // partial sums of all blocks kept take no more memory than the spectra (many
-  // inputs with few partitions each would) or 64 MB
-  c->tiled = c->n_tiers == 1 && c->rows_per_item == 0 && c->tier[0].parts >= 2 * kTile + 2 &&
-             (int64_t)c->tier[0].K * c->tier[0].P <= (int64_t(1) << 28);  // 32-bit byte offsets
-  if (c->tiled && (double)tile_plan(c).slots * (c->batch_ok ? 2 * kBatch : 2 * kTile) * c->G * c->tier[0].P * 8.0 >
-                      std::max((double)(64 << 20), (double)c->spectra_bytes))
-    c->tiled = false;
-  c->batch_ok = c->batch_ok && c->tiled;
   if (c->tiled && sv == nullptr) {  // far rows are streamed once in kTile blocks, and so are their delay-line slots
     const TierHost& T = c->tier[0];
     auto streamed = [](int kp) { return std::min(kp, kTile + 1) + std::max(0, kp - kTile - 1) / (double)kTile; };
@@ -1816,9 +1831,11 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
 
   for (int t = 0; t < c->n_tiers; ++t) {
     TierHost& T = c->tier[t];
-    const size_t bufs = t == 0 ? partial_blocks(c) : 1;  // the first tier's partials go by block index
-    if ((st = dev_alloc(c, &T.partial, bufs * (size_t)std::max(1, T.nslots) * c->G * T.P)) != RTA_OK)
-      return st;
+    if (t == 0 && c->tiled) {
+      if (T.nslots > tile_plan(c).slots) return RTA_E_STATE;
+      continue;
+    }
+    if ((st = alloc_partial(c, T, T.nslots)) != RTA_OK) return st;
   }
   if ((st = dev_alloc(c, &c->hist, (size_t)c->Q * c->hist_len)) != RTA_OK) return st;
 
@@ -2256,13 +2273,16 @@ bool tuning_ok(const rta_tuning* tuning) {
            tuning->spectra_loads < 0 || tuning->spectra_loads > 2);
 }
 
-int create_ctx(rta_ctx** out, double fs, int32_t block, const std::vector<int>& size,
-               const std::vector<int>& count, int32_t n_in, int32_t n_out,
-               const float* const* filters, const int64_t* lengths, int32_t spectra,
-               uint32_t flags, const rta_tuning* tuning, const rta_serve_config* cfg,
-               int min_ring = 1, int tail_p0 = 2) {
+// kept: blocks whose partial sums the context keeps, or would have kept
+int create_with(rta_ctx** out, double fs, int32_t block, const std::vector<int>& size,
+                const std::vector<int>& count, int32_t n_in, int32_t n_out,
+                const float* const* filters, const int64_t* lengths, int32_t spectra,
+                uint32_t flags, const rta_tuning* tuning, const rta_serve_config* cfg,
+                int min_ring, int tail_p0, int max_sums, int* kept) {
+  *kept = 2;
   rta_ctx* c = new (std::nothrow) rta_ctx();
   if (c == nullptr) return RTA_E_NOMEM;
+  c->max_sums = max_sums;
   c->min_ring = min_ring;
   c->tail_p0 = tail_p0;
   c->fs = fs;
@@ -2312,6 +2332,7 @@ int create_ctx(rta_ctx** out, double fs, int32_t block, const std::vector<int>& 
     c->serve->slots.resize((size_t)n_in);
   }
   const int st = create_impl(c, size, count, filters, lengths);
+  *kept = partial_blocks(c);
   if (st != RTA_OK) {
     free_all(c);
     delete c;
@@ -2319,6 +2340,21 @@ int create_ctx(rta_ctx** out, double fs, int32_t block, const std::vector<int>& 
   }
   *out = c;
   return RTA_OK;
+}
+
+// Partial sums of many blocks buy speed, not function: a context that does not
+// fit in memory with them is made with those of fewer blocks (no kBatch blocks
+// at once in graphs, then every row read every block).
+int create_ctx(rta_ctx** out, double fs, int32_t block, const std::vector<int>& size,
+               const std::vector<int>& count, int32_t n_in, int32_t n_out,
+               const float* const* filters, const int64_t* lengths, int32_t spectra,
+               uint32_t flags, const rta_tuning* tuning, const rta_serve_config* cfg,
+               int min_ring = 1, int tail_p0 = 2) {
+  for (int sums = 2 * kBatch, kept;; sums = kept > 2 * kTile ? 2 * kTile : 2) {
+    const int st = create_with(out, fs, block, size, count, n_in, n_out, filters, lengths, spectra, flags, tuning,
+                               cfg, min_ring, tail_p0, sums, &kept);
+    if (st != RTA_E_NOMEM || kept <= 2) return st;
+  }
 }
 
 }  // namespace

@@ -136,3 +136,64 @@ def test_near_rows_of_many_outputs_take_the_whole_chip(rta):
         plain = block_us(cv)
     say(f"  tiled {tiled:.1f} us, every row every block {plain:.1f} us")
     assert tiled < 1.4 * plain
+
+
+def one_filter(B, parts, Q, L, seed):
+    """Q x L paths through the same few filters (host memory for one)."""
+    f = (make_filters(seed, [[B * parts - 3]])[0][0] * 0.1).astype(np.float32)
+    return [[f] * L for _ in range(Q)]
+
+
+def test_tiled_where_only_graphs_lack_room(rta):
+    """64 inputs of 18 partitions: the partial sums of 32 blocks (a graph's 16
+    at once) take more than the spectra, those of 16 do not.  The far rows are
+    then still read once for eight blocks, and a graph runs one block after
+    another."""
+    import torch
+    B, parts, Q, L = 128, 18, 64, 128
+    filt = one_filter(B, parts, Q, L, 770)
+    x = workloads.white_noise(771, Q, 40 * B)
+    xb = torch.from_numpy(np.ascontiguousarray(x.reshape(Q, 40, B).transpose(1, 0, 2))).cuda()
+    with rta.Convolver(filt, B, spectra="fp16") as cv:
+        info = cv.info()
+        # (9 near rows and an eighth of 9 far ones, of 18)
+        assert info["h_bytes_per_block"] == pytest.approx(info["spectra_bytes"] * (9 + 9 / 8) / 18)
+        y = cv.run_device(x)
+        cv.reset()
+        out = torch.empty((20, L, B), device="cuda")
+        with cv.graph(xb[:20].contiguous(), out, 20) as g:
+            g.launch()
+            torch.cuda.synchronize()
+    assert np.array_equal(out.permute(1, 0, 2).reshape(L, -1).cpu().numpy(), y[:, :20 * B])
+    ref = oracle.direct(np.sum(x, axis=0, dtype=np.float64)[None].astype(np.float32), [[filt[0][0]]], 0, x.shape[1])
+    check_db(y[:1], ref, FP16_DB, "64 x 128 of 18 partitions")
+    assert (y == y[0]).all()
+
+
+def test_little_memory_left(rta):
+    """Where the device has no room for the partial sums of 32 blocks, a context
+    is made with fewer: same output, less memory."""
+    import torch
+    B, parts, Q, L = 128, 40, 128, 128
+    filt = one_filter(B, parts, Q, L, 780)
+    x = workloads.white_noise(781, Q, 50 * B)
+    with rta.Convolver(filt, B, spectra="fp16") as cv:
+        full = cv.info()["device_bytes"]
+        y = cv.run_device(x)
+    # room for all but 40 MB of it and of the 64 MB that stage the taps
+    left = full + (64 << 20) - (40 << 20)
+    torch.cuda.empty_cache()
+    hold = []
+    try:
+        for size in (8 << 30, 1 << 30, 64 << 20, 2 << 20):
+            while torch.cuda.mem_get_info()[0] - size >= left:
+                hold.append(torch.empty(size, dtype=torch.uint8, device="cuda"))
+        say(f"free {torch.cuda.mem_get_info()[0] >> 20} MB of {left >> 20}, full context {full >> 20} MB")
+        with rta.Convolver(filt, B, spectra="fp16") as cv:
+            assert cv.info()["device_bytes"] < full
+            del hold[:]
+            torch.cuda.empty_cache()
+            assert np.array_equal(cv.run_device(x), y)
+    finally:
+        del hold[:]
+        torch.cuda.empty_cache()
