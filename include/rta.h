@@ -318,10 +318,13 @@ int rta_process_device(rta_ctx* ctx, const float* d_in, float* d_out,
  *   rta_graph_launch: processes the context's next n_blocks blocks from the
  *     current contents of d_in into d_out, stream-ordered on `stream`
  *     (NULL: the null stream), exactly as n_blocks rta_process_device()
- *     calls would (bit-identical output).  Uniform partitions of 16 to 256
- *     samples (256: FP32 spectra) without feedback paths run up to 16
- *     blocks at once if d_in and d_out do not overlap: all their input has
- *     been read before the first of their output is written.  Mixing with rta_process[_device]
+ *     calls would (bit-identical output).  Runs of three blocks or more go up
+ *     to 16 blocks at once where far rows are read once for eight blocks
+ *     (rta_tuning, tail_rows), partitions are of 16 to 256 samples (256: FP32
+ *     spectra; no RTA_FLAG_NF3), no feedback paths are set, the partial sums of 32
+ *     blocks take no more memory than the spectra or 64 MB, and d_in and
+ *     d_out do not overlap: a block's input is then read again while other
+ *     blocks' output is written.  Mixing with rta_process[_device]
  *     is allowed as long as the context's block index is a multiple of
  *     n_phases away from where the graph was captured (RTA_E_STATE
  *     otherwise); if other launches moved the index since the last replay, a

@@ -31,6 +31,7 @@
 
 #include "rta.h"
 #include "arena.hpp"
+#include "batch.hpp"
 #include "kernels.hpp"
 
 using namespace rta;
@@ -42,7 +43,6 @@ constexpr int kMaxBlock = 4096;
 constexpr int kXcds = 8;                     // MI355X: 8 XCDs, workgroups round-robin
 constexpr int64_t kStageBytes = 64ll << 20;  // filter taps staged per spectra batch
 constexpr size_t kMaxTimedBlocks = 65536;
-constexpr int kBatch = 16;                   // blocks that graph replay runs at once (see graph_batch)
 
 // Scratch of rta_serve_admit_noalloc: the staging of one admission's filter
 // spectra build -- an FP16 range flag, the row table and the staged taps --
@@ -2640,11 +2640,15 @@ int rta_graph_create(rta_ctx* c, const float* d_in, float* d_out, int32_t n_bloc
   hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
   if (e == hipSuccess) {
     int32_t j = 0;
-    for (; batched && j < n_blocks && e == hipSuccess; j += kBatch)
-      e = graph_batch(c, d_in + (int64_t)j * c->Q * c->B, d_out + (int64_t)j * c->L * c->B, j,
-                      std::min(kBatch, n_blocks - j), cs);
-    for (; !batched && j < n_blocks && e == hipSuccess; ++j) {
-      KArgs a = make_args(c, d_in + (int64_t)j * c->Q * c->B, d_out + (int64_t)j * c->L * c->B, j);
+    for (int32_t nb; j < n_blocks && e == hipSuccess; j += nb) {
+      const float* in = d_in + (int64_t)j * c->Q * c->B;
+      float* out = d_out + (int64_t)j * c->L * c->B;
+      nb = graph_run(batched, n_blocks - j);
+      if (nb > 1) {
+        e = graph_batch(c, in, out, j, nb, cs);
+        continue;
+      }
+      KArgs a = make_args(c, in, out, j);
       a.n_base = c->n_dev;
       unsigned grid = 0;
       size_t lds = 0;
