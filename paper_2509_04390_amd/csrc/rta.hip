@@ -1338,12 +1338,17 @@ int launch_block(rta_ctx* c, const float* in, float* out, hipStream_t s, bool fl
   KArgs a = make_args(c, in, out, c->block);
   if (flag) {
     a.done_flag = c->m_flag;
-    // a real-time block: its output first, when the tails stream enough to
-    // slow the heads down (measured: 1 -> 32 x 480,000 taps FP32 paced p50
-    // 41 -> 33 us, 1 -> 64 x 576,000 taps 56 -> 41 us; with the 11 MB per
-    // block of the 4 -> 64 NUPC workload the waiting tails' polls cost more
-    // than they saved)
-    a.tails_wait = c->h_bytes >= 32e6 ? 1 : 0;
+    // a real-time block: its output first, when the tails stream enough to slow
+    // the heads down.  Those that read every row every block do (us without and
+    // with the wait, paced p50 / back to back: 1 -> 32 x 480,000 taps FP32 with
+    // tail_rows set, 123 MB per block, 31.4 -> 26.1 / 25.5 -> 31.3), unless the
+    // polls cost more than they save (4 -> 64, 128/1024/8192 FP16, 11 MB: 23.7
+    // -> 24.5 / 17.6 -> 19.5).  Tiled ones stream an eighth and compute the rest
+    // of the time, so nothing is gained and the next block starts later (1 ->
+    // 64 x 576,000 FP32, 37 MB: 24.8 -> 24.1 / 19.2 -> 23.9; 4 -> 64 x 576,000
+    // FP16, 75 MB: 24.6 -> 24.7 / 32.0 -> 39.2; 16 served sources -> 64 x
+    // 576,000 FP16: 29.1 -> 29.4 / 101.7 -> 111.3).
+    a.tails_wait = !c->tiled && c->h_bytes >= 32e6 ? 1 : 0;
   }
   unsigned grid = 0;
   size_t lds = 0;
@@ -1639,6 +1644,26 @@ void choose_tiling(rta_ctx* c) {
   if (c->batch_ok) T.K += kBatch;
 }
 
+// Bytes that a tiled context streams per block (rta_info), from the partitions
+// of its pairs: far rows once in kTile blocks, and so their delay-line slots.
+void tiled_bytes(const rta_ctx* c, double* h, double* x, double* tail) {
+  const TierHost& T = c->tier[0];
+  const double row = (double)T.P * spectra_elem_bytes(c->dtype);
+  auto streamed = [](int kp) { return std::min(kp, kTile + 1) + std::max(0, kp - kTile - 1) / (double)kTile; };
+  *h = *x = *tail = 0;
+  for (int q = 0; q < c->Q; ++q) {
+    int kmax = c->serve != nullptr ? 0 : T.parts;  // (its source's; a convolver's longest of all)
+    for (int l = 0; l < c->L; ++l) {
+      const int kp = T.kp[(size_t)l * c->Q + q];
+      *h += streamed(kp) * row;
+      *tail += std::max(0.0, streamed(kp) - 2) * row;
+      kmax = std::max(kmax, kp);
+    }
+    *x += streamed(kmax) * T.P * 8.0;
+    *tail += std::max(0.0, streamed(kmax) - 2) * T.P * 8.0;
+  }
+}
+
 // Partial sums of a tier's `slots` slots (the first tier's go by block index).
 int alloc_partial(rta_ctx* c, TierHost& T, int64_t slots) {
   const size_t bufs = &T == &c->tier[0] ? partial_blocks(c) : 1;
@@ -1765,20 +1790,7 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
   int max_lds = 0;
   HIP_TRY(c, hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device));
 
-  if (c->tiled && sv == nullptr) {  // far rows are streamed once in kTile blocks, and so are their delay-line slots
-    const TierHost& T = c->tier[0];
-    auto streamed = [](int kp) { return std::min(kp, kTile + 1) + std::max(0, kp - kTile - 1) / (double)kTile; };
-    double rows = 0, tail_rows = 0;
-    int kmax = 0;
-    for (int32_t kp : T.kp) {
-      rows += streamed(kp);
-      tail_rows += std::max(0.0, streamed(kp) - 2);
-      kmax = std::max(kmax, (int)kp);
-    }
-    c->h_bytes = rows * T.P * eb;
-    c->x_bytes = (double)c->Q * streamed(kmax) * T.P * 8.0;
-    c->tail_bytes = tail_rows * T.P * eb + (double)c->Q * std::max(0.0, streamed(kmax) - 2) * T.P * 8.0;
-  }
+  if (c->tiled && sv == nullptr) tiled_bytes(c, &c->h_bytes, &c->x_bytes, &c->tail_bytes);
 
   // work lists
   Plan plan;
@@ -2057,6 +2069,7 @@ int commit_plan(rta_ctx* c, std::vector<int> states, bool gather, F after) {
     for (int k : kq) xr += std::max(0, k - 2);
     tmp.tb = tail_rows * T.P * ebytes + xr * T.P * 8.0;
   }
+  if (c->tiled) tiled_bytes(c, &tmp.hb, &tmp.xb, &tmp.tb);  // (admission's budget counts every row once)
   Plan plan;
   if ((st = build_plan(c, plan)) != RTA_OK) return st;
 

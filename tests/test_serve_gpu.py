@@ -276,3 +276,23 @@ def test_serving_with_feedback_cancellation_matches_oracle(rta, B, scheme, spect
     say(f"  {rec}; |c| / |m - c| = {g:.3f}, bound {bound:.1f} dB")
     assert g > 0.01, "the feedback estimate must matter"
     check_db(y, l_ref, bound, f"serving + feedback B={B} {spectra}")
+
+def test_streamed_bytes_of_a_server(rta):
+    """rta_info counts a server's bytes as a convolver's: what a block streams
+    (far rows once for eight blocks); admission's budget goes on counting every
+    row."""
+    B, L, K = 64, 4, 50
+    src = make_sources(95, {k: [B * K, B * 30, 0, 700] for k in "AB"}, B)
+    def rows(near):  # of one source: near ones, and an eighth of the far ones
+        return sum(min(k, 9) + max(0, k - 9) / 8 if near else k for k in (K, 30, 0, 11))
+    with rta.Server(3, L, B * K, B) as srv:
+        for name in "AB":
+            srv.admit(src[name][0])
+        srv.process(np.zeros((3, B), np.float32))
+        info = rta.rta_query(srv.ctx)
+        assert info["h_bytes_per_block"] == pytest.approx(2 * rows(True) * B * 8)
+        assert info["x_bytes_per_block"] == pytest.approx(2 * (9 + (K - 9) / 8) * B * 8)
+        assert srv.query()[0]["bytes_per_block"] == pytest.approx(2 * (rows(False) + K) * B * 8)
+    with rta.Convolver([src["A"][0], src["B"][0]], B) as cv:
+        assert cv.info()["h_bytes_per_block"] == info["h_bytes_per_block"]
+        assert cv.info()["x_bytes_per_block"] == info["x_bytes_per_block"]
