@@ -455,8 +455,9 @@ int rta_probe_read(const void* d_buf, int64_t bytes, int32_t grid, float* d_sink
  *
  * Release (rta_serve_release) stops the slot's input at the next block
  * boundary (stop_block); the slot keeps streaming its filters until every
- * delay line, history sample and partial sum it owns has returned to zero
- * (free_block), then becomes free and its arena rows are reused.
+ * delay line and history sample it owns, and every partial sum of blocks to
+ * come, has returned to zero (free_block), then becomes free and its arena
+ * rows are reused.
  * Its output tail (the filter's reverberation) is thus played out in full.
  *
  * Threads: one thread may run rta_process / rta_process_device while one

@@ -2373,6 +2373,15 @@ __global__ __launch_bounds__(64) void k_batch_in(const KArgs args) {
   }
 }
 
+// Clears partial-sum slots `list` of every block kept: workgroup (i, b) the
+// n values of slot list[i] of block position b (serving, when a work list
+// drops the items that wrote them).
+__global__ __launch_bounds__(kThreads) void k_clear_slots(float2* partial, const int32_t* list, int32_t nslots,
+                                                          int32_t n) {
+  float2* p = partial + ((int64_t)blockIdx.y * nslots + list[blockIdx.x]) * n;
+  for (int i = threadIdx.x; i < n; i += kThreads) p[i] = make_float2(0.f, 0.f);
+}
+
 // Graph replay's device block counter: set to v (add = 0), or advanced by v
 // (add = 1) by the graph's last node.
 // ctr[0] is the block index, ctr[1] and ctr[2] its slots in delay lines of K

@@ -211,6 +211,11 @@ struct ServeSlot {
   int state = RTA_SLOT_FREE;
   bool rows_held = false;  // arena rows not yet returned
   int64_t start = -1, stop = -1, free_at = -1, taps = 0;
+  // Tiled: the partial sums of blocks kept hold values of the slot's earlier
+  // sources until block sums_until (-1: none), in the chunks of up to sums_k
+  // partitions.
+  int64_t sums_until = -1;
+  int sums_k = 0;
   double hb = 0, xb = 0, cm = 0;           // per-block figures of the source
   std::vector<int64_t> row[kMaxTiers];     // [l] first arena row, -1 = none
   std::vector<int32_t> kp[kMaxTiers];      // [l] partitions
@@ -224,6 +229,8 @@ struct PlanDev {  // one of the two work-list buffers
   int64_t* pair_row[kMaxTiers] = {};
   int32_t* pair_K[kMaxTiers] = {};
   int32_t* live = nullptr;
+  int32_t* stale = nullptr;  // tiled: first-tier slots to clear when the list is switched to
+  int n_stale = 0;
   std::vector<int32_t> tier_count_host, block_count_host;
   int grid_items = 0;
   double hb = 0, xb = 0, cm = 0, tb = 0;
@@ -1266,18 +1273,18 @@ int64_t floor_div(int64_t a, int64_t b) { return a >= 0 ? a / b : -((-a + b - 1)
 
 // Serving: first block from which a slot whose input stopped at block m owns
 // only zeros -- its delay lines of every tier, input history and partial
-// sums -- so its work items can be dropped and its rows reused.  Tier t's
+// sums, the first tier's of the last `sums` blocks -- so its work items can be
+// dropped and its rows reused.  Tier t's
 // frames f <= f_last see input before m; frame f_last + K_t is the first
 // whose delay line is all zero, and its slots are rewritten (with zeros) by
 // the time its final step has run.
-int64_t drain_end(const rta_ctx* c, int64_t m) {
+int64_t drain_end(const rta_ctx* c, int64_t m, int sums) {
   int64_t end = m;
   for (int t = 0; t < c->n_tiers; ++t) {
     const TierHost& T = c->tier[t];
     const int64_t P = T.P, r = T.P / c->B;
     const int64_t fl = floor_div(m * c->B - 1, P) + 1;
-    // (first tier: until the partial sums of every block kept are zero too)
-    const int64_t e = t == 0 ? fl + T.K + partial_blocks(c) - 1 : (fl + T.K + 1) * r + tier_nmac(c, t) + 3;
+    const int64_t e = t == 0 ? fl + T.K + sums - 1 : (fl + T.K + 1) * r + tier_nmac(c, t) + 3;
     end = std::max(end, e + 1);
   }
   return end;
@@ -1296,7 +1303,14 @@ int serve_boundary(rta_ctx* c, hipStream_t s) {
     sv->active ^= 1;
     sv->pending = false;
     ++sv->swaps;
-    activate(c, sv->dev[sv->active]);
+    const PlanDev& d = sv->dev[sv->active];
+    activate(c, d);
+    if (d.n_stale > 0) {  // before the block, whose heads read all slots of their group
+      const TierHost& T = c->tier[0];
+      hipLaunchKernelGGL(k_clear_slots, dim3((unsigned)d.n_stale, (unsigned)partial_blocks(c)), dim3(kThreads), 0, s,
+                         T.partial, d.stale, T.nslots, c->G * T.P);
+      HIP_TRY(c, hipGetLastError());
+    }
     for (ServeSlot& sl : sv->slots) {
       if (sl.state == RTA_SLOT_JOINING) {
         sl.state = RTA_SLOT_LIVE;
@@ -1304,12 +1318,19 @@ int serve_boundary(rta_ctx* c, hipStream_t s) {
       } else if (sl.state == RTA_SLOT_LEAVING) {
         sl.state = RTA_SLOT_DRAINING;
         sl.stop = c->block;
-        sl.free_at = drain_end(c, c->block);
+        // The source's terms have ended by then: with two blocks of sums kept,
+        // so have its sums; with more, those of later blocks' positions are
+        // overwritten by then if its items go on, and cleared if a list drops
+        // them (commit_plan).
+        sl.free_at = drain_end(c, c->block, 2);
+        if (c->tiled) sl.sums_until = drain_end(c, c->block, partial_blocks(c));
       }
     }
   }
-  for (ServeSlot& sl : sv->slots)
+  for (ServeSlot& sl : sv->slots) {
     if (sl.state == RTA_SLOT_DRAINING && c->block >= sl.free_at) sl.state = RTA_SLOT_FREE;
+    if (sl.sums_until >= 0 && c->block >= sl.sums_until) sl.sums_until = -1;
+  }
   return RTA_OK;
 }
 
@@ -1606,6 +1627,7 @@ int serve_lists(rta_ctx* c, Plan& plan) {
       if ((st = dev_alloc(c, &d.pair_K[t], c->tier[t].kp.size())) != RTA_OK) return st;
     }
     if ((st = dev_alloc(c, &d.live, (size_t)c->Q)) != RTA_OK) return st;
+    if (c->tiled && (st = dev_alloc(c, &d.stale, (size_t)c->tier[0].nslots)) != RTA_OK) return st;
   }
   const std::vector<int32_t> live((size_t)c->Q, 0);
   if ((st = upload_plan(c, plan, sv->dev[0], live, c->stream)) != RTA_OK) return st;
@@ -2023,6 +2045,37 @@ void reclaim(Serve* sv, int n_tiers) {
   }
 }
 
+// Tiled: the first-tier partial slots that held sums of the sources in
+// `left` (input, partitions) and that no item of `plan` writes.  While an item
+// writes a slot, each block's sum is there before the block needs it; without
+// one, sums of up to partial_blocks() blocks ago would be taken for later
+// blocks'.  Every source that such a slot belongs to has drained, so zero is
+// its sum for the block at which the list is switched to, and from then on.
+std::vector<int32_t> stale_slots(const rta_ctx* c, const Plan& plan,
+                                 const std::vector<std::pair<int, int>>& left) {
+  std::vector<int32_t> out;
+  if (left.empty()) return out;
+  const TilePlan t = tile_plan(c);
+  std::vector<char> done((size_t)c->tier[0].nslots, 0);  // written by an item, or in `out`
+  for (const auto& list : plan.block)
+    for (const Item& it : list)
+      if (it.kind == K_NEAR || it.kind == K_TILE) done[it.slot] = 1;
+  auto add = [&](int slot) {
+    if (!done[slot]) out.push_back(slot);
+    done[slot] = 1;
+  };
+  for (int g = 0; g < (int)plan.groups.size(); ++g)
+    for (const auto& l : left) {
+      const int q = l.first, k = l.second;
+      if (k > c->tail_p0) add(plan.groups[g].slot0 + q / kNearInputs);
+      int slot = plan.groups[g].slot0 + near_slots(c);  // (the layout of tile_items)
+      for (int q0 = 0; q0 + t.span <= q; q0 += t.span) slot += far_chunks(c, t, g, q0);
+      const int cap = far_chunks(c, t, g, q / t.span * t.span);
+      for (int ch = 0; ch < cap && kTile + 1 + ch * t.rows < k; ++ch) add(slot + ch);
+    }
+  return out;
+}
+
 // Build the work list for the slot states `states` (one slot may be given a
 // state it will take when the list is published), write it into the
 // buffer launches are not reading, and publish it: the next block switches
@@ -2075,8 +2128,11 @@ int commit_plan(rta_ctx* c, std::vector<int> states, bool gather, F after) {
 
   int target;
   bool wait = false;
+  std::vector<std::pair<int, int>> left;  // whose sums may not have been overwritten yet
   {
     std::lock_guard<std::mutex> lk(sv->mu);
+    for (int q = 0; q < Q; ++q)
+      if (sv->slots[q].sums_until >= 0) left.push_back({q, sv->slots[q].sums_k});
     target = sv->active ^ 1;
     if (sv->pending)
       sv->pending = false;  // the other buffer was published but not yet read
@@ -2085,6 +2141,10 @@ int commit_plan(rta_ctx* c, std::vector<int> states, bool gather, F after) {
   }
   if (wait) HIP_TRY(c, hipEventSynchronize(sv->retire[target]));
   PlanDev& d = sv->dev[target];
+  const std::vector<int32_t> stale = stale_slots(c, plan, left);
+  d.n_stale = (int)stale.size();
+  if (!stale.empty())  // (before upload_plan, which waits for the stream)
+    HIP_TRY(c, hipMemcpyAsync(d.stale, stale.data(), sizeof(int32_t) * stale.size(), hipMemcpyHostToDevice, sv->aux));
   if ((st = upload_plan(c, plan, d, live, sv->aux)) != RTA_OK) return st;
   if (gather) {
     TierHost T0 = c->tier[0];
@@ -2243,7 +2303,12 @@ int serve_release(rta_ctx* c, int32_t q) {
   std::vector<int> states = slot_states(sv);
   if (states[q] != RTA_SLOT_JOINING && states[q] != RTA_SLOT_LIVE) return RTA_E_STATE;
   states[q] = RTA_SLOT_LEAVING;
-  return commit_plan(c, states, false, [&]() { sv->slots[q].state = RTA_SLOT_LEAVING; });
+  return commit_plan(c, states, false, [&]() {
+    ServeSlot& sl = sv->slots[q];
+    sl.state = RTA_SLOT_LEAVING;
+    if (sl.sums_until < 0) sl.sums_k = 0;
+    for (int32_t k : sl.kp[0]) sl.sums_k = std::max(sl.sums_k, (int)k);
+  });
 }
 
 // rta_reset for a serving context: the device is idle; zero the state, keep
@@ -2261,6 +2326,7 @@ int serve_reset(rta_ctx* c) {
       } else if (sl.state != RTA_SLOT_FREE) {
         sl.state = RTA_SLOT_FREE;
       }
+      sl.sums_until = -1;  // (zero_state)
     }
   }
   reclaim(sv, c->n_tiers);

@@ -296,3 +296,46 @@ def test_streamed_bytes_of_a_server(rta):
     with rta.Convolver([src["A"][0], src["B"][0]], B) as cv:
         assert cv.info()["h_bytes_per_block"] == info["h_bytes_per_block"]
         assert cv.info()["x_bytes_per_block"] == info["x_bytes_per_block"]
+
+
+@pytest.mark.parametrize("K", [12, 40])
+def test_a_slot_is_free_once_its_last_term_has_sounded(rta, K):
+    """A released source's last partition pairs with its last spectrum K blocks
+    after it, whether far rows are read every block (K = 12) or once for eight
+    blocks (K = 40, partial sums of 16 blocks).  The slot is free two blocks
+    later, and a shorter source admitted at once hears nothing of the sums that
+    the longer one left behind."""
+    B, L, n_blocks = 32, 2, 50 + 2 * K + 30
+    src = make_sources(90 + K, {"A": [B * K, B * (K - 9) - 3], "B": [B * 3 + 5, 40]}, n_blocks * B)
+    events = {0: [("admit", "A")], 50: [("release", "A")], 51: [("admit", "B")]}
+    with rta.Server(1, L, B * K, B) as srv:
+        y, rec, _ = run_scenario(rta, srv, src, events, n_blocks, retry=("B",))
+    # (the block that finds the slot free, K + 2 after the stop, then the first
+    # block that could hear the new source)
+    assert rec["B"][1] == 50 + K + 3, rec
+    check_db(y, reference(src, rec, L, B, n_blocks * B), FP32_DB, f"slot reuse K={K}")
+
+
+def test_sources_that_share_far_slots(rta):
+    """40 slots, all taken: far items take several inputs each.  Sources join at
+    eight block residues; the longest of some shared slots leave while their
+    neighbours play, and shorter and longer ones take their places at once."""
+    B, L, K, n_slots, n_blocks = 64, 2, 60, 40, 170
+    rng = np.random.default_rng(97)
+    lens = {"s%02d" % i: [int(rng.integers(20 * B, K * B)), int(rng.integers(0, 30 * B))] for i in range(n_slots)}
+    for name in ("s00", "s07", "s20", "s21"):
+        lens[name] = [K * B, 35 * B]
+    lens.update(t0=[22 * B, 300], t1=[K * B - 1, 0], t2=[100, 57 * B], t3=[19 * B, 18 * B])
+    src = make_sources(98, lens, n_blocks * B)
+    events = {}
+    for i in range(n_slots):
+        events.setdefault(i // 5, []).append(("admit", "s%02d" % i))
+    for n, name in ((12, "s00"), (13, "s07"), (17, "s20"), (17, "s21")):
+        events.setdefault(n, []).append(("release", name))
+    for n, name in ((20, "t0"), (21, "t1"), (22, "t2"), (23, "t3")):
+        events.setdefault(n, []).append(("admit", name))
+    events.setdefault(100, []).extend([("release", "t2"), ("release", "s08")])
+    with rta.Server(n_slots, L, K * B, B) as srv:
+        y, rec, refused = run_scenario(rta, srv, src, events, n_blocks, retry=("t0", "t1", "t2", "t3"))
+    assert refused > 0 and sorted(rec[t][0] for t in ("t0", "t1", "t2", "t3")) == [0, 7, 20, 21]
+    check_db(y, reference(src, rec, L, B, n_blocks * B), FP32_DB, "shared far slots")
