@@ -8,7 +8,7 @@ import pytest
 import oracle
 from paper_2509_04390_amd import workloads
 
-from test_parity_gpu import FP32_DB, check_db, make_filters, say
+from test_parity_gpu import BF16_DB, FP16_DB, FP32_DB, check_db, make_filters, say
 
 pytestmark = pytest.mark.gpu
 
@@ -78,3 +78,33 @@ def test_unaligned_device_buffers(rta, B):
             cv.process_device(buf[1:1 + 2 * B], out[3:3 + 2 * B])
             got[:, b * B:(b + 1) * B] = out[3:3 + 2 * B].reshape(2, B).cpu().numpy()
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("B,spectra,flags", [(256, "fp16", 0), (256, "bf16", 0), (512, "fp32", 0), (1024, "fp16", 0),
+                                             (16, "fp32", 2), (32, "fp16", 2), (128, "fp32", 2), (512, "fp32", 2)])
+@pytest.mark.parametrize("Q,rows", [(1, 40), (4, 17), (5, 9), (9, 4)])
+def test_workgroup_heads(rta, B, spectra, flags, Q, rows):
+    """Heads that run by workgroups: inputs and partial slots that are whole and
+    broken multiples of those a thread has in flight (rows partitions read one
+    to an item), plain and as feedback heads of Q outputs."""
+    L = 3
+    lens = [[max(1, B * rows - 7 * q - 3 * l) for l in range(L)] for q in range(Q)]
+    filt = [[(f / 64).astype(np.float32) for f in row] for row in make_filters(870 + Q, lens)]
+    n = B * (rows + 6)
+    x = workloads.white_noise(871, Q, n)
+    limit = {"fp32": FP32_DB, "fp16": FP16_DB, "bf16": BF16_DB}[spectra]
+    say(f"B={B} Q={Q} rows={rows} {spectra} flags={flags}")
+    with rta.Convolver(filt, B, spectra=spectra, flags=flags, tuning=rta.make_tuning(tail_rows=1)) as cv:
+        y = cv.run(x)
+        cv.reset()
+        assert np.array_equal(cv.run_device(x), y)
+    check_db(y, oracle.direct(x, filt, 0, n), limit, f"B={B} Q={Q} rows={rows}")
+    # outputs of this room fed back into L microphones (loop gain about 0.1)
+    fb = [[(0.004 * f).astype(np.float32) for f in row] for row in make_filters(872, [[B * 3 + q for q in range(Q)]] * L)]
+    room = [[filt[q][l] for q in range(Q)] for l in range(L)]
+    m = workloads.white_noise(873, L, n)
+    with rta.Convolver(room, B, spectra=spectra, flags=flags) as cv:
+        cv.set_feedback(fb, spectra=spectra)
+        assert cv.info()["feedback_fused"] == 1
+        y = cv.run_device(m)
+    check_db(y, oracle.feedback_loop(m, room, fb, B)[0], limit, f"feedback B={B} Q={Q}")
