@@ -212,10 +212,10 @@ int rta_create(rta_ctx** out, double fs, int32_t block,
  *                      of rows each; rta_info reports the choice).
  *   spectra_loads      how the multiply-accumulate streams the spectra:
  *                      1 = non-temporal loads, 2 = ordinary loads, 0 =
- *                      default (ordinary for uniform partitions, which
- *                      re-read every row every block, up to 384 MB of
- *                      spectra; non-temporal beyond that, with later tiers
- *                      and for serving contexts).
+ *                      default (ordinary for 16-bit spectra whose far rows
+ *                      are read once for eight blocks, and for other uniform
+ *                      partitions up to 384 MB of spectra; non-temporal beyond
+ *                      that, with later tiers and for other serving contexts).
  * rta_autotune() also fills the scheme it selected (n_tiers, size, count). */
 typedef struct rta_tuning {
     int32_t outputs_per_group;

@@ -1895,15 +1895,19 @@ int create_impl(rta_ctx* c, const std::vector<int>& size, const std::vector<int>
   // LDS: the larger of a head's layout (HeadLds) and a tail item's row-group
   // reduction.  head_nq: as many inputs per pass as fit in 48 KB, at least 1.
   const int C = vec_bins(c->dtype);
-  // uniform partitions re-read every spectrum row every block: ordinary
-  // loads stream them faster up to a few hundred MB (measured with 61 to
-  // 295 MB of spectra, inside and beyond the 256 MB Infinity Cache), while
-  // 443 MB (4 -> 64 x U[3,12] s FP16) went faster non-temporal; later tiers
-  // touch their rows once per frame, and serving contexts stream whatever
-  // is admitted: non-temporal loads there
+  // Ordinary or non-temporal loads of the spectra.  Uniform partitions: ordinary
+  // up to a few hundred MB (inside and beyond the 256 MB Infinity Cache).  Tiled
+  // 16-bit ones: ordinary at any size, as two workgroups and more read a far
+  // line about at once; FP32 gains in graphs what it loses alone (us per block,
+  // ordinary / non-temporal, alone and in graphs: 1 -> 64 x 576,000 FP16, 147 MB,
+  // 12.4 / 13.5, 9.3 / 10.4; 4 -> 64, 590 MB, 29.3 / 29.8, 20.7 / 23.1; 16 served
+  // sources, 2.4 GB, 89.3 / 95.4; 1 -> 64 FP32, 295 MB, 18.0 / 17.3, 12.2 / 12.6;
+  // 2 -> 64, 590 MB, 24.9 / 24.2, 16.5 / 17.5).  Later tiers touch their rows
+  // once per frame, and other serving contexts stream whatever is admitted:
+  // non-temporal.
   c->nt = c->spectra_loads == 1 ||
-          (c->spectra_loads == 0 && (c->serve != nullptr || c->n_tiers > 1 ||
-                                     c->spectra_bytes > (int64_t(384) << 20)));
+          (c->spectra_loads == 0 && !(c->tiled && c->dtype != RTA_FP32) &&
+           (c->serve != nullptr || c->n_tiers > 1 || c->spectra_bytes > (int64_t(384) << 20)));
   const int P0 = c->tier[0].P;
   const int fixed = head_lds(P0, 1, 1).total - 2 * P0;
   c->head_nq = std::max(1, std::min(c->Q, (6144 - fixed) / (2 * P0)));
