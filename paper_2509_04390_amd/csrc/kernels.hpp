@@ -527,7 +527,12 @@ __device__ __forceinline__ void mac_near(const DevTier& T, const Item& it, int64
 // for 4 kTile multiply-adds per output; kTile rows are in flight per lane.
 // Where an output has many inputs with few partitions each, an item takes
 // several inputs, one after another, into its one slot.
-// Bound by the VALU: 4 multiply-adds per (bin, row, block, output).  16-bit
+// Work: 4 multiply-adds per (bin, row, block, output).  Bound by its loads'
+// latency and the VALU about equally: counters of the tails of 16 blocks, 1 ->
+// 32 x 480,000 taps FP32 (73 us): 54% of the VALU instructions are those
+// multiply-adds, the VALU is busy about 60% of the time, wavefronts wait 41% of
+// theirs (8 rows per run: 15 spectra for one step, then 16 runs added up in LDS);
+// 16 served sources -> 64 x 576,000 FP16: they wait 49%.  16-bit
 // spectra are converted once per row: left to itself the compiler folds the
 // conversion into every multiply-add (v_fma_mix_f32), which runs at half the
 // rate (1 -> 64 x 576,000 taps FP16: launch 13.8 -> 11.2 us).

@@ -511,10 +511,11 @@ void add_to_bucket(std::vector<Bucket>& buckets, const Item& it, int nl, int uni
 //     of several steps (1 s feedback paths of 32 outputs into one microphone:
 //     16 items of 18 us each on the launch's critical path).
 //   - Every (output group, span inputs, chunk) owns a partial slot.  A chunk
-//     has 8 rows per run, longer ones until a group's slots are within what a
-//     head adds up from registers (HeadRed; within 32 where it adds them up in
-//     a loop) and a launch's items within tail_items and a half; then an item
-//     takes several inputs.
+//     has 8 rows per run, longer ones until a group's slots are within 16 per
+//     256 / P threads of a bin, which is what heads request up front (head_wave:
+//     slot_shares times its SL; HeadRed), or within 32 where there are more than
+//     four inputs to such a thread, and a launch's items within tail_items and a
+//     half; then an item takes several inputs.
 //   - The items of one chunk and `unit` output groups are read in the same
 //     launch on one XCD (they share their delay-line rows): as many groups as
 //     leave every XCD of every launch two units.
@@ -760,9 +761,9 @@ int build_plan(rta_ctx* c, Plan& plan) {
     if (R <= 0) {
       const int64_t target_items = std::max(1, c->tail_items);
       R = (int)std::max<int64_t>(8, (total_rows * nslice + target_items - 1) / target_items);
-      // Slots per output group within what a head adds up from registers
-      // while it transforms its window (HeadRed: 16 slots per thread, 256 / P
-      // threads per bin): with few outputs and long filters the item count
+      // Slots per output group within what a head requests up front, before it
+      // transforms its window (16 slots per thread, 256 / P threads per bin:
+      // HeadRed, and head_wave's shares come to the same): with few outputs and long filters the item count
       // above would give one group hundreds of slots, and its head would
       // reduce them after the transform.  Rows per item grow to the cap; with
       // automatic slices, narrower bin ranges then cut the items back to
