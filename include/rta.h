@@ -285,11 +285,12 @@ int rta_autotune_cached(const char* cache_path, double fs, int32_t block,
  * flag in pinned memory, on which the call spins before copying the output
  * to `out`.  The multiply-accumulate of partitions >= 2 for the next block,
  * in the same launch, keeps running after the call returns; the next call is
- * stream-ordered after it.  When that multiply-accumulate reads every row
- * every block (see rta_tuning, tail_rows) and streams 32 MB or more per block,
- * its workgroups start only once this block's output workgroups are done
- * (they would slow them down), which shortens this call at no cost to
- * correctness.  Must not be interleaved with rta_process_device()
+ * stream-ordered after it.  When that multiply-accumulate streams 32 MB or
+ * more per block, its workgroups start only once this block's output
+ * workgroups are done (they would slow them down), which shortens this call
+ * at no cost to correctness; not where far rows are read once for eight blocks
+ * (see rta_tuning, tail_rows) and blocks are of 16 to 256 samples (256: FP32
+ * spectra; no RTA_FLAG_NF3), where it gains nothing.  Must not be interleaved with rta_process_device()
  * calls still in flight on another stream. */
 int rta_process(rta_ctx* ctx, const float* in, float* out);
 

@@ -1365,12 +1365,14 @@ int launch_block(rta_ctx* c, const float* in, float* out, hipStream_t s, bool fl
     // with the wait, paced p50 / back to back: 1 -> 32 x 480,000 taps FP32 with
     // tail_rows set, 123 MB per block, 31.4 -> 26.1 / 25.5 -> 31.3), unless the
     // polls cost more than they save (4 -> 64, 128/1024/8192 FP16, 11 MB: 23.7
-    // -> 24.5 / 17.6 -> 19.5).  Tiled ones stream an eighth and compute the rest
-    // of the time, so nothing is gained and the next block starts later (1 ->
-    // 64 x 576,000 FP32, 37 MB: 24.8 -> 24.1 / 19.2 -> 23.9; 4 -> 64 x 576,000
-    // FP16, 75 MB: 24.6 -> 24.7 / 32.0 -> 39.2; 16 served sources -> 64 x
-    // 576,000 FP16: 29.1 -> 29.4 / 101.7 -> 111.3).
-    a.tails_wait = !c->tiled && c->h_bytes >= 32e6 ? 1 : 0;
+    // -> 24.5 / 17.6 -> 19.5).  So do tiled ones beside heads that run by
+    // workgroups (1 -> 128 x 580,000, B = 512 FP32, 78 MB: 75 -> 65 / 69 -> 65; 4 ->
+    // 64 x 576,000, B = 256 FP16: 55 -> 47 / 49 -> 57; 3 -> 50 x 463,048, B = 2048
+    // FP16: 119 -> 100 paced).  Wavefront heads beside tiled tails gain nothing,
+    // and the next block starts later (1 -> 64 x 576,000 FP32, 37 MB: 24.8 -> 24.1 /
+    // 19.2 -> 23.9; 4 -> 64 x 576,000 FP16, 75 MB: 24.6 -> 24.7 / 32.0 -> 39.2; 16
+    // served sources -> 64 x 576,000 FP16: 29.1 -> 29.4 / 101.7 -> 111.3).
+    a.tails_wait = c->h_bytes >= 32e6 && !(c->tiled && wave_heads(c->dtype, c->B, c->tier[0].r3)) ? 1 : 0;
   }
   unsigned grid = 0;
   size_t lds = 0;
