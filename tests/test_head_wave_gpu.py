@@ -8,7 +8,7 @@ import pytest
 import oracle
 from paper_2509_04390_amd import workloads
 
-from test_parity_gpu import BF16_DB, FP16_DB, FP32_DB, check_db, make_filters, say
+from test_parity_gpu import FP32_DB, check_db, make_filters, say
 
 pytestmark = pytest.mark.gpu
 
@@ -78,6 +78,9 @@ def test_unaligned_device_buffers(rta, B):
             cv.process_device(buf[1:1 + 2 * B], out[3:3 + 2 * B])
             got[:, b * B:(b + 1) * B] = out[3:3 + 2 * B].reshape(2, B).cpu().numpy()
     assert np.array_equal(got, want)
+
+
+from test_parity_gpu import BF16_DB, FP16_DB  # noqa: E402
 
 
 @pytest.mark.parametrize("B,spectra,flags", [(256, "fp16", 0), (256, "bf16", 0), (512, "fp32", 0), (1024, "fp16", 0),
